@@ -31,13 +31,25 @@ COMMON = [
 ]
 
 
+# hv.hip holds a few hundred kernel instances: it is compiled in pieces (see
+# EDX_HV_PART there), the pieces first since they take longest
+PARTS = {"hv.hip": 6}
+
+
 def sources():
-    return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
+    """(source, piece or None) of every translation unit."""
+    files = sorted(f for f in os.listdir(CSRC) if f.endswith(".hip"))
+    pieces = [(os.path.join(CSRC, f), k) for f in files for k in range(PARTS.get(f, 0))]
+    return pieces + [(os.path.join(CSRC, f), None) for f in files]
 
 
-def _compile(src, debug):
-    obj = os.path.join(BUILD, os.path.basename(src) + ".o")
+def _compile(unit, debug):
+    src, part = unit
+    name = os.path.basename(src) + ("" if part is None else f".{part}")
+    obj = os.path.join(BUILD, name + ".o")
     cmd = [HIPCC, "-x", "hip", "-c", src, "-o", obj] + COMMON + (["-O1", "-g"] if debug else ["-O3"])
+    if part is not None:
+        cmd.append(f"-DEDX_HV_PART={part}")
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")

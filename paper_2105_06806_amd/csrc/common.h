@@ -30,6 +30,43 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
   return s;
 }
 
+// Reductions folded into the kernel that needs their results: every workgroup
+// (256 threads) sums the partial sums of the previous kernels for itself, in
+// the order of the one-workgroup reduction (threads strided over the partials,
+// wave trees, then the four waves in turn), so the values are the same.
+// fold_load issues the loads of n <= 256 U partials (before the kernel's own
+// loads, so that the latencies overlap); fold_sum2 adds up two such sets at
+// once, valid in every thread; red holds 8 doubles.
+template <int U>
+__device__ __forceinline__ void fold_load(double (&x)[U], const double* __restrict__ part, int n) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = (int)threadIdx.x + 256 * u;
+    x[u] = i < n ? part[i] : 0.0;
+  }
+}
+
+template <int U, int V>
+__device__ __forceinline__ void fold_sum2(const double (&x)[U], const double (&y)[V], double* red,
+                                          double& sx, double& sy) {
+  double s = 0.0, t = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) s += x[u];
+#pragma unroll
+  for (int u = 0; u < V; ++u) t += y[u];
+  s = wave_sum(s);
+  t = wave_sum(t);
+  const int wid = threadIdx.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) {
+    red[wid] = s;
+    red[4 + wid] = t;
+  }
+  __syncthreads();
+  sx = ((red[0] + red[1]) + red[2]) + red[3];
+  sy = ((red[4] + red[5]) + red[6]) + red[7];
+}
+
 // Counter-based SplitMix64 (Steele, Lea and Flood's finaliser): draw k of
 // stream `seed` (the start vectors' element k takes draw k).
 __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t k) {

@@ -190,6 +190,7 @@ edx_status k_transpose(int vtype, const void* src, int64_t rows, int64_t cols, i
                        void* dst, int64_t ldd, int add, hipStream_t st);
 
 // ---- krylov.hip
+constexpr int kMaxElemBlocks = 1024;   // workgroups of the element-wise kernels
 int elem_blocks(int64_t n);
 // random start vector in [-1, 1) of the element with logical index r + c*dup
 // (the same values for every ld); zero in the padding rows.  With src, the
@@ -209,11 +210,23 @@ edx_status k_alpha_finish(const double* partial, int nparts, double* alpha_j,
                           hipStream_t st);
 edx_status k_beta_finish(const double* partial, int nparts, double* beta_next,
                          double* scale_next, hipStream_t st);
-edx_status k_update(int vtype, void* w, const void* vcur, const double* scur,
+// The step's reductions folded into the update: the product's partials of
+// <v, H v>, and, where the product took the unscaled u_j, the partials of
+// |u_j|^2 that the previous step left (nb > 0).  The kernel writes alpha_j, and
+// with nb > 0 beta_j = |u_j| and scale_j = 1/|u_j|, that it otherwise reads.
+// `partial` must overlap neither.
+struct UpdateFold {
+  const double* apart = nullptr;   // na <= kMaxPartials
+  int na = 0;
+  bool unscaled = false;           // w = H u_j (not H v_j)
+  const double* bpart = nullptr;   // nb <= kMaxElemBlocks; nb = 0 unless unscaled
+  int nb = 0;
+};
+edx_status k_update(int vtype, void* w, const void* vcur, double* scur,
                     const void* vprev, const double* sprev,
-                    const double* alpha, const double* beta, int64_t n,
+                    double* alpha, double* beta, int64_t n,
                     void* psi, const double* ycoef, double* partial,
-                    hipStream_t st);
+                    hipStream_t st, const UpdateFold* fold = nullptr);
 edx_status k_norm2(int vtype, const void* x, int64_t n, double* partial,
                    hipStream_t st);
 edx_status k_scale_copy(int vtype, const void* x, const double* scale,

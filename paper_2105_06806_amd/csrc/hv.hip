@@ -56,6 +56,7 @@ struct HvArgs {
   const uint8_t* __restrict__ hrow;   // compact spin-up rows (fused pass) or nullptr
 };
 
+#ifndef EDX_HV_PART
 template <typename T>
 HvArgs<T> make_args(const edx_sector* s, int64_t ld);
 
@@ -71,6 +72,8 @@ HvArgs<float> make_args<float>(const edx_sector* s, int64_t ld) {
                        s->up.e32, s->dw.e32, s->up.pat, s->dw.pat, s->amp32, s->w32,
                        s->hrow};
 }
+
+#endif
 
 // ---------------------------------------------------------------- small
 template <typename T>
@@ -402,6 +405,7 @@ inline int nd_lds_terms(const edx_sector* s) {
   return s->dph > 1 ? s->ph_nt_max : s->nd_nt;
 }
 
+#ifndef EDX_HV_PART
 template <typename T>
 const T* ph_amp(const edx_sector* s);
 template <>
@@ -414,6 +418,8 @@ template <>
 const double* wph<double>(const edx_sector* s) { return s->wph64; }
 template <>
 const float* wph<float>(const edx_sector* s) { return s->wph32; }
+
+#endif
 
 // Holstein terms of one phonon slice p for the fused pass (Sec. "Electron-phonon
 // coupling"): (g(pu) + g(pd)) (sp v_{p-1} + sp1 v_{p+1}) at the element itself,
@@ -431,12 +437,15 @@ __device__ __forceinline__ T gpat(const PhArgs<T>& ph, int pat) {
   return ((pat & 1) ? ph.g0 : T(0)) + ((pat & 2) ? ph.g1 : T(0)) + ((pat & 4) ? ph.g2 : T(0));
 }
 
+#ifndef EDX_HV_PART
 template <typename T>
 const T* nd_amp(const edx_sector* s);
 template <>
 const double* nd_amp<double>(const edx_sector* s) { return s->nd_amp64; }
 template <>
 const float* nd_amp<float>(const edx_sector* s) { return s->nd_amp32; }
+
+#endif
 
 __host__ __device__ constexpr size_t al16(size_t x) { return (x + 15) & ~(size_t)15; }
 
@@ -758,6 +767,101 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
   }
 }
 
+// ---------------------------------------------------------------- fused launches
+template <typename T>
+struct FusedOrder {
+  int order;
+  const int32_t* corder;
+  NdTab<T> nd;   // nd.nt = 0: no spin exchange / pair hopping in this pass
+  bool ph = false;   // phonon slice without H_nd: the direct phonon terms
+  PhArgs<T> pa{};
+};
+
+// The fused pass has one instance per vector type, pair of row widths, columns
+// per workgroup and variant, which take minutes to compile in one piece: the
+// build compiles this file once per (type, spin-up width) with EDX_HV_PART set,
+// for these launchers alone, and once without, for everything else.
+#ifndef EDX_HV_PART
+template <typename T, int WUP, int WDW>
+edx_status launch_fused_c(const HvArgs<T>& a, int ncol, int nblk, int nthr, size_t lds,
+                          hipStream_t st, const T* v, T* w, const double* vscale,
+                          double* partial, FusedOrder<T> fo);
+#else
+namespace {
+
+template <typename T, int WUP, int WDW, int NC, bool ND, bool PH, bool BUF = false>
+edx_status launch_fused_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hipStream_t st,
+                          const T* v, T* w, const double* vscale, double* partial,
+                          FusedOrder<T> fo, const NdTab<T>& nd, uint32_t vbytes = 0) {
+  const void* kern = (const void*)k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>;
+  EDX_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL((k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>), dim3(nblk), dim3(nthr), lds, st,
+                     a, v, w, vscale, partial, fo.order, fo.corder, nd, fo.pa, vbytes);
+  EDX_HIP(hipGetLastError());
+  return EDX_OK;
+}
+
+template <typename T, int WUP, int WDW, int NC>
+edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hipStream_t st,
+                          const T* v, T* w, const double* vscale, double* partial,
+                          FusedOrder<T> fo) {
+  // buffer-load gathers when every byte offset into v (one phonon slice) fits
+  // in 32 bits; the H_nd terms read outside it keep global loads.  The direct
+  // phonon variant keeps global loads throughout (measured 2 % faster so, Ns=14
+  // N_ph=4: 262-267 us against 270-271 us)
+  const uint64_t vb = (uint64_t)a.ld * (uint64_t)a.ddw * sizeof(T);
+  const bool buf = vb <= 0xFFFFFFFFull && a.hrow;
+  if (fo.nd.nt > 0)
+    return buf ? launch_fused_n<T, WUP, WDW, NC, true, false, true>(
+                     a, nblk, nthr, lds, st, v, w, vscale, partial, fo, fo.nd, (uint32_t)vb)
+               : launch_fused_n<T, WUP, WDW, NC, true, false>(a, nblk, nthr, lds, st, v, w,
+                                                              vscale, partial, fo, fo.nd);
+  if (fo.ph)
+    return launch_fused_n<T, WUP, WDW, NC, false, true>(a, nblk, nthr, lds, st, v, w, vscale,
+                                                        partial, fo, fo.nd);
+  if (buf)
+    return launch_fused_n<T, WUP, WDW, NC, false, false, true>(a, nblk, nthr, lds, st, v, w,
+                                                               vscale, partial, fo, fo.nd,
+                                                               (uint32_t)vb);
+  return launch_fused_n<T, WUP, WDW, NC, false, false>(a, nblk, nthr, lds, st, v, w, vscale,
+                                                       partial, fo, fo.nd);
+}
+
+}  // namespace
+
+template <typename T, int WUP, int WDW>
+edx_status launch_fused_c(const HvArgs<T>& a, int ncol, int nblk, int nthr, size_t lds,
+                          hipStream_t st, const T* v, T* w, const double* vscale,
+                          double* partial, FusedOrder<T> fo) {
+  switch (ncol) {
+    case 1: return launch_fused_k<T, WUP, WDW, 1>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
+    case 2: return launch_fused_k<T, WUP, WDW, 2>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
+    case 3: return launch_fused_k<T, WUP, WDW, 3>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
+    default: return launch_fused_k<T, WUP, WDW, 4>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
+  }
+}
+
+#define EDX_FUSED(T, WUP, WDW)                                                                  \
+  template edx_status launch_fused_c<T, WUP, WDW>(const HvArgs<T>&, int, int, int, size_t,      \
+                                                  hipStream_t, const T*, T*, const double*,     \
+                                                  double*, FusedOrder<T>);
+#define EDX_FUSED_PART(T, WUP) EDX_FUSED(T, WUP, 8) EDX_FUSED(T, WUP, 16) EDX_FUSED(T, WUP, 24)
+#if EDX_HV_PART == 0
+EDX_FUSED_PART(double, 8)
+#elif EDX_HV_PART == 1
+EDX_FUSED_PART(double, 16)
+#elif EDX_HV_PART == 2
+EDX_FUSED_PART(double, 24)
+#elif EDX_HV_PART == 3
+EDX_FUSED_PART(float, 8)
+#elif EDX_HV_PART == 4
+EDX_FUSED_PART(float, 16)
+#else
+EDX_FUSED_PART(float, 24)
+#endif
+#endif  // EDX_HV_PART
+
+#ifndef EDX_HV_PART
 // ---------------------------------------------------------------- row pass
 // A wave covers R*VEC consecutive rows (VEC rows per lane, one vector load) of
 // 64/R columns; each thread handles two columns per iteration with all their
@@ -1039,65 +1143,6 @@ int hv_partial_blocks(const edx_sector* s, int vtype) {
 namespace {
 
 
-template <typename T>
-struct FusedOrder {
-  int order;
-  const int32_t* corder;
-  NdTab<T> nd;   // nd.nt = 0: no spin exchange / pair hopping in this pass
-  bool ph = false;   // phonon slice without H_nd: the direct phonon terms
-  PhArgs<T> pa{};
-};
-
-template <typename T, int WUP, int WDW, int NC, bool ND, bool PH, bool BUF = false>
-edx_status launch_fused_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hipStream_t st,
-                          const T* v, T* w, const double* vscale, double* partial,
-                          FusedOrder<T> fo, const NdTab<T>& nd, uint32_t vbytes = 0) {
-  const void* kern = (const void*)k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>;
-  EDX_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>), dim3(nblk), dim3(nthr), lds, st,
-                     a, v, w, vscale, partial, fo.order, fo.corder, nd, fo.pa, vbytes);
-  EDX_HIP(hipGetLastError());
-  return EDX_OK;
-}
-
-template <typename T, int WUP, int WDW, int NC>
-edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hipStream_t st,
-                          const T* v, T* w, const double* vscale, double* partial,
-                          FusedOrder<T> fo) {
-  // buffer-load gathers when every byte offset into v (one phonon slice) fits
-  // in 32 bits; the H_nd terms read outside it keep global loads.  The direct
-  // phonon variant keeps global loads throughout (measured 2 % faster so, Ns=14
-  // N_ph=4: 262-267 us against 270-271 us)
-  const uint64_t vb = (uint64_t)a.ld * (uint64_t)a.ddw * sizeof(T);
-  const bool buf = vb <= 0xFFFFFFFFull && a.hrow;
-  if (fo.nd.nt > 0)
-    return buf ? launch_fused_n<T, WUP, WDW, NC, true, false, true>(
-                     a, nblk, nthr, lds, st, v, w, vscale, partial, fo, fo.nd, (uint32_t)vb)
-               : launch_fused_n<T, WUP, WDW, NC, true, false>(a, nblk, nthr, lds, st, v, w,
-                                                              vscale, partial, fo, fo.nd);
-  if (fo.ph)
-    return launch_fused_n<T, WUP, WDW, NC, false, true>(a, nblk, nthr, lds, st, v, w, vscale,
-                                                        partial, fo, fo.nd);
-  if (buf)
-    return launch_fused_n<T, WUP, WDW, NC, false, false, true>(a, nblk, nthr, lds, st, v, w,
-                                                               vscale, partial, fo, fo.nd,
-                                                               (uint32_t)vb);
-  return launch_fused_n<T, WUP, WDW, NC, false, false>(a, nblk, nthr, lds, st, v, w, vscale,
-                                                       partial, fo, fo.nd);
-}
-
-template <typename T, int WUP, int WDW>
-edx_status launch_fused_c(const HvArgs<T>& a, int ncol, int nblk, int nthr, size_t lds,
-                          hipStream_t st, const T* v, T* w, const double* vscale,
-                          double* partial, FusedOrder<T> fo) {
-  switch (ncol) {
-    case 1: return launch_fused_k<T, WUP, WDW, 1>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
-    case 2: return launch_fused_k<T, WUP, WDW, 2>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
-    case 3: return launch_fused_k<T, WUP, WDW, 3>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
-    default: return launch_fused_k<T, WUP, WDW, 4>(a, nblk, nthr, lds, st, v, w, vscale, partial, fo);
-  }
-}
-
 template <typename T, int WUP>
 edx_status launch_col_w(const HvArgs<T>& a, bool fused, int nblk, int nthr, size_t lds,
                         hipStream_t st, const T* v, T* w, const double* vscale, double* partial,
@@ -1105,8 +1150,8 @@ edx_status launch_col_w(const HvArgs<T>& a, bool fused, int nblk, int nthr, size
   if (!fused) {
     EDX_HIP(hipFuncSetAttribute((const void*)k_hv_col<T, WUP>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((k_hv_col<T, WUP>), dim3(nblk), dim3(nthr), lds, st, a, v, w, vscale,
-                       partial, ncol, 1);
+    hipLaunchKernelGGL((k_hv_col<T, WUP>), dim3(nblk), dim3(nthr), lds, st, a, v, w,
+                       vscale, partial, ncol, 1);
     EDX_HIP(hipGetLastError());
     return EDX_OK;
   }
@@ -1656,5 +1701,7 @@ edx_status hv_autotune(edx_sector* s, int vtype, const void* v, void* w, int64_t
   if (best_us) *best_us = best_t;
   return EDX_OK;
 }
+
+#endif  // !EDX_HV_PART
 
 }  // namespace edx

@@ -19,7 +19,6 @@ namespace edx {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxElemBlocks = 1024;
 
 // element (r, c) of a vector with column stride ld draws counter r + c*dup, so
 // the start vector is the same for every ld; padding rows are zero
@@ -71,26 +70,94 @@ __global__ __launch_bounds__(kThreads) void k_reduce_kernel(const double* __rest
   }
 }
 
+// The three-term update w <- w - alpha_j v_j - beta_j v_{j-1} with |w|^2, and
+// psi += y_j v_j in a replay; v_j = s_j u_j.
+//
+// With a fold (UpdateFold) the step's reductions are done here by every
+// workgroup.  FP64: w holds H u_j of the unscaled u_j, s_j = 1/|u_j| comes from
+// the previous step's partials and alpha_j = s_j^2 <u_j, H u_j> from the
+// product's, so a step is two launches instead of four.  FP32 vectors: alpha_j
+// alone (three launches), because there the unscaled product would round
+// differently: the same accuracy, but now and then another number of steps to
+// the FP32 energy floor.  Each one-workgroup reduction took 3.5 us of a 23 us
+// step at Ns = 12 (FP64 G, 2 x 200 steps: 9.19 -> 7.00 ms).  With more than
+// kMaxPartials partials (sectors whose step takes 100 us and more) every
+// workgroup would re-read tens of KB, so those keep the separate reductions.
+constexpr int kFoldA = kMaxPartials / kThreads;
+constexpr int kFoldB = kMaxElemBlocks / kThreads;
+
+struct StepCoef {
+  double wc, ac, bp, yc;   // w' = wc w - ac u_j - bp u_{j-1};  psi += yc u_j
+};
+
+struct UpdateScalars {
+  double* alpha;
+  double* beta;
+  double* scur;
+  const double* sprev;   // nullptr: no previous vector
+  const double* ycoef;   // nullptr: no psi
+  UpdateFold f;
+};
+
+// px, py: the fold's partials, loaded by fold_load
+__device__ __forceinline__ StepCoef step_coef(const UpdateScalars& c, const double (&px)[kFoldA],
+                                              const double (&py)[kFoldB], double* red) {
+  double al, be = 0.0, s, wc = 1.0;
+  if (c.f.apart) {
+    double sa, sb;
+    fold_sum2(px, py, red, sa, sb);
+    if (c.f.nb > 0) {
+      be = sqrt(sb > 0.0 ? sb : 0.0);
+      s = be > 0.0 ? 1.0 / be : 0.0;
+    } else {
+      s = *c.scur;
+      be = *c.beta;
+    }
+    if (c.f.unscaled) {
+      al = sa * s * s;
+      wc = s;
+    } else {
+      al = sa;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *c.alpha = al;
+      if (c.f.nb > 0) {
+        *c.beta = be;
+        *c.scur = s;
+      }
+    }
+  } else {
+    al = *c.alpha;
+    s = *c.scur;
+    be = *c.beta;
+  }
+  return {wc, al * s, c.sprev ? be * (*c.sprev) : 0.0, c.ycoef ? (*c.ycoef) * s : 0.0};
+}
+
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_update_kernel(
-    T* __restrict__ w, const T* __restrict__ vc, const double* __restrict__ scur,
-    const T* __restrict__ vp, const double* __restrict__ sprev,
-    const double* __restrict__ alpha, const double* __restrict__ beta, int64_t n,
-    T* __restrict__ psi, const double* __restrict__ ycoef, double* __restrict__ partial) {
-  __shared__ double red[kThreads / 64];
-  const double ac = (*alpha) * (*scur);
-  const double bp = vp ? (*beta) * (*sprev) : 0.0;
-  const double yc = psi ? (*ycoef) * (*scur) : 0.0;
+__global__ __launch_bounds__(kThreads) void k_update_kernel(T* __restrict__ w,
+                                                            const T* __restrict__ vc,
+                                                            const T* __restrict__ vp,
+                                                            UpdateScalars c, int64_t n,
+                                                            T* __restrict__ psi,
+                                                            double* __restrict__ partial) {
+  __shared__ double red[8];
+  double px[kFoldA], py[kFoldB];
+  if (c.f.apart) {
+    fold_load(px, c.f.apart, c.f.na);
+    fold_load(py, c.f.bpart, c.f.nb);
+  }
+  const StepCoef k = step_coef(c, px, py, red);
   double acc = 0.0;
   for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kThreads) {
     const double x = (double)vc[i];
-    double r = (double)w[i] - ac * x;
-    if (vp) r -= bp * (double)vp[i];
+    double r = k.wc * (double)w[i] - k.ac * x;
+    if (vp) r -= k.bp * (double)vp[i];
     const T t = (T)r;
     w[i] = t;
     acc += (double)t * (double)t;
-    if (psi) psi[i] = (T)((double)psi[i] + yc * x);
+    if (psi) psi[i] = (T)((double)psi[i] + k.yc * x);
   }
   const double s = block_sum(acc, red);
   if (threadIdx.x == 0) partial[blockIdx.x] = s;
@@ -103,55 +170,70 @@ __global__ __launch_bounds__(kThreads) void k_update_kernel(
 // Requires every vector 16-byte aligned; elements past the last full vector
 // are done by scalar lanes.  Each lane sums its elements' squares in element
 // order, so the result is deterministic for a given n and grid.
+// The first elements are loaded before the scalars are summed: on small
+// sectors a lane has one or two vectors, and the two latencies overlap.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_update_vec_kernel(
-    T* __restrict__ w, const T* __restrict__ vc, const double* __restrict__ scur,
-    const T* __restrict__ vp, const double* __restrict__ sprev,
-    const double* __restrict__ alpha, const double* __restrict__ beta, int64_t n,
-    T* __restrict__ psi, const double* __restrict__ ycoef, double* __restrict__ partial) {
+__global__ __launch_bounds__(kThreads) void k_update_vec_kernel(T* __restrict__ w,
+                                                                const T* __restrict__ vc,
+                                                                const T* __restrict__ vp,
+                                                                UpdateScalars c, int64_t n,
+                                                                T* __restrict__ psi,
+                                                                double* __restrict__ partial) {
   constexpr int V = 16 / (int)sizeof(T);
   typedef T VT __attribute__((ext_vector_type(V)));
-  __shared__ double red[kThreads / 64];
-  const double ac = (*alpha) * (*scur);
-  const double bp = vp ? (*beta) * (*sprev) : 0.0;
-  const double yc = psi ? (*ycoef) * (*scur) : 0.0;
+  __shared__ double red[8];
   VT* __restrict__ wv = reinterpret_cast<VT*>(w);
   const VT* __restrict__ cv = reinterpret_cast<const VT*>(vc);
   const VT* __restrict__ pv = reinterpret_cast<const VT*>(vp);
   VT* __restrict__ sv = reinterpret_cast<VT*>(psi);
   const int64_t nv = n / V;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
-  double acc = 0.0;
-  for (int64_t q = blockIdx.x * (int64_t)kThreads + threadIdx.x; q < nv; q += stride) {
-    const VT x = cv[q];
-    const VT a = wv[q];
-    VT b = {};
+  int64_t q = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+  double px[kFoldA], py[kFoldB];
+  if (c.f.apart) {
+    fold_load(px, c.f.apart, c.f.na);
+    fold_load(py, c.f.bpart, c.f.nb);
+  }
+  VT x = {}, a = {}, b = {};
+  if (q < nv) {
+    x = cv[q];
+    a = wv[q];
     if (vp) b = pv[q];
+  }
+  const StepCoef k = step_coef(c, px, py, red);
+  double acc = 0.0;
+  while (q < nv) {
     VT out;
 #pragma unroll
-    for (int k = 0; k < V; ++k) {
-      double r = (double)a[k] - ac * (double)x[k];
-      if (vp) r -= bp * (double)b[k];
+    for (int e = 0; e < V; ++e) {
+      double r = k.wc * (double)a[e] - k.ac * (double)x[e];
+      if (vp) r -= k.bp * (double)b[e];
       const T t = (T)r;
-      out[k] = t;
+      out[e] = t;
       acc += (double)t * (double)t;
     }
     wv[q] = out;
     if (psi) {
       VT y = sv[q];
 #pragma unroll
-      for (int k = 0; k < V; ++k) y[k] = (T)((double)y[k] + yc * (double)x[k]);
+      for (int e = 0; e < V; ++e) y[e] = (T)((double)y[e] + k.yc * (double)x[e]);
       sv[q] = y;
+    }
+    q += stride;
+    if (q < nv) {
+      x = cv[q];
+      a = wv[q];
+      if (vp) b = pv[q];
     }
   }
   for (int64_t i = nv * V + blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n; i += stride) {
-    const double x = (double)vc[i];
-    double r = (double)w[i] - ac * x;
-    if (vp) r -= bp * (double)vp[i];
+    const double xs = (double)vc[i];
+    double r = k.wc * (double)w[i] - k.ac * xs;
+    if (vp) r -= k.bp * (double)vp[i];
     const T t = (T)r;
     w[i] = t;
     acc += (double)t * (double)t;
-    if (psi) psi[i] = (T)((double)psi[i] + yc * x);
+    if (psi) psi[i] = (T)((double)psi[i] + k.yc * xs);
   }
   const double s = block_sum(acc, red);
   if (threadIdx.x == 0) partial[blockIdx.x] = s;
@@ -594,21 +676,23 @@ edx_status k_beta_finish(const double* partial, int nparts, double* beta_next,
   return EDX_OK;
 }
 
-edx_status k_update(int vtype, void* w, const void* vcur, const double* scur, const void* vprev,
-                    const double* sprev, const double* alpha, const double* beta, int64_t n,
-                    void* psi, const double* ycoef, double* partial, hipStream_t st) {
+edx_status k_update(int vtype, void* w, const void* vcur, double* scur, const void* vprev,
+                    const double* sprev, double* alpha, double* beta, int64_t n, void* psi,
+                    const double* ycoef, double* partial, hipStream_t st, const UpdateFold* fold) {
   const int g = elem_blocks(n);
+  UpdateScalars c{alpha, beta, scur, vprev ? sprev : nullptr, psi ? ycoef : nullptr, {}};
+  if (fold) c.f = *fold;
   // 16-byte vector lanes when every vector allows them (workspace vectors are
   // 256-byte aligned), else the element-wise kernel
   const bool vec = aligned16(w, vcur, vprev, psi);
   if (vtype == EDX_F64) {
     auto kern = vec ? k_update_vec_kernel<double> : k_update_kernel<double>;
-    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (double*)w, (const double*)vcur, scur,
-                       (const double*)vprev, sprev, alpha, beta, n, (double*)psi, ycoef, partial);
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (double*)w, (const double*)vcur,
+                       (const double*)vprev, c, n, (double*)psi, partial);
   } else {
     auto kern = vec ? k_update_vec_kernel<float> : k_update_kernel<float>;
-    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (float*)w, (const float*)vcur, scur,
-                       (const float*)vprev, sprev, alpha, beta, n, (float*)psi, ycoef, partial);
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (float*)w, (const float*)vcur,
+                       (const float*)vprev, c, n, (float*)psi, partial);
   }
   EDX_HIP(hipGetLastError());
   return EDX_OK;

@@ -294,30 +294,43 @@ StepBufs bufs_for(const LanczosWs& L, int j, int reorth) {
 // defl (nullable): a unit vector x (times *defl_scale) projected out of every
 // new vector, w -= <w, x> x, with the coefficient in defl_coef[0] (the
 // degeneracy check of the ground state: Lanczos on the complement of psi0).
+// `more`: step j + 1 follows on the same stream and arrays.  Where the product
+// leaves at most kMaxPartials partials, the step's reductions are folded into
+// the update (see k_update): alpha_j, and with FP64 vectors also beta_j and
+// scale_j, whose `pend` partials the step before left (0: they are written);
+// the product then takes the unscaled u_j.  The |w|^2 partials go to the halves
+// of the second slot in turn, since the update reads those of the step before.
 edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int j, int reorth,
                         double* alpha, double* beta, double* scale, void* psi,
-                        const double* ycoef, hipStream_t st, const char* locked = nullptr,
-                        int nlock = 0, const void* defl = nullptr,
-                        const double* defl_scale = nullptr, double* defl_coef = nullptr) {
+                        const double* ycoef, hipStream_t st, bool more, int* pend,
+                        const char* locked = nullptr, int nlock = 0,
+                        const void* defl = nullptr, const double* defl_scale = nullptr,
+                        double* defl_coef = nullptr) {
   const StepBufs b = bufs_for(L, j, reorth);
   const int64_t n = s->vlen;
   const int hb = hv_partial_blocks(s, vtype);
-  EDX_TRY(hv_launch(s, vtype, b.cur, b.w, s->ld, scale + j, L.partial, st));
-  EDX_TRY(k_alpha_finish(L.partial, hb, alpha + j, st));
+  const bool fold = hb <= kMaxPartials;
+  const bool unscaled = fold && vtype == EDX_F64;
+  double* const half[2] = {L.partial + kMaxPartials, L.partial + kMaxPartials + kMaxElemBlocks};
+  double* const out = fold ? half[j & 1] : L.partial;
+  EDX_TRY(hv_launch(s, vtype, b.cur, b.w, s->ld, unscaled ? nullptr : scale + j, L.partial,
+                    st));
+  if (!fold) EDX_TRY(k_alpha_finish(L.partial, hb, alpha + j, st));
+  const UpdateFold f{L.partial, hb, unscaled, half[(j + 1) & 1], *pend};
   EDX_TRY(k_update(vtype, b.w, b.cur, scale + j, b.prev, j > 0 ? scale + j - 1 : nullptr,
-                   alpha + j, beta + j, n, psi, ycoef, L.partial, st));
+                   alpha + j, beta + j, n, psi, ycoef, out, st, fold ? &f : nullptr));
   if (defl) {
     EDX_TRY(k_dot2(vtype, b.w, defl, defl_scale, nullptr, nullptr, n, L.partial, st));
     EDX_TRY(k_reduce_strided(L.partial, elem_blocks(n), kMaxPartials, 1, defl_coef, st));
-    EDX_TRY(k_axpy2(vtype, b.w, defl, defl_coef, defl_scale, nullptr, nullptr, nullptr, n,
-                    L.partial, st));
+    EDX_TRY(k_axpy2(vtype, b.w, defl, defl_coef, defl_scale, nullptr, nullptr, nullptr, n, out,
+                    st));
   }
   if (reorth == 1) {
     EDX_TRY(k_dot2(vtype, b.w, b.cur, scale + j, b.prev, j > 0 ? scale + j - 1 : nullptr, n,
                    L.partial, st));
     EDX_TRY(k_reduce_strided(L.partial, elem_blocks(n), kMaxPartials, 2, L.coef, st));
     EDX_TRY(k_axpy2(vtype, b.w, b.cur, L.coef, scale + j, b.prev, L.coef + 1,
-                    j > 0 ? scale + j - 1 : nullptr, n, L.partial, st));
+                    j > 0 ? scale + j - 1 : nullptr, n, out, st));
   } else if (reorth == 2) {
     const int64_t ldv = (int64_t)(L.vstride / vbytes(vtype));
     for (int pass = 0; pass < 2; ++pass) {
@@ -332,11 +345,15 @@ edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int 
       EDX_TRY(k_reduce_strided(L.partial, multi_blocks(n), kMaxPartials, j + 1, L.coef, st));
       EDX_TRY(k_coef_scale2(L.coef, scale, j + 1, st));
       EDX_TRY(k_multi_axpy(vtype, b.w, L.vec, (int64_t)(L.vstride / vbytes(vtype)), j + 1,
-                           L.coef, n, L.partial, st));
+                           L.coef, n, pass == 1 ? out : L.partial, st));
     }
   }
   const int eb = reorth == 2 ? multi_blocks(n) : elem_blocks(n);
-  EDX_TRY(k_beta_finish(L.partial, eb, beta + j + 1, scale + j + 1, st));
+  *pend = 0;
+  if (unscaled && more)
+    *pend = eb;
+  else
+    EDX_TRY(k_beta_finish(out, eb, beta + j + 1, scale + j + 1, st));
   return EDX_OK;
 }
 
@@ -390,9 +407,10 @@ edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, cons
   bool stop = false;
   while (done < niter && !stop) {
     const int upto = std::min(niter, done + every);
+    int pend = 0;
     for (int j = done; j < upto; ++j)
       EDX_TRY(lanczos_step(s, vtype, L, j, 0, L.alpha2, L.beta2, L.scale2, nullptr, nullptr, st,
-                           nullptr, 0, x, xs, xc));
+                           j + 1 < upto, &pend, nullptr, 0, x, xs, xc));
     EDX_HIP(hipMemcpyAsync(ha.data(), L.alpha2, sizeof(double) * upto, hipMemcpyDeviceToHost, st));
     EDX_HIP(hipMemcpyAsync(hb.data(), L.beta2, sizeof(double) * (upto + 1), hipMemcpyDeviceToHost,
                            st));
@@ -466,8 +484,10 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
   const int every = std::max(1, o->check_every);
   while (done < niter && m == 0) {
     const int upto = std::min(niter, done + every);
+    int pend = 0;
     for (int j = done; j < upto; ++j)
-      EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha, L.beta, L.scale, nullptr, nullptr, st));
+      EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
+                           j + 1 < upto, &pend));
     EDX_HIP(hipMemcpyAsync(ha.data(), L.alpha, sizeof(double) * upto, hipMemcpyDeviceToHost, st));
     EDX_HIP(hipMemcpyAsync(hb.data(), L.beta, sizeof(double) * (upto + 1), hipMemcpyDeviceToHost, st));
     EDX_HIP(hipStreamSynchronize(st));
@@ -535,9 +555,10 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
                              o->start));
       EDX_TRY(k_beta_finish(L.partial, elem_blocks(n), L.beta2, L.scale2, st));
       EDX_HIP(hipMemsetAsync(L.beta2, 0, sizeof(double), st));
+      int pend = 0;
       for (int j = 0; j < m; ++j)
-        EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha2, L.beta2, L.scale2, acc, L.y + j,
-                             st));
+        EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha2, L.beta2, L.scale2, acc, L.y + j, st,
+                             j + 1 < m, &pend));
     }
     // normalise psi0
     EDX_TRY(k_norm2(vtype, acc, n, L.partial, st));
@@ -876,9 +897,10 @@ edx_status lowest_states_impl(const edx_sector* s, int k, const edx_lanczos_opts
     while (done < niter && m == 0) {
       const int upto = (int)std::min<int64_t>({(int64_t)niter, (int64_t)done + every,
                                                s->dim - nl});
+      int pend = 0;
       for (int j = done; j < upto; ++j)
         EDX_TRY(lanczos_step(s, vtype, L, j, 2, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
-                             X, nl));
+                             j + 1 < upto, &pend, X, nl));
       EDX_HIP(hipMemcpyAsync(ha.data(), L.alpha, sizeof(double) * upto, hipMemcpyDeviceToHost,
                              st));
       EDX_HIP(hipMemcpyAsync(hb.data(), L.beta, sizeof(double) * (upto + 1),
@@ -1170,8 +1192,10 @@ edx_status green_cf_impl(const edx_sector* gs, const void* psi0, double e0, int 
     w[br] = nrm * nrm;
     if (!(nrm > 0.0)) continue;
     EDX_HIP(hipMemsetAsync(L.beta, 0, sizeof(double), st));
+    int pend = 0;
     for (int j = 0; j < ngf; ++j)
-      EDX_TRY(lanczos_step(t, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st));
+      EDX_TRY(lanczos_step(t, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
+                           j + 1 < ngf, &pend));
     ha[br].resize(ngf + 1);
     hb[br].resize(ngf + 1);
     EDX_HIP(hipMemcpyAsync(ha[br].data(), L.alpha, sizeof(double) * ngf, hipMemcpyDeviceToHost, st));
@@ -1282,8 +1306,10 @@ edx_status chi_impl(const edx_sector* s, const void* psi0, double e0, const Diag
   int len = 0, dropped = 0;
   if (h[0] > 0.0) {
     EDX_HIP(hipMemsetAsync(L.beta, 0, sizeof(double), st));
+    int pend = 0;
     for (int j = 0; j < ngf; ++j)
-      EDX_TRY(lanczos_step(s, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st));
+      EDX_TRY(lanczos_step(s, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
+                           j + 1 < ngf, &pend));
     std::vector<double> ha(ngf + 1), hb(ngf + 1);
     EDX_HIP(hipMemcpyAsync(ha.data(), L.alpha, sizeof(double) * ngf, hipMemcpyDeviceToHost, st));
     EDX_HIP(hipMemcpyAsync(hb.data(), L.beta, sizeof(double) * (ngf + 1), hipMemcpyDeviceToHost,
@@ -1419,8 +1445,10 @@ edx_status pair_impl(const edx_sector* gs, const void* psi0, double e0, int a,
     w[br] = nrm * nrm;
     if (!(nrm > 0.0)) continue;
     EDX_HIP(hipMemsetAsync(L.beta, 0, sizeof(double), st));
+    int pend = 0;
     for (int j = 0; j < ngf; ++j)
-      EDX_TRY(lanczos_step(t, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st));
+      EDX_TRY(lanczos_step(t, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
+                           j + 1 < ngf, &pend));
     ha[br].resize(ngf + 1);
     hb[br].resize(ngf + 1);
     EDX_HIP(hipMemcpyAsync(ha[br].data(), L.alpha, sizeof(double) * ngf, hipMemcpyDeviceToHost, st));

@@ -1,0 +1,59 @@
+"""Lanczos step variants against each other and against the oracle.
+
+The step's reductions run inside the update (few product partials) or as
+kernels of their own (many), with the vectors unscaled (FP64) or scaled (FP32);
+every variant must give the oracle's energy and the same ground vector.
+"""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import fock
+from paper_2105_06806_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def edx():
+    import torch
+    from paper_2105_06806_amd import edx as E
+    assert torch.cuda.is_available()
+    return E
+
+
+@pytest.mark.parametrize("dtype,reorth", [("f64", 0), ("f64", 1), ("f64", 2), ("f32", 0), ("f32", 1)])
+def test_step_folded_and_separate(edx, dtype, reorth):
+    """Ns=14 1/13: D_dw = 14 columns; Ns=14 4/7: 3432 one-column workgroups (the
+    reductions are separate above 2048 partials), 1716 two-column ones (folded)."""
+    m = inputs.make_model(1, 13, 2.0, seed=77)
+    S = edx.build_sector(m, 4, 7)
+    tol, rtol = (1e-14, 1e-11) if dtype == "f64" else (1e-9, 1e-6)
+    got = []
+    for cols in (1, 2):
+        edx.set_plan(S, dtype, mode=2, col_cols=cols, col_threads=256, col_order=0)
+        assert (math.ceil(S.ddw / cols) > 2048) == (cols == 1)
+        e0, psi, rep, _ = edx.lanczos_ground_state(S, vtype=dtype, niter=300, tol=tol, rtol=rtol,
+                                                   seed=5, reorth=reorth)
+        assert rep["converged"] == 1
+        got.append((e0, psi.double().cpu().numpy()))
+    (ea, pa), (eb, pb) = got
+    # FP64: E to rounding, psi to residual / gap (rtol |E| = 1e-10 over a gap of
+    # 0.01 and more); FP32: E and psi at the energy and residual floors
+    eps = 1e-12 if dtype == "f64" else 1e-6
+    assert abs(ea - eb) <= eps * abs(ea)
+    assert abs(abs(np.dot(pa, pb)) - 1.0) <= (1e-12 if dtype == "f64" else 1e-6)
+
+
+@pytest.mark.parametrize("ns,nup,ndw", [(4, 2, 2), (6, 3, 2), (8, 4, 5), (9, 1, 4)])
+@pytest.mark.parametrize("reorth", [0, 1, 2, 3])
+def test_step_small_sectors(edx, ns, nup, ndw, reorth):
+    m = inputs.make_model(1, ns - 1, 2.0, seed=70 + ns)
+    S = edx.build_sector(m, nup, ndw)
+    e0, psi, _, _ = edx.lanczos_ground_state(S, niter=300, tol=1e-14, rtol=1e-11, seed=5, reorth=reorth)
+    H = fock.explicit_hamiltonian(m, nup, ndw)
+    e = np.linalg.eigvalsh(H.toarray() if hasattr(H, "toarray") else H)[0]
+    assert abs(e0 - e) <= 1e-12 * max(1.0, abs(e))
+    x = psi.cpu().numpy()
+    assert np.linalg.norm(H @ x - e * x) <= 1e-8
