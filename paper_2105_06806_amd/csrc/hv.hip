@@ -40,6 +40,15 @@
 
 namespace edx {
 
+// More dynamic LDS than a launch gets by itself has to be asked for; the call
+// costs as much host time as a quarter of a launch, so only then.
+constexpr size_t kPlainLds = 64 * 1024;
+inline hipError_t allow_lds(const void* kern, size_t lds) {
+  return lds <= kPlainLds ? hipSuccess
+                          : hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                (int)lds);
+}
+
 template <typename T>
 struct HvArgs {
   int64_t dup, ddw;
@@ -233,19 +242,40 @@ __device__ __forceinline__ T stage_load(__amdgpu_buffer_rsrc_t r, uint32_t voff,
     return buf_load<T>(r, voff, soff);
 }
 
+// b0: first row of the pass (block-uniform).  Whole passes of blockDim rows
+// are skipped by a uniform branch; inside one, lanes past the last row load the
+// last row again and stage_put_buf drops their values, and the clamped columns
+// of the last workgroup are loaded like the others.  (A check per load was an
+// exec-mask branch per load, 20-40 of them in a row even where a column has one
+// row per thread: half-filled Ns=11 FP32 7.1 -> 3.8 us, Ns=12 8.4 -> 5.8 us,
+// Ns=13 19.7 -> 16.0 us, Ns=16 808 -> 767 us; FP64 5.7 -> 4.4, 9.6 -> 8.9,
+// 26.7 -> 25.3, 1702 -> 1690 us.)
 template <typename T, int NC, int U>
 __device__ __forceinline__ void stage_issue_buf(StageBuf<T, NC, U>& b, __amdgpu_buffer_rsrc_t r,
-                                                const uint32_t (&coff)[NC], int nc, uint32_t dup,
-                                                uint32_t r0) {
+                                                const uint32_t (&coff)[NC], uint32_t dup,
+                                                uint32_t b0) {
   const uint32_t bd = blockDim.x;
 #pragma unroll
-  for (int c = 0; c < NC; ++c)
+  for (int u = 0; u < U; ++u) {
+    if (b0 + (uint32_t)u * bd >= dup) break;
+    const uint32_t row = std::min(b0 + (uint32_t)u * bd + (uint32_t)threadIdx.x, dup - 1);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t row = r0 + (uint32_t)u * bd;
-      b.x[c][u] = (c < nc && row < dup) ? stage_load<T>(r, row * (uint32_t)sizeof(T), coff[c])
-                                        : T(0);
-    }
+    for (int c = 0; c < NC; ++c) b.x[c][u] = stage_load<T>(r, row * (uint32_t)sizeof(T), coff[c]);
+  }
+}
+
+template <typename T, int NC, int U>
+__device__ __forceinline__ void stage_put_buf(T* __restrict__ vs, const StageBuf<T, NC, U>& b,
+                                              uint32_t dup, uint32_t b0, T sc) {
+  const uint32_t bd = blockDim.x;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (b0 + (uint32_t)u * bd >= dup) break;
+    const uint32_t row = b0 + (uint32_t)u * bd + threadIdx.x;
+    if (row < dup)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) vs[row * NC + c] = b.x[c][u] * sc;
+  }
 }
 
 template <typename T, int NC, int U>
@@ -540,7 +570,7 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
 #pragma unroll
     for (int c = 0; c < NC; ++c)
       coff[c] = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)jc[c] * ld * sizeof(T)));
-    stage_issue_buf(sb, vres, coff, nc, (uint32_t)dup, threadIdx.x);
+    stage_issue_buf(sb, vres, coff, (uint32_t)dup, 0);
   } else {
     stage_issue(sb, v, jc, nc, dup, ld, (int64_t)threadIdx.x);
   }
@@ -573,14 +603,19 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
     }
     nreal[c] = (int)__builtin_amdgcn_readfirstlane((uint32_t)cnt);
   }
-  stage_put(vs, sb, nc, dup, (int64_t)threadIdx.x, sc);
-  for (int64_t r0 = threadIdx.x + (int64_t)SU * blockDim.x; r0 < dup;
-       r0 += (int64_t)SU * blockDim.x) {
-    if constexpr (BUF)
-      stage_issue_buf(sb, vres, coff, nc, (uint32_t)dup, (uint32_t)r0);
-    else
+  if constexpr (BUF) {
+    stage_put_buf(vs, sb, (uint32_t)dup, 0, sc);
+    for (uint32_t b0 = SU * blockDim.x; b0 < (uint32_t)dup; b0 += SU * blockDim.x) {
+      stage_issue_buf(sb, vres, coff, (uint32_t)dup, b0);
+      stage_put_buf(vs, sb, (uint32_t)dup, b0, sc);
+    }
+  } else {
+    stage_put(vs, sb, nc, dup, (int64_t)threadIdx.x, sc);
+    for (int64_t r0 = threadIdx.x + (int64_t)SU * blockDim.x; r0 < dup;
+         r0 += (int64_t)SU * blockDim.x) {
       stage_issue(sb, v, jc, nc, dup, ld, r0);
-    stage_put(vs, sb, nc, dup, r0, sc);
+      stage_put(vs, sb, nc, dup, r0, sc);
+    }
   }
   // BUF: buffer resources over v, w and the row tables; every row offset is
   // 32-bit and the store offsets of the NC output columns are block-uniform
@@ -794,7 +829,7 @@ edx_status launch_fused_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
                           const T* v, T* w, const double* vscale, double* partial,
                           FusedOrder<T> fo, const NdTab<T>& nd, uint32_t vbytes = 0) {
   const void* kern = (const void*)k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>;
-  EDX_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  EDX_HIP(allow_lds(kern, lds));
   hipLaunchKernelGGL((k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>), dim3(nblk), dim3(nthr), lds, st,
                      a, v, w, vscale, partial, fo.order, fo.corder, nd, fo.pa, vbytes);
   EDX_HIP(hipGetLastError());
@@ -1148,8 +1183,7 @@ edx_status launch_col_w(const HvArgs<T>& a, bool fused, int nblk, int nthr, size
                         hipStream_t st, const T* v, T* w, const double* vscale, double* partial,
                         int ncol, FusedOrder<T> fo) {
   if (!fused) {
-    EDX_HIP(hipFuncSetAttribute((const void*)k_hv_col<T, WUP>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    EDX_HIP(allow_lds((const void*)k_hv_col<T, WUP>, lds));
     hipLaunchKernelGGL((k_hv_col<T, WUP>), dim3(nblk), dim3(nthr), lds, st, a, v, w,
                        vscale, partial, ncol, 1);
     EDX_HIP(hipGetLastError());
@@ -1191,8 +1225,7 @@ edx_status launch_t(const edx_sector* s, const T* v, T* w, int64_t ld, const dou
   if (p.mode == 0) {
     const size_t lds = hdr + (size_t)s->dim * sizeof(T);
     if (lds > 160 * 1024) return EDX_E_UNSUPPORTED;
-    EDX_HIP(hipFuncSetAttribute((const void*)k_hv_small<T>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    EDX_HIP(allow_lds((const void*)k_hv_small<T>, lds));
     hipLaunchKernelGGL(k_hv_small<T>, dim3(1), dim3(1024), lds, st, a, v, w, vscale, partial);
     EDX_HIP(hipGetLastError());
     return EDX_OK;
@@ -1438,13 +1471,13 @@ __global__ __launch_bounds__(1024) void k_hv_colx(HvArgs<T> a, const T* __restri
   }
   constexpr int SU = std::max(1, (sizeof(T) == 4 ? 40 : 20) / NC);
   StageBuf<T, NC, SU> sb;
-  stage_issue_buf(sb, vres, coff, nc, dup, threadIdx.x);
+  stage_issue_buf(sb, vres, coff, dup, 0);
   for (int i = threadIdx.x; i < kAmpTable; i += blockDim.x) amp[i] = a.amp[i];
   for (int i = threadIdx.x; i < 64; i += blockDim.x) Wt[i] = a.W[i];
-  stage_put(vs, sb, nc, (int64_t)dup, (int64_t)threadIdx.x, T(1));
-  for (uint32_t r0 = threadIdx.x + SU * blockDim.x; r0 < dup; r0 += SU * blockDim.x) {
-    stage_issue_buf(sb, vres, coff, nc, dup, r0);
-    stage_put(vs, sb, nc, (int64_t)dup, (int64_t)r0, T(1));
+  stage_put_buf(vs, sb, dup, 0, T(1));
+  for (uint32_t b0 = SU * blockDim.x; b0 < dup; b0 += SU * blockDim.x) {
+    stage_issue_buf(sb, vres, coff, dup, b0);
+    stage_put_buf(vs, sb, dup, b0, T(1));
   }
   __syncthreads();
   for (uint32_t iu = threadIdx.x; iu < dup; iu += blockDim.x) {
@@ -1542,8 +1575,7 @@ edx_status block_t(const edx_sector* s, int part, const T* v, T* w, int64_t ld, 
     a.hrow = hr;
     const size_t ldsx = smem_header() + 16 + (size_t)C * len * sizeof(T);
     auto gox = [&](auto kern) -> edx_status {
-      EDX_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)ldsx));
+      EDX_HIP(allow_lds((const void*)kern, ldsx));
       hipLaunchKernelGGL(kern, dim3(nblk), dim3(nthr), ldsx, st, a, vb, wb, (uint32_t)bytes);
       EDX_HIP(hipGetLastError());
       return EDX_OK;
@@ -1563,8 +1595,7 @@ edx_status block_t(const edx_sector* s, int part, const T* v, T* w, int64_t ld, 
     }
   }
   auto go = [&](auto kern) -> edx_status {
-    EDX_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds));
+    EDX_HIP(allow_lds((const void*)kern, lds));
     hipLaunchKernelGGL(kern, dim3(nblk), dim3(nthr), lds, st, a, vb, wb, nullptr, nullptr, C, 0);
     EDX_HIP(hipGetLastError());
     return EDX_OK;
