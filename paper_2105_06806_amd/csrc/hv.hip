@@ -451,15 +451,18 @@ const float* wph<float>(const edx_sector* s) { return s->wph32; }
 
 #endif
 
-// Holstein terms of one phonon slice p for the fused pass (Sec. "Electron-phonon
-// coupling"): (g(pu) + g(pd)) (sp v_{p-1} + sp1 v_{p+1}) at the element itself,
-// the neighbouring slices `slice` elements away; g(pattern) = sum_a g_a n_a.
+// Holstein terms for the fused pass (Sec. "Electron-phonon coupling"): phonon
+// slice p adds (g(pu) + g(pd)) (sqrt(p) v_{p-1} + sqrt(p+1) v_{p+1}) at the
+// element itself, the neighbouring slices `slice` elements away; g(pattern) =
+// sum_a g_a n_a.  One launch covers all slices (blockIdx.y = p): their
+// workgroups fill the chip together where one slice does not, and a slice's
+// neighbours are still in cache (N_ph = 4, one launch a slice -> one launch:
+// Ns=10 FP64 19.8 -> 7.7 us, Ns=12 FP32 40.1 -> 26.1 us, FP64 58 -> 42 us).
 template <typename T>
 struct PhArgs {
-  int64_t slice;   // elements per phonon slice (ld * D_dw)
-  T sp, sp1;       // sqrt(p), sqrt(p + 1)
-  T g0, g1, g2;    // couplings g_a
-  int lo, hi;      // slice p - 1 / p + 1 exists
+  int64_t slice = 0;   // elements per phonon slice (ld * D_dw)
+  int dph = 1;         // slices
+  T g0 = 0, g1 = 0, g2 = 0;   // couplings g_a
 };
 
 template <typename T>
@@ -494,6 +497,19 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
                                                    const int32_t* __restrict__ corder,
                                                    NdTab<T> nd, PhArgs<T> ph, uint32_t vbytes) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
+  bool ph_lo = false, ph_hi = false;   // slice p - 1 / p + 1 exists
+  T ph_sp = T(0), ph_sp1 = T(0);       // sqrt(p), sqrt(p + 1)
+  if constexpr (PH) {
+    const int p = blockIdx.y;
+    v += p * ph.slice;
+    w += p * ph.slice;
+    a.W += p * 64;
+    if (partial) partial += (int64_t)p * gridDim.x;
+    ph_lo = p > 0;
+    ph_hi = p + 1 < ph.dph;
+    ph_sp = (T)sqrt((double)p);
+    ph_sp1 = (T)sqrt((double)(p + 1));
+  }
   // LDS: the staged columns first (at offset 0, so a spin-up hop's address is
   // a single multiply), then the amplitude and W tables and the reduction slots
   T* vs = reinterpret_cast<T*>(smem_raw);
@@ -719,8 +735,8 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
         pn[c] = T(0);
         if constexpr (PH) {
           const int64_t e0 = iu + jc[c] * ld;
-          if (ph.lo) pv[c] = v[e0 - ph.slice];
-          if (ph.hi) pn[c] = v[e0 + ph.slice];
+          if (ph_lo) pv[c] = v[e0 - ph.slice];
+          if (ph_hi) pn[c] = v[e0 + ph.slice];
         }
       }
       T acc[NC];
@@ -740,7 +756,7 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
 #pragma unroll
         for (int k = 0; k < WK; ++k) s2 += gamp[c][k] * g[c][k];
         T res = acc[c] + (eu + ed[c] + Wt[pu + pd[c]]) * x + s2;
-        if constexpr (PH) res += (gpat(ph, patu) + gd[c]) * (ph.sp * pv[c] + ph.sp1 * pn[c]) * sc;
+        if constexpr (PH) res += (gpat(ph, patu) + gd[c]) * (ph_sp * pv[c] + ph_sp1 * pn[c]) * sc;
         if constexpr (ND) {
           // spin exchange / pair hopping: sources near (iu, jc[c])
           const int key = patu * nd.P + pd[c];
@@ -808,7 +824,7 @@ struct FusedOrder {
   int order;
   const int32_t* corder;
   NdTab<T> nd;   // nd.nt = 0: no spin exchange / pair hopping in this pass
-  bool ph = false;   // phonon slice without H_nd: the direct phonon terms
+  bool ph = false;   // phonon slices without H_nd: the direct phonon terms, all slices
   PhArgs<T> pa{};
 };
 
@@ -830,8 +846,9 @@ edx_status launch_fused_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
                           FusedOrder<T> fo, const NdTab<T>& nd, uint32_t vbytes = 0) {
   const void* kern = (const void*)k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>;
   EDX_HIP(allow_lds(kern, lds));
-  hipLaunchKernelGGL((k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>), dim3(nblk), dim3(nthr), lds, st,
-                     a, v, w, vscale, partial, fo.order, fo.corder, nd, fo.pa, vbytes);
+  const dim3 grid((unsigned)nblk, PH ? (unsigned)fo.pa.dph : 1u);
+  hipLaunchKernelGGL((k_hv_fused<T, WUP, WDW, NC, ND, PH, BUF>), grid, dim3(nthr), lds, st, a, v, w,
+                     vscale, partial, fo.order, fo.corder, nd, fo.pa, vbytes);
   EDX_HIP(hipGetLastError());
   return EDX_OK;
 }
@@ -841,9 +858,8 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
                           const T* v, T* w, const double* vscale, double* partial,
                           FusedOrder<T> fo) {
   // buffer-load gathers when every byte offset into v (one phonon slice) fits
-  // in 32 bits; the H_nd terms read outside it keep global loads.  The direct
-  // phonon variant keeps global loads throughout (measured 2 % faster so, Ns=14
-  // N_ph=4: 262-267 us against 270-271 us)
+  // in 32 bits; the H_nd terms and the neighbouring phonon slices lie outside
+  // it and keep global loads
   const uint64_t vb = (uint64_t)a.ld * (uint64_t)a.ddw * sizeof(T);
   const bool buf = vb <= 0xFFFFFFFFull && a.hrow;
   if (fo.nd.nt > 0)
@@ -852,8 +868,10 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
                : launch_fused_n<T, WUP, WDW, NC, true, false>(a, nblk, nthr, lds, st, v, w,
                                                               vscale, partial, fo, fo.nd);
   if (fo.ph)
-    return launch_fused_n<T, WUP, WDW, NC, false, true>(a, nblk, nthr, lds, st, v, w, vscale,
-                                                        partial, fo, fo.nd);
+    return buf ? launch_fused_n<T, WUP, WDW, NC, false, true, true>(
+                     a, nblk, nthr, lds, st, v, w, vscale, partial, fo, fo.nd, (uint32_t)vb)
+               : launch_fused_n<T, WUP, WDW, NC, false, true>(a, nblk, nthr, lds, st, v, w, vscale,
+                                                              partial, fo, fo.nd);
   if (buf)
     return launch_fused_n<T, WUP, WDW, NC, false, false, true>(a, nblk, nthr, lds, st, v, w,
                                                                vscale, partial, fo, fo.nd,
@@ -1237,18 +1255,15 @@ edx_status launch_t(const edx_sector* s, const T* v, T* w, int64_t ld, const dou
   bool use_ph = false;
   PhArgs<T> pa{};
   if (p.mode == 2 && s->dph > 1 && slice >= 0 && !s->nd) {
-    // phonon slice: W + w0 p, and the coupling to the neighbouring slices
+    // all phonon slices: W + w0 p, and the coupling to the neighbouring slices
     // read directly next to the gathers
-    a.W = wph<T>(s) + (size_t)slice * 64;
+    a.W = wph<T>(s);
     use_ph = true;
     pa.slice = ld * s->ddw;
-    pa.sp = (T)std::sqrt((double)slice);
-    pa.sp1 = (T)std::sqrt((double)(slice + 1));
+    pa.dph = s->dph;
     pa.g0 = (T)s->model.g[0];
     pa.g1 = (T)s->model.g[1];
     pa.g2 = (T)s->model.g[2];
-    pa.lo = slice > 0;
-    pa.hi = slice + 1 < s->dph;
   } else if (p.mode == 2 && s->dph > 1 && slice >= 0) {
     // phonon slice with H_nd: W + w0 p and the slice's merged term table
     const int P = 1 << s->model.norb;
@@ -1407,9 +1422,10 @@ edx_status hv_launch(const edx_sector* s, int vtype, const void* v, void* w, int
   const HvPlan p = plan ? *plan : hv_plan(s, vtype);
   const int eb = hv_el_partial_blocks(s, p);
   const size_t sb = (size_t)(ld * s->ddw) * vbytes(vtype);
-  // fused plan: each slice's pass applies its phonon terms (term table); the
-  // other plans add them in a separate pass
+  // fused plan: one launch for all slices (with H_nd one each, with the slice's
+  // term table); the other plans add the phonon terms in a separate pass
   const bool fused = p.mode == 2;
+  if (fused && !s->nd) return hv_launch_el(s, vtype, v, w, ld, vscale, partial, st, &p, 0);
   for (int q = 0; q < s->dph; ++q)
     EDX_TRY(hv_launch_el(s, vtype, static_cast<const char*>(v) + q * sb,
                          static_cast<char*>(w) + q * sb, ld, vscale,
