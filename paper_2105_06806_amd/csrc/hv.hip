@@ -1087,42 +1087,64 @@ int nd_blocks(const edx_sector* s) {
 // ---------------------------------------------------------------- planning
 namespace {
 
-constexpr size_t kSmallLdsBytes = 60 * 1024;
-constexpr size_t kColLdsBytes = 150 * 1024;
+constexpr size_t kLdsBytes = 160 * 1024;   // of a CU, all usable by one workgroup
 
 size_t smem_header() { return kAmpTable * 8 + 64 * 8 + 16 * 8; }
 
 }  // namespace
 
+// Every sector takes the fused pass: it beat the two-pass plan on every sector
+// measured and, since its staging has no check per load, the one-workgroup pass
+// too (half-filled Ns=8 FP64 9.8 -> 3.6 us, Ns=7 4.4 -> 3.5 us).  The rules
+// below are the fastest of (columns, threads, order) swept over Ns = 7..16, Norb
+// 1..3, both types, launches back to back; a CU holds 16 waves of these kernels.
 HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   HvPlan p;
+  p.mode = 2;
+  const bool f64 = vtype == EDX_F64;
   const size_t sz = vbytes(vtype);
-  const size_t bytes = (size_t)s->dim * sz;
-  if (bytes + smem_header() <= kSmallLdsBytes) {
-    p.mode = 0;
-    p.col_blocks = 1;
-    return p;
-  }
-  // One fused pass (spin-down neighbours gathered from global memory); it beat
-  // the two-pass plan on every sector measured (Ns = 12..16, Norb = 1..3).
-  // Columns per block: 2, or 3 for columns of 48 KB and more (the spin-up
-  // table row is then reused over more columns), as far as LDS allows and
-  // keeping a block per CU.
   const size_t colb = (size_t)s->dup * sz;
+  const bool wide = s->up.wpad > 8 || s->dw.wpad > 8;
   const int ndt = nd_lds_terms(s);
   const size_t ndl = ndt > 0 ? 16 + nd_tab_lds(1 << s->model.norb, ndt, sz) : 0;
-  int c = (int)std::max<size_t>(1, (kColLdsBytes - ndl) / colb);
-  c = std::min(c, colb >= 48 * 1024 ? 3 : 2);
-  while (c > 1 && (s->ddw + c - 1) / c < 256) --c;
+  // with phonons and no H_nd one launch covers all slices
+  const int64_t slices = s->dph > 1 && !s->nd ? s->dph : 1;
+  auto blocks = [&](int c) { return slices * ((s->ddw + c - 1) / c); };
+  auto fits = [&](int c) { return smem_header() + 16 + ndl + c * colb <= kLdsBytes; };
+  // Columns per block: a spin-up table row serves them all.  Three FP32 columns
+  // from 40 KB on (Ns=16 2 -> 3 columns: 767 -> 701 us) or, with 8-slot rows,
+  // from 24 KB (Ns=15 167 -> 162 us); else two; fewer where that leaves less
+  // than 1.5 blocks per CU (Ns=11 FP64, 462 columns: 1 column 4.6 us, 2 columns
+  // 5.0 us).  FP64 with H_nd takes one: the second column's gathers and table
+  // pointers spill to scratch (Kanamori Ns=12 FP64 35 -> 12 us, Ns=14 350 -> 108
+  // us, Ns=15 Norb=3 1376 -> 319 us), as do 16-slot rows in grids of one round
+  // (Norb=2 Ns=12 FP64 12.3 -> 11.2 us); FP32 with H_nd, 12 bytes a hop less,
+  // only in such grids (Ns=12 9.6 -> 9.0 us).
+  int c = 2;
+  if (!f64 && !s->nd && (colb >= 40 * 1024 || (!wide && colb >= 24 * 1024))) c = 3;
+  if (f64 && s->nd) c = 1;
+  if (c == 2 && blocks(2) <= 512 && (s->nd || (f64 && s->up.wpad > 8 && s->dw.wpad > 8))) c = 1;
+  while (c > 1 && (!fits(c) || blocks(c) < 384)) --c;
   p.col_cols = c;
-  p.col_threads = colb >= 48 * 1024 && c == 3 ? 1024 : 512;
   p.col_blocks = (int)((s->ddw + c - 1) / c);
-  p.mode = 2;
-  // XCD-contiguous groups inside windows all XCDs walk together (the L2 and
-  // the MALL both see the shared spin-down neighbours): FP32 over the
-  // pattern-sorted columns, FP64 (vectors twice the size) in listing order --
-  // the faster of each on the Ns = 16 sector
-  p.col_order = vtype == EDX_F32 ? 4 : 3;
+  // Threads: all of a CU's waves in one block where its LDS image leaves room
+  // for one block only (Norb=2 Ns=16 FP64 with H_nd: 512 -> 1024 threads 2303 ->
+  // 2041 us); four blocks of 256 instead of two of 512 where the columns are
+  // short -- a grid of 513-1024 blocks then runs in one round (Ns=13 25.0 -> 23.3
+  // us FP64, 14.8 -> 14.4 us FP32) -- and with H_nd, whose term loops diverge.
+  const size_t lds = c * colb + ndl;
+  p.col_threads = 512;
+  if (lds > kLdsBytes / 2)
+    p.col_threads = 1024;
+  else if (s->dup <= 256 || (s->dup <= 2048 && blocks(c) > 512) || (s->nd && s->dup <= 4096))
+    p.col_threads = 256;
+  // Order: XCD-contiguous groups while the vector stays in the MALL next to its
+  // product (Ns=14 FP64 86.2 -> 84.4 us against windows), beyond that inside
+  // windows all XCDs walk together: over the columns in listing order, or for
+  // FP32 columns of 40 KB and more over the pattern-sorted ones (Ns=16 FP32 742
+  // -> 701 us; FP64 1682 us against 1705 us sorted).
+  const size_t bytes = (size_t)s->ld * (size_t)s->ddw * sz;
+  p.col_order = bytes <= ((size_t)160 << 20) ? 1 : (!f64 && !s->nd && colb >= 40 * 1024 ? 4 : 3);
   p.row_rows = (s->dup % 2 == 0) ? 128 : 64;
   p.row_cols = 8;
   return p;
