@@ -222,11 +222,22 @@ struct UpdateFold {
   const double* bpart = nullptr;   // nb <= kMaxElemBlocks; nb = 0 unless unscaled
   int nb = 0;
 };
+// Gram-Schmidt dot products of the updated vector w in the update itself
+// (instead of |w|^2), for the axpy that follows (k_axpy2): workgroup b leaves
+// sx <w, x> in pa[b]; without x, scale_j <w, u_j> in pa[b] and
+// scale_{j-1} <w, u_{j-1}> in pb[b].
+struct UpdateDots {
+  const void* x = nullptr;
+  const double* sx = nullptr;
+  double* pa = nullptr;
+  double* pb = nullptr;
+};
 edx_status k_update(int vtype, void* w, const void* vcur, double* scur,
                     const void* vprev, const double* sprev,
                     double* alpha, double* beta, int64_t n,
                     void* psi, const double* ycoef, double* partial,
-                    hipStream_t st, const UpdateFold* fold = nullptr);
+                    hipStream_t st, const UpdateFold* fold = nullptr,
+                    const UpdateDots* dots = nullptr);
 edx_status k_norm2(int vtype, const void* x, int64_t n, double* partial,
                    hipStream_t st);
 edx_status k_scale_copy(int vtype, const void* x, const double* scale,
@@ -234,9 +245,11 @@ edx_status k_scale_copy(int vtype, const void* x, const double* scale,
 edx_status k_dot2(int vtype, const void* w, const void* a, const double* sa,
                   const void* b, const double* sb, int64_t n, double* partial,
                   hipStream_t st);
-edx_status k_axpy2(int vtype, void* w, const void* a, const double* ca,
-                   const double* sa, const void* b, const double* cb,
-                   const double* sb, int64_t n, double* partial,
+// w -= (sum of the np partials pa) sa a + (... pb) sb b; partial |w|^2 (must not
+// overlap pa, pb); np <= kMaxElemBlocks, summed in the kernel
+edx_status k_axpy2(int vtype, void* w, const void* a, const double* pa,
+                   const double* sa, const void* b, const double* pb,
+                   const double* sb, int np, int64_t n, double* partial,
                    hipStream_t st);
 edx_status k_multi_dot(int vtype, const void* basis, int64_t ld, int m,
                        const void* w, int64_t n, double* partial,

@@ -88,6 +88,7 @@ constexpr int kFoldB = kMaxElemBlocks / kThreads;
 
 struct StepCoef {
   double wc, ac, bp, yc;   // w' = wc w - ac u_j - bp u_{j-1};  psi += yc u_j
+  double s;                // scale_j
 };
 
 struct UpdateScalars {
@@ -99,19 +100,35 @@ struct UpdateScalars {
   UpdateFold f;
 };
 
-// px, py: the fold's partials, loaded by fold_load
-__device__ __forceinline__ StepCoef step_coef(const UpdateScalars& c, const double (&px)[kFoldA],
-                                              const double (&py)[kFoldB], double* red) {
-  double al, be = 0.0, s, wc = 1.0;
+// Everything the step's scalars are made of, loaded up front: their latency and
+// that of the first vector elements overlap (a small sector's update is one
+// such latency long: Ns=8 FP64 4.8 -> 4.2 us).
+struct StepLoads {
+  double px[kFoldA], py[kFoldB];
+  double al, be, s, sp, yc;
+};
+
+__device__ __forceinline__ void step_load(StepLoads& l, const UpdateScalars& c) {
+  if (c.f.apart) {
+    fold_load(l.px, c.f.apart, c.f.na);
+    fold_load(l.py, c.f.bpart, c.f.nb);
+  }
+  l.al = c.f.apart ? 0.0 : *c.alpha;
+  l.be = c.f.nb > 0 ? 0.0 : *c.beta;
+  l.s = c.f.nb > 0 ? 0.0 : *c.scur;
+  l.sp = c.sprev ? *c.sprev : 0.0;
+  l.yc = c.ycoef ? *c.ycoef : 0.0;
+}
+
+__device__ __forceinline__ StepCoef step_coef(const UpdateScalars& c, const StepLoads& l,
+                                              double* red) {
+  double al = l.al, be = l.be, s = l.s, wc = 1.0;
   if (c.f.apart) {
     double sa, sb;
-    fold_sum2(px, py, red, sa, sb);
+    fold_sum2(l.px, l.py, red, sa, sb);
     if (c.f.nb > 0) {
       be = sqrt(sb > 0.0 ? sb : 0.0);
       s = be > 0.0 ? 1.0 / be : 0.0;
-    } else {
-      s = *c.scur;
-      be = *c.beta;
     }
     if (c.f.unscaled) {
       al = sa * s * s;
@@ -126,29 +143,52 @@ __device__ __forceinline__ StepCoef step_coef(const UpdateScalars& c, const doub
         *c.scur = s;
       }
     }
-  } else {
-    al = *c.alpha;
-    s = *c.scur;
-    be = *c.beta;
   }
-  return {wc, al * s, c.sprev ? be * (*c.sprev) : 0.0, c.ycoef ? (*c.ycoef) * s : 0.0};
+  return {wc, al * s, c.sprev ? be * l.sp : 0.0, l.yc * s, s};
 }
 
+// What the update leaves of the new w: partial sums of |w|^2, or its dot
+// products with one or two vectors (DOTS): 0 none, 1 with the given x, 2 with
+// u_j and u_{j-1} (local re-orthogonalisation), which it has loaded anyway.
 template <typename T>
+struct DotArgs {
+  const T* x;          // DOTS = 1
+  const double* sx;
+  double* pa;
+  double* pb;          // DOTS = 2
+};
+
+template <typename T, int DOTS>
+__device__ __forceinline__ void update_finish(double acc, double da, double db, bool prev,
+                                              const StepCoef& k, const StepLoads& l,
+                                              double* __restrict__ partial, const DotArgs<T>& d,
+                                              double* red) {
+  if (DOTS == 0) {
+    const double s = block_sum(acc, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    return;
+  }
+  const double s1 = block_sum(da, red);
+  const double s2 = DOTS == 2 ? block_sum(db, red) : 0.0;
+  if (threadIdx.x == 0) {
+    d.pa[blockIdx.x] = s1 * (DOTS == 1 ? *d.sx : k.s);
+    if (DOTS == 2) d.pb[blockIdx.x] = prev ? s2 * l.sp : 0.0;
+  }
+}
+
+template <typename T, int DOTS>
 __global__ __launch_bounds__(kThreads) void k_update_kernel(T* __restrict__ w,
                                                             const T* __restrict__ vc,
                                                             const T* __restrict__ vp,
                                                             UpdateScalars c, int64_t n,
                                                             T* __restrict__ psi,
-                                                            double* __restrict__ partial) {
+                                                            double* __restrict__ partial,
+                                                            DotArgs<T> d) {
   __shared__ double red[8];
-  double px[kFoldA], py[kFoldB];
-  if (c.f.apart) {
-    fold_load(px, c.f.apart, c.f.na);
-    fold_load(py, c.f.bpart, c.f.nb);
-  }
-  const StepCoef k = step_coef(c, px, py, red);
-  double acc = 0.0;
+  StepLoads l;
+  step_load(l, c);
+  const StepCoef k = step_coef(c, l, red);
+  double acc = 0.0, da = 0.0, db = 0.0;
   for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kThreads) {
     const double x = (double)vc[i];
@@ -156,11 +196,15 @@ __global__ __launch_bounds__(kThreads) void k_update_kernel(T* __restrict__ w,
     if (vp) r -= k.bp * (double)vp[i];
     const T t = (T)r;
     w[i] = t;
-    acc += (double)t * (double)t;
+    if (DOTS == 0) acc += (double)t * (double)t;
+    if (DOTS == 1) da += (double)t * (double)d.x[i];
+    if (DOTS == 2) {
+      da += (double)t * x;
+      if (vp) db += (double)t * (double)vp[i];
+    }
     if (psi) psi[i] = (T)((double)psi[i] + k.yc * x);
   }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+  update_finish<T, DOTS>(acc, da, db, vp != nullptr, k, l, partial, d, red);
 }
 
 // The same update on 16-byte vectors (4 FP32 or 2 FP64 elements a lane):
@@ -170,38 +214,37 @@ __global__ __launch_bounds__(kThreads) void k_update_kernel(T* __restrict__ w,
 // Requires every vector 16-byte aligned; elements past the last full vector
 // are done by scalar lanes.  Each lane sums its elements' squares in element
 // order, so the result is deterministic for a given n and grid.
-// The first elements are loaded before the scalars are summed: on small
-// sectors a lane has one or two vectors, and the two latencies overlap.
-template <typename T>
+template <typename T, int DOTS>
 __global__ __launch_bounds__(kThreads) void k_update_vec_kernel(T* __restrict__ w,
                                                                 const T* __restrict__ vc,
                                                                 const T* __restrict__ vp,
                                                                 UpdateScalars c, int64_t n,
                                                                 T* __restrict__ psi,
-                                                                double* __restrict__ partial) {
+                                                                double* __restrict__ partial,
+                                                                DotArgs<T> d) {
   constexpr int V = 16 / (int)sizeof(T);
   typedef T VT __attribute__((ext_vector_type(V)));
   __shared__ double red[8];
   VT* __restrict__ wv = reinterpret_cast<VT*>(w);
   const VT* __restrict__ cv = reinterpret_cast<const VT*>(vc);
   const VT* __restrict__ pv = reinterpret_cast<const VT*>(vp);
+  const VT* __restrict__ xv = reinterpret_cast<const VT*>(d.x);
   VT* __restrict__ sv = reinterpret_cast<VT*>(psi);
   const int64_t nv = n / V;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   int64_t q = blockIdx.x * (int64_t)kThreads + threadIdx.x;
-  double px[kFoldA], py[kFoldB];
-  if (c.f.apart) {
-    fold_load(px, c.f.apart, c.f.na);
-    fold_load(py, c.f.bpart, c.f.nb);
-  }
-  VT x = {}, a = {}, b = {};
-  if (q < nv) {
+  StepLoads l;
+  step_load(l, c);
+  VT x = {}, a = {}, b = {}, y = {};
+  auto load = [&]() {
     x = cv[q];
     a = wv[q];
     if (vp) b = pv[q];
-  }
-  const StepCoef k = step_coef(c, px, py, red);
-  double acc = 0.0;
+    if (DOTS == 1) y = xv[q];
+  };
+  if (q < nv) load();
+  const StepCoef k = step_coef(c, l, red);
+  double acc = 0.0, da = 0.0, db = 0.0;
   while (q < nv) {
     VT out;
 #pragma unroll
@@ -210,21 +253,22 @@ __global__ __launch_bounds__(kThreads) void k_update_vec_kernel(T* __restrict__ 
       if (vp) r -= k.bp * (double)b[e];
       const T t = (T)r;
       out[e] = t;
-      acc += (double)t * (double)t;
+      if (DOTS == 0) acc += (double)t * (double)t;
+      if (DOTS == 1) da += (double)t * (double)y[e];
+      if (DOTS == 2) {
+        da += (double)t * (double)x[e];
+        if (vp) db += (double)t * (double)b[e];
+      }
     }
     wv[q] = out;
     if (psi) {
-      VT y = sv[q];
+      VT z = sv[q];
 #pragma unroll
-      for (int e = 0; e < V; ++e) y[e] = (T)((double)y[e] + k.yc * (double)x[e]);
-      sv[q] = y;
+      for (int e = 0; e < V; ++e) z[e] = (T)((double)z[e] + k.yc * (double)x[e]);
+      sv[q] = z;
     }
     q += stride;
-    if (q < nv) {
-      x = cv[q];
-      a = wv[q];
-      if (vp) b = pv[q];
-    }
+    if (q < nv) load();
   }
   for (int64_t i = nv * V + blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n; i += stride) {
     const double xs = (double)vc[i];
@@ -232,11 +276,15 @@ __global__ __launch_bounds__(kThreads) void k_update_vec_kernel(T* __restrict__ 
     if (vp) r -= k.bp * (double)vp[i];
     const T t = (T)r;
     w[i] = t;
-    acc += (double)t * (double)t;
+    if (DOTS == 0) acc += (double)t * (double)t;
+    if (DOTS == 1) da += (double)t * (double)d.x[i];
+    if (DOTS == 2) {
+      da += (double)t * xs;
+      if (vp) db += (double)t * (double)vp[i];
+    }
     if (psi) psi[i] = (T)((double)psi[i] + k.yc * xs);
   }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+  update_finish<T, DOTS>(acc, da, db, vp != nullptr, k, l, partial, d, red);
 }
 
 template <typename T>
@@ -288,15 +336,42 @@ __global__ __launch_bounds__(kThreads) void k_dot2_kernel(const T* __restrict__ 
   }
 }
 
-// w -= ca sa a + cb sb b; partial |w|^2
+// w -= ca sa a + cb sb b; partial |w|^2.  The coefficients are the sums of the
+// np partials that the dots left, added up here by every workgroup (as in the
+// update: one launch of one workgroup less per projection).
+struct AxpyCoef {
+  const double* pa;
+  const double* pb;
+  const double* sa;
+  const double* sb;
+  int np;
+};
+
+struct AxpyLoads {
+  double px[kFoldB], py[kFoldB];
+  double sa, sb;
+};
+
+__device__ __forceinline__ void axpy_load(AxpyLoads& l, const AxpyCoef& c) {
+  fold_load(l.px, c.pa, c.np);
+  fold_load(l.py, c.pb, c.pb ? c.np : 0);
+  l.sa = *c.sa;
+  l.sb = c.sb ? *c.sb : 0.0;
+}
+
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_axpy2_kernel(
-    T* __restrict__ w, const T* __restrict__ a, const double* __restrict__ ca,
-    const double* __restrict__ sa, const T* __restrict__ b, const double* __restrict__ cb,
-    const double* __restrict__ sb, int64_t n, double* __restrict__ partial) {
-  __shared__ double red[kThreads / 64];
-  const double fa = (*ca) * (*sa);
-  const double fb = b ? (*cb) * (*sb) : 0.0;
+__global__ __launch_bounds__(kThreads) void k_axpy2_kernel(T* __restrict__ w,
+                                                           const T* __restrict__ a,
+                                                           const T* __restrict__ b, AxpyCoef c,
+                                                           int64_t n,
+                                                           double* __restrict__ partial) {
+  __shared__ double red[8];
+  AxpyLoads l;
+  axpy_load(l, c);
+  double ca, cb;
+  fold_sum2(l.px, l.py, red, ca, cb);
+  const double fa = ca * l.sa;
+  const double fb = b ? cb * l.sb : 0.0;
   double acc = 0.0;
   for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kThreads) {
@@ -410,23 +485,33 @@ __global__ __launch_bounds__(kThreads) void k_dot2_vec_kernel(const T* __restric
 }
 
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_axpy2_vec_kernel(
-    T* __restrict__ w, const T* __restrict__ a, const double* __restrict__ ca,
-    const double* __restrict__ sa, const T* __restrict__ b, const double* __restrict__ cb,
-    const double* __restrict__ sb, int64_t n, double* __restrict__ partial) {
+__global__ __launch_bounds__(kThreads) void k_axpy2_vec_kernel(T* __restrict__ w,
+                                                               const T* __restrict__ a,
+                                                               const T* __restrict__ b, AxpyCoef c,
+                                                               int64_t n,
+                                                               double* __restrict__ partial) {
   constexpr int V = 16 / (int)sizeof(T);
-  __shared__ double red[kThreads / 64];
-  const double fa = (*ca) * (*sa);
-  const double fb = b ? (*cb) * (*sb) : 0.0;
+  __shared__ double red[8];
   Vec16<T>* __restrict__ wv = reinterpret_cast<Vec16<T>*>(w);
   const Vec16<T>* __restrict__ av = reinterpret_cast<const Vec16<T>*>(a);
   const Vec16<T>* __restrict__ bv = reinterpret_cast<const Vec16<T>*>(b);
   const int64_t nv = n / V, step = (int64_t)gridDim.x * kThreads;
-  double acc = 0.0;
-  for (int64_t q = blockIdx.x * (int64_t)kThreads + threadIdx.x; q < nv; q += step) {
-    const Vec16<T> x = wv[q], y = av[q];
-    Vec16<T> z = {};
+  int64_t q = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+  AxpyLoads l;
+  axpy_load(l, c);
+  Vec16<T> x = {}, y = {}, z = {};
+  auto load = [&]() {
+    x = wv[q];
+    y = av[q];
     if (b) z = bv[q];
+  };
+  if (q < nv) load();
+  double ca, cb;
+  fold_sum2(l.px, l.py, red, ca, cb);
+  const double fa = ca * l.sa;
+  const double fb = b ? cb * l.sb : 0.0;
+  double acc = 0.0;
+  while (q < nv) {
     Vec16<T> out;
 #pragma unroll
     for (int k = 0; k < V; ++k) {
@@ -436,6 +521,8 @@ __global__ __launch_bounds__(kThreads) void k_axpy2_vec_kernel(
       acc += (double)out[k] * (double)out[k];
     }
     wv[q] = out;
+    q += step;
+    if (q < nv) load();
   }
   for (int64_t i = nv * V + blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n; i += step) {
     double r = (double)w[i] - fa * (double)a[i];
@@ -676,24 +763,42 @@ edx_status k_beta_finish(const double* partial, int nparts, double* beta_next,
   return EDX_OK;
 }
 
-edx_status k_update(int vtype, void* w, const void* vcur, double* scur, const void* vprev,
-                    const double* sprev, double* alpha, double* beta, int64_t n, void* psi,
-                    const double* ycoef, double* partial, hipStream_t st, const UpdateFold* fold) {
+namespace {
+
+template <typename T>
+void update_t(void* w, const void* vcur, const void* vprev, const UpdateScalars& c, int64_t n,
+              void* psi, double* partial, hipStream_t st, const UpdateDots* dots) {
   const int g = elem_blocks(n);
-  UpdateScalars c{alpha, beta, scur, vprev ? sprev : nullptr, psi ? ycoef : nullptr, {}};
-  if (fold) c.f = *fold;
   // 16-byte vector lanes when every vector allows them (workspace vectors are
   // 256-byte aligned), else the element-wise kernel
-  const bool vec = aligned16(w, vcur, vprev, psi);
-  if (vtype == EDX_F64) {
-    auto kern = vec ? k_update_vec_kernel<double> : k_update_kernel<double>;
-    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (double*)w, (const double*)vcur,
-                       (const double*)vprev, c, n, (double*)psi, partial);
-  } else {
-    auto kern = vec ? k_update_vec_kernel<float> : k_update_kernel<float>;
-    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (float*)w, (const float*)vcur,
-                       (const float*)vprev, c, n, (float*)psi, partial);
-  }
+  const bool vec = aligned16(w, vcur, vprev, psi, dots ? dots->x : nullptr);
+  DotArgs<T> d{};
+  const int kind = dots ? (dots->x ? 1 : 2) : 0;
+  if (dots) d = DotArgs<T>{(const T*)dots->x, dots->sx, dots->pa, dots->pb};
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (T*)w, (const T*)vcur,
+                       (const T*)vprev, c, n, (T*)psi, partial, d);
+  };
+  if (kind == 0)
+    vec ? go(k_update_vec_kernel<T, 0>) : go(k_update_kernel<T, 0>);
+  else if (kind == 1)
+    vec ? go(k_update_vec_kernel<T, 1>) : go(k_update_kernel<T, 1>);
+  else
+    vec ? go(k_update_vec_kernel<T, 2>) : go(k_update_kernel<T, 2>);
+}
+
+}  // namespace
+
+edx_status k_update(int vtype, void* w, const void* vcur, double* scur, const void* vprev,
+                    const double* sprev, double* alpha, double* beta, int64_t n, void* psi,
+                    const double* ycoef, double* partial, hipStream_t st, const UpdateFold* fold,
+                    const UpdateDots* dots) {
+  UpdateScalars c{alpha, beta, scur, vprev ? sprev : nullptr, psi ? ycoef : nullptr, {}};
+  if (fold) c.f = *fold;
+  if (vtype == EDX_F64)
+    update_t<double>(w, vcur, vprev, c, n, psi, partial, st, dots);
+  else
+    update_t<float>(w, vcur, vprev, c, n, psi, partial, st, dots);
   EDX_HIP(hipGetLastError());
   return EDX_OK;
 }
@@ -740,19 +845,20 @@ edx_status k_dot2(int vtype, const void* w, const void* a, const double* sa, con
   return EDX_OK;
 }
 
-edx_status k_axpy2(int vtype, void* w, const void* a, const double* ca, const double* sa,
-                   const void* b, const double* cb, const double* sb, int64_t n,
+edx_status k_axpy2(int vtype, void* w, const void* a, const double* pa, const double* sa,
+                   const void* b, const double* pb, const double* sb, int np, int64_t n,
                    double* partial, hipStream_t st) {
   const int g = elem_blocks(n);
   const bool vec = aligned16(w, a, b);
+  const AxpyCoef c{pa, b ? pb : nullptr, sa, b ? sb : nullptr, np};
   if (vtype == EDX_F64) {
     auto kern = vec ? k_axpy2_vec_kernel<double> : k_axpy2_kernel<double>;
-    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (double*)w, (const double*)a, ca, sa,
-                       (const double*)b, cb, sb, n, partial);
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (double*)w, (const double*)a,
+                       (const double*)b, c, n, partial);
   } else {
     auto kern = vec ? k_axpy2_vec_kernel<float> : k_axpy2_kernel<float>;
-    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (float*)w, (const float*)a, ca, sa,
-                       (const float*)b, cb, sb, n, partial);
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (float*)w, (const float*)a,
+                       (const float*)b, c, n, partial);
   }
   EDX_HIP(hipGetLastError());
   return EDX_OK;

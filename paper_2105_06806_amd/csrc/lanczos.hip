@@ -292,46 +292,63 @@ StepBufs bufs_for(const LanczosWs& L, int j, int reorth) {
 // re-orthogonalisation, beta_{j+1} and scale_{j+1}.  psi/ycoef accumulate
 // psi += y_j v_j (replay).
 // defl (nullable): a unit vector x (times *defl_scale) projected out of every
-// new vector, w -= <w, x> x, with the coefficient in defl_coef[0] (the
-// degeneracy check of the ground state: Lanczos on the complement of psi0).
+// new vector, w -= <w, x> x (the degeneracy check of the ground state: Lanczos
+// on the complement of psi0; reorth = 0).
 // `more`: step j + 1 follows on the same stream and arrays.  Where the product
-// leaves at most kMaxPartials partials, the step's reductions are folded into
-// the update (see k_update): alpha_j, and with FP64 vectors also beta_j and
-// scale_j, whose `pend` partials the step before left (0: they are written);
-// the product then takes the unscaled u_j.  The |w|^2 partials go to the halves
-// of the second slot in turn, since the update reads those of the step before.
+// leaves few partials, the step's reductions are folded into the update (see
+// k_update): alpha_j, and with FP64 vectors also beta_j and scale_j, whose
+// partials the step before left in `pend` (n = 0: they are written); the
+// product then takes the unscaled u_j.  The update also forms the dot products
+// of a projection that follows (local re-orthogonalisation, defl), which so
+// costs one launch and one more pass over w (Ns=13 FP32 with reorth = 1: three
+// reads of vectors and two launches a step less).
+struct Pending {
+  double* part = nullptr;   // |w|^2 partials of the last step
+  int n = 0;
+};
+
 edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int j, int reorth,
                         double* alpha, double* beta, double* scale, void* psi,
-                        const double* ycoef, hipStream_t st, bool more, int* pend,
+                        const double* ycoef, hipStream_t st, bool more, Pending* pend,
                         const char* locked = nullptr, int nlock = 0,
-                        const void* defl = nullptr, const double* defl_scale = nullptr,
-                        double* defl_coef = nullptr) {
+                        const void* defl = nullptr, const double* defl_scale = nullptr) {
   const StepBufs b = bufs_for(L, j, reorth);
   const int64_t n = s->vlen;
   const int hb = hv_partial_blocks(s, vtype);
-  const bool fold = hb <= kMaxPartials;
+  const int eb = reorth == 2 ? multi_blocks(n) : elem_blocks(n);
+  // Partials: slot 0 holds the product's, the halves X and Y of slot 1 the
+  // |w|^2 of the last step and what this one leaves.  The two dots of reorth = 1
+  // take Y and the upper half of slot 0, so folding needs the product in its
+  // lower half there.
+  const bool local = reorth == 1;
+  const bool fold = hb <= (local ? kMaxElemBlocks : kMaxPartials);
   const bool unscaled = fold && vtype == EDX_F64;
-  double* const half[2] = {L.partial + kMaxPartials, L.partial + kMaxPartials + kMaxElemBlocks};
-  double* const out = fold ? half[j & 1] : L.partial;
+  double* X = L.partial + kMaxPartials;
+  double* Y = X + kMaxElemBlocks;
+  if (pend->n > 0 && pend->part == Y) std::swap(X, Y);
   EDX_TRY(hv_launch(s, vtype, b.cur, b.w, s->ld, unscaled ? nullptr : scale + j, L.partial,
                     st));
   if (!fold) EDX_TRY(k_alpha_finish(L.partial, hb, alpha + j, st));
-  const UpdateFold f{L.partial, hb, unscaled, half[(j + 1) & 1], *pend};
-  EDX_TRY(k_update(vtype, b.w, b.cur, scale + j, b.prev, j > 0 ? scale + j - 1 : nullptr,
-                   alpha + j, beta + j, n, psi, ycoef, out, st, fold ? &f : nullptr));
-  if (defl) {
-    EDX_TRY(k_dot2(vtype, b.w, defl, defl_scale, nullptr, nullptr, n, L.partial, st));
-    EDX_TRY(k_reduce_strided(L.partial, elem_blocks(n), kMaxPartials, 1, defl_coef, st));
-    EDX_TRY(k_axpy2(vtype, b.w, defl, defl_coef, defl_scale, nullptr, nullptr, nullptr, n, out,
-                    st));
+  const UpdateFold f{L.partial, hb, unscaled, pend->part, pend->n};
+  const double* sprev = j > 0 ? scale + j - 1 : nullptr;
+  UpdateDots d;
+  if (local) {
+    d.pa = L.partial + kMaxElemBlocks;
+    d.pb = Y;
+  } else if (defl) {
+    d.x = defl;
+    d.sx = defl_scale;
+    d.pa = Y;
   }
-  if (reorth == 1) {
-    EDX_TRY(k_dot2(vtype, b.w, b.cur, scale + j, b.prev, j > 0 ? scale + j - 1 : nullptr, n,
-                   L.partial, st));
-    EDX_TRY(k_reduce_strided(L.partial, elem_blocks(n), kMaxPartials, 2, L.coef, st));
-    EDX_TRY(k_axpy2(vtype, b.w, b.cur, L.coef, scale + j, b.prev, L.coef + 1,
-                    j > 0 ? scale + j - 1 : nullptr, n, out, st));
-  } else if (reorth == 2) {
+  const bool dots = local || defl;
+  double* out = dots ? X : Y;
+  EDX_TRY(k_update(vtype, b.w, b.cur, scale + j, b.prev, sprev, alpha + j, beta + j, n, psi, ycoef,
+                   out, st, fold ? &f : nullptr, dots ? &d : nullptr));
+  if (local)
+    EDX_TRY(k_axpy2(vtype, b.w, b.cur, d.pa, scale + j, b.prev, d.pb, sprev, eb, n, out, st));
+  else if (defl)
+    EDX_TRY(k_axpy2(vtype, b.w, defl, d.pa, defl_scale, nullptr, nullptr, nullptr, eb, n, out, st));
+  if (reorth == 2) {
     const int64_t ldv = (int64_t)(L.vstride / vbytes(vtype));
     for (int pass = 0; pass < 2; ++pass) {
       if (nlock > 0) {
@@ -348,10 +365,9 @@ edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int 
                            L.coef, n, pass == 1 ? out : L.partial, st));
     }
   }
-  const int eb = reorth == 2 ? multi_blocks(n) : elem_blocks(n);
-  *pend = 0;
+  *pend = Pending{};
   if (unscaled && more)
-    *pend = eb;
+    *pend = Pending{out, eb};
   else
     EDX_TRY(k_beta_finish(out, eb, beta + j + 1, scale + j + 1, st));
   return EDX_OK;
@@ -377,7 +393,6 @@ edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, cons
   const double floor32 = vtype == EDX_F32 ? 2.0 * 1.1920929e-7 * tnorm : 0.0;
   const double thr = std::max(1e-9 * std::max(1.0, std::fabs(e0)), floor32);
   double* xs = L.coef + 3;      // 1 / |x|
-  double* xc = L.coef + 4;      // projection coefficient
   EDX_TRY(k_norm2(vtype, x, n, L.partial, st));
   EDX_TRY(k_beta_finish(L.partial, elem_blocks(n), L.coef + 2, xs, st));
   // start vector orthogonal to x (another counter-based stream than the
@@ -385,9 +400,9 @@ edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, cons
   EDX_TRY(k_start_vector(vtype, L.vec, s->dup, s->ld, s->ddw * s->dph,
                          o->seed ^ 0xD1B54A32D192ED03ull, L.partial, st));
   EDX_TRY(k_dot2(vtype, L.vec, x, xs, nullptr, nullptr, n, L.partial, st));
-  EDX_TRY(k_reduce_strided(L.partial, elem_blocks(n), kMaxPartials, 1, xc, st));
-  EDX_TRY(k_axpy2(vtype, L.vec, x, xc, xs, nullptr, nullptr, nullptr, n, L.partial, st));
-  EDX_TRY(k_beta_finish(L.partial, elem_blocks(n), L.beta2, L.scale2, st));
+  EDX_TRY(k_axpy2(vtype, L.vec, x, L.partial, xs, nullptr, nullptr, nullptr, elem_blocks(n), n,
+                  L.partial + kMaxPartials, st));
+  EDX_TRY(k_beta_finish(L.partial + kMaxPartials, elem_blocks(n), L.beta2, L.scale2, st));
   double u0 = 0.0;
   EDX_HIP(hipMemcpyAsync(&u0, L.beta2, sizeof(double), hipMemcpyDeviceToHost, st));
   EDX_HIP(hipStreamSynchronize(st));
@@ -407,10 +422,10 @@ edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, cons
   bool stop = false;
   while (done < niter && !stop) {
     const int upto = std::min(niter, done + every);
-    int pend = 0;
+    Pending pend;
     for (int j = done; j < upto; ++j)
       EDX_TRY(lanczos_step(s, vtype, L, j, 0, L.alpha2, L.beta2, L.scale2, nullptr, nullptr, st,
-                           j + 1 < upto, &pend, nullptr, 0, x, xs, xc));
+                           j + 1 < upto, &pend, nullptr, 0, x, xs));
     EDX_HIP(hipMemcpyAsync(ha.data(), L.alpha2, sizeof(double) * upto, hipMemcpyDeviceToHost, st));
     EDX_HIP(hipMemcpyAsync(hb.data(), L.beta2, sizeof(double) * (upto + 1), hipMemcpyDeviceToHost,
                            st));
@@ -484,7 +499,7 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
   const int every = std::max(1, o->check_every);
   while (done < niter && m == 0) {
     const int upto = std::min(niter, done + every);
-    int pend = 0;
+    Pending pend;
     for (int j = done; j < upto; ++j)
       EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
                            j + 1 < upto, &pend));
@@ -555,7 +570,7 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
                              o->start));
       EDX_TRY(k_beta_finish(L.partial, elem_blocks(n), L.beta2, L.scale2, st));
       EDX_HIP(hipMemsetAsync(L.beta2, 0, sizeof(double), st));
-      int pend = 0;
+      Pending pend;
       for (int j = 0; j < m; ++j)
         EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha2, L.beta2, L.scale2, acc, L.y + j, st,
                              j + 1 < m, &pend));
@@ -897,7 +912,7 @@ edx_status lowest_states_impl(const edx_sector* s, int k, const edx_lanczos_opts
     while (done < niter && m == 0) {
       const int upto = (int)std::min<int64_t>({(int64_t)niter, (int64_t)done + every,
                                                s->dim - nl});
-      int pend = 0;
+      Pending pend;
       for (int j = done; j < upto; ++j)
         EDX_TRY(lanczos_step(s, vtype, L, j, 2, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
                              j + 1 < upto, &pend, X, nl));
@@ -1192,7 +1207,7 @@ edx_status green_cf_impl(const edx_sector* gs, const void* psi0, double e0, int 
     w[br] = nrm * nrm;
     if (!(nrm > 0.0)) continue;
     EDX_HIP(hipMemsetAsync(L.beta, 0, sizeof(double), st));
-    int pend = 0;
+    Pending pend;
     for (int j = 0; j < ngf; ++j)
       EDX_TRY(lanczos_step(t, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
                            j + 1 < ngf, &pend));
@@ -1306,7 +1321,7 @@ edx_status chi_impl(const edx_sector* s, const void* psi0, double e0, const Diag
   int len = 0, dropped = 0;
   if (h[0] > 0.0) {
     EDX_HIP(hipMemsetAsync(L.beta, 0, sizeof(double), st));
-    int pend = 0;
+    Pending pend;
     for (int j = 0; j < ngf; ++j)
       EDX_TRY(lanczos_step(s, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
                            j + 1 < ngf, &pend));
@@ -1445,7 +1460,7 @@ edx_status pair_impl(const edx_sector* gs, const void* psi0, double e0, int a,
     w[br] = nrm * nrm;
     if (!(nrm > 0.0)) continue;
     EDX_HIP(hipMemsetAsync(L.beta, 0, sizeof(double), st));
-    int pend = 0;
+    Pending pend;
     for (int j = 0; j < ngf; ++j)
       EDX_TRY(lanczos_step(t, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
                            j + 1 < ngf, &pend));
