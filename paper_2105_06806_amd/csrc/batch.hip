@@ -650,7 +650,7 @@ edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opt
         double e = 0.0;
         edx_lanczos_report rep{};
         const edx_status sj =
-            lanczos_ground_state_impl(s, &q, wsp, B.wide_bytes, &e, nullptr, &rep, sts[t]);
+            lanczos_ground_state_impl(s, &q, wsp, B.wide_bytes, &e, nullptr, &rep, sts[t], false);
         if (sj != EDX_OK && sj != EDX_E_NOCONV && sj != EDX_E_DEGENERATE) {
           tst[t] = sj;
           terr[t] = std::string("batch: whole-GPU job: ") + edx_last_error();

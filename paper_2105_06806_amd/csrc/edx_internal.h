@@ -304,7 +304,12 @@ edx_status batch_autotune(const edx_sector* const* secs, int n, const edx_lanczo
 size_t lanczos_workspace_bytes(const edx_sector* s, int vtype, int niter, int reorth);
 edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts* o, void* ws,
                                      size_t ws_bytes, double* e0, void* psi0,
-                                     edx_lanczos_report* rep, hipStream_t st);
+                                     edx_lanczos_report* rep, hipStream_t st,
+                                     bool ahead = true);
+// ahead: may keep the device a chunk of steps ahead of the host's stop rule
+// (small sectors; takes a slot of pinned host memory, which a first call
+// allocates).  Not where other solves fill the device meanwhile (batch, server):
+// the chunk after the last one would be lost to them.
 // ---- multi.hip: K bath sets of one sector shape at once (interleaved vectors)
 bool multi_supported(const edx_sector* s, int K, int vtype);
 bool multi_same_shape(const edx_sector* a, const edx_sector* b);
@@ -339,6 +344,15 @@ edx_status pair_impl(const edx_sector* gs, const void* psi0, double e0, int a,
                      edx_gf_report* rep, hipStream_t st);
 // ---- lanczos.cpp (host)
 double tridiag_lowest(const double* a, const double* b, int m, int k);
+// Lowest eigenvalue of a tridiagonal matrix that grows by a row at a time (the
+// stop rule asks for it after every step): each value starts from the last.
+class LowestRitz {
+ public:
+  double next(const double* a, const double* b, int m);   // m = 1, 2, 3, ...
+ private:
+  double e_ = 0.0, de_ = 0.0;   // last value and its last decrease
+  int m_ = 0;
+};
 void tridiag_vector(const double* a, const double* b, int m, double lam,
                     double* y);
 bool tridiag_spectrum(const double* a, const double* b, int m, double* theta, double* w);

@@ -22,6 +22,8 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
+#include <mutex>
+#include <utility>
 
 #include "edx_internal.h"
 
@@ -73,6 +75,92 @@ double tridiag_lowest(const double* a, const double* b, int m, int k) {
     if (hi - lo <= 2.0 * eps * std::max(std::fabs(lo), std::fabs(hi))) break;
   }
   return 0.5 * (lo + hi);
+}
+
+namespace {
+
+// For kLanes shifts at once, whether T - x has a negative pivot (x above the
+// lowest eigenvalue).  The pivot recurrence is one division after another, so
+// independent shifts in vector lanes cost little more than one.
+constexpr int kLanes = 8;
+void any_below(const double* a, const double* b, int m, const double (&x)[kLanes], double tiny,
+               bool (&neg)[kLanes]) {
+  double q[kLanes], low[kLanes];
+  for (int l = 0; l < kLanes; ++l) {
+    q[l] = a[0] - x[l];
+    q[l] = std::fabs(q[l]) < tiny ? -tiny : q[l];   // a zero pivot counts as negative
+    low[l] = q[l];
+  }
+  for (int i = 1; i < m; ++i) {
+    const double bb = b[i - 1] * b[i - 1], ai = a[i];
+    for (int l = 0; l < kLanes; ++l) {
+      q[l] = ai - x[l] - bb / q[l];
+      q[l] = std::fabs(q[l]) < tiny ? -tiny : q[l];
+      low[l] = low[l] < q[l] ? low[l] : q[l];
+    }
+  }
+  for (int l = 0; l < kLanes; ++l) neg[l] = low[l] < 0.0;
+}
+
+}  // namespace
+
+// The lowest eigenvalue of T_m lies at or below that of T_{m-1} (interlacing)
+// and, once the run converges, hardly below it: the bracket starts there, as
+// wide as a few of the last decreases, and is cut into kLanes + 1 parts per
+// sweep down to the width at which tridiag_lowest stops.  4-8 sweeps where the
+// bisection from the Gershgorin bounds takes 55 (ground state of half-filled
+// Ns=12, 140 steps: 30 us of host time a step before).
+double LowestRitz::next(const double* a, const double* b, int m) {
+  const bool warm = m == m_ + 1 && m > 2;
+  const double eold = e_;
+  double e;
+  if (m == 1) {
+    e = a[0];
+  } else {
+    double lo = a[0], hi = a[0], nrm = 0.0;
+    for (int i = 0; i < m; ++i) {
+      const double r = (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i < m - 1 ? std::fabs(b[i]) : 0.0);
+      lo = std::min(lo, a[i] - r);
+      hi = std::max(hi, a[i] + r);
+      nrm = std::max(nrm, std::fabs(a[i]) + r);
+    }
+    const double tiny = std::max(nrm, 1.0) * 1e-300;
+    const double eps = std::numeric_limits<double>::epsilon();
+    lo -= eps * nrm + tiny;
+    hi += eps * nrm + tiny;
+    double x[kLanes];
+    bool neg[kLanes];
+    if (warm) {
+      // x[0] just above the last value, the others at growing distances below
+      double d = std::max(2.0 * de_, 8.0 * eps * nrm);
+      x[0] = eold + 4.0 * eps * nrm;
+      for (int l = 1; l < kLanes; ++l, d *= 8.0) x[l] = eold - d;
+      any_below(a, b, m, x, tiny, neg);
+      for (int l = 0; l < kLanes; ++l)
+        if (neg[l])
+          hi = std::min(hi, x[l]);
+        else
+          lo = std::max(lo, x[l]);
+    }
+    for (int it = 0; it < 60 && hi - lo > 2.0 * eps * std::max(std::fabs(lo), std::fabs(hi)); ++it) {
+      const double w = hi - lo;
+      for (int l = 0; l < kLanes; ++l) x[l] = lo + w * ((l + 1) * (1.0 / (kLanes + 1)));
+      any_below(a, b, m, x, tiny, neg);
+      for (int l = 0; l < kLanes; ++l)
+        if (neg[l]) {
+          hi = std::min(hi, x[l]);
+          break;
+        } else {
+          lo = std::max(lo, x[l]);
+        }
+      if (!(hi - lo < w)) break;   // no point between them is left
+    }
+    e = 0.5 * (lo + hi);
+  }
+  de_ = m > 1 ? std::max(0.0, eold - e) : 0.0;
+  e_ = e;
+  m_ = m;
+  return e;
 }
 
 // Eigenvector of T for eigenvalue lam by inverse iteration, Gaussian
@@ -373,10 +461,141 @@ edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int 
   return EDX_OK;
 }
 
-struct StopState {
-  double tnorm = 0.0;
-  double Eprev = NAN;
+// alpha and beta of finished steps on the host, a chunk of steps at a time.
+// With a slot of pinned memory the copies of a chunk are queued behind it and
+// the next chunk behind them, so the device goes on while the host applies the
+// stop rule; without one a chunk is copied and waited for before the next.
+// Slots are kept for the life of the process (at most kMaxSlots of them, 4 KiB
+// and two events each), held by one call at a time.
+class ChunkReader {
+ public:
+  static constexpr int kMaxChunk = 128;
+  ChunkReader(bool ahead, int every, hipStream_t st) : st_(st) {
+    if (ahead && every <= kMaxChunk) slot_ = acquire();
+  }
+  ~ChunkReader() {
+    if (!slot_) return;
+    for (int i = 0; i < 2; ++i)
+      if (busy_[i]) (void)hipEventSynchronize(slot_->ev[i]);
+    std::lock_guard<std::mutex> lk(mutex());
+    slot_->used = false;
+  }
+  ChunkReader(const ChunkReader&) = delete;
+  ChunkReader& operator=(const ChunkReader&) = delete;
+  bool ahead() const { return slot_ != nullptr; }
+  void restart() { posted_ = taken_ = 0; }   // the next run's chunks; an untaken one is dropped
+
+  // steps from .. to - 1 are enqueued on the stream: queue their copies
+  edx_status post(const double* alpha, const double* beta, int from, int to) {
+    const int i = posted_++ & 1;
+    if (!slot_) return EDX_OK;
+    double* h = slot_->host + i * 2 * kMaxChunk;
+    EDX_HIP(hipMemcpyAsync(h, alpha + from, sizeof(double) * (to - from), hipMemcpyDeviceToHost,
+                           st_));
+    EDX_HIP(hipMemcpyAsync(h + kMaxChunk, beta + from + 1, sizeof(double) * (to - from),
+                           hipMemcpyDeviceToHost, st_));
+    EDX_HIP(hipEventRecord(slot_->ev[i], st_));
+    busy_[i] = true;
+    return EDX_OK;
+  }
+
+  // wait for the oldest posted chunk: alpha[from..to), beta[from + 1..to]
+  edx_status take(const double* alpha, const double* beta, int from, int to, double* ha,
+                  double* hb) {
+    const int i = taken_++ & 1;
+    const size_t bytes = sizeof(double) * (to - from);
+    if (!slot_) {
+      EDX_HIP(hipMemcpyAsync(ha + from, alpha + from, bytes, hipMemcpyDeviceToHost, st_));
+      EDX_HIP(hipMemcpyAsync(hb + from + 1, beta + from + 1, bytes, hipMemcpyDeviceToHost, st_));
+      EDX_HIP(hipStreamSynchronize(st_));
+      return EDX_OK;
+    }
+    EDX_HIP(hipEventSynchronize(slot_->ev[i]));
+    busy_[i] = false;
+    const double* h = slot_->host + i * 2 * kMaxChunk;
+    std::memcpy(ha + from, h, bytes);
+    std::memcpy(hb + from + 1, h + kMaxChunk, bytes);
+    return EDX_OK;
+  }
+
+ private:
+  struct Slot {
+    double* host = nullptr;   // two chunks of alpha and beta
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    int device = 0;
+    bool used = false;
+  };
+  static constexpr int kMaxSlots = 64;
+  static std::mutex& mutex() {
+    static std::mutex* m = new std::mutex;   // never destroyed: calls may outlive statics
+    return *m;
+  }
+  static Slot* acquire() {
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess) return nullptr;
+    static std::vector<Slot*>* all = new std::vector<Slot*>;
+    std::lock_guard<std::mutex> lk(mutex());
+    for (Slot* q : *all)
+      if (!q->used && q->device == device) {
+        q->used = true;
+        return q;
+      }
+    if ((int)all->size() >= kMaxSlots) return nullptr;
+    Slot q;
+    q.device = device;
+    q.used = true;
+    if (hipHostMalloc((void**)&q.host, sizeof(double) * 4 * kMaxChunk, hipHostMallocDefault) !=
+        hipSuccess)
+      return nullptr;
+    for (hipEvent_t& e : q.ev)
+      if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        if (q.ev[0]) (void)hipEventDestroy(q.ev[0]);
+        (void)hipHostFree(q.host);
+        return nullptr;
+      }
+    all->push_back(new Slot(q));
+    return all->back();
+  }
+
+  hipStream_t st_;
+  Slot* slot_ = nullptr;
+  int posted_ = 0, taken_ = 0;
+  bool busy_[2] = {false, false};
 };
+
+// Steps 0 .. niter - 1 in chunks of `every`, until check(from, to) says stop:
+// step(j, more, pend) enqueues step j, check sees ha[0..to), hb[0..to] filled.
+template <typename Step, typename Check>
+edx_status run_chunks(ChunkReader& rd, const double* alpha, const double* beta, int niter,
+                      int every, double* ha, double* hb, Step step, Check check) {
+  int enq = 0, seen = 0;   // steps enqueued, steps checked
+  auto enqueue = [&]() -> edx_status {
+    const int to = std::min(niter, enq + every);
+    Pending pend;
+    for (int j = enq; j < to; ++j) EDX_TRY(step(j, j + 1 < to, &pend));
+    EDX_TRY(rd.post(alpha, beta, enq, to));
+    enq = to;
+    return EDX_OK;
+  };
+  bool stop = false;
+  rd.restart();
+  hb[0] = 0.0;   // beta_0 couples nothing
+  while (seen < niter && !stop) {
+    if (enq == seen) EDX_TRY(enqueue());
+    const int to = std::min(niter, seen + every);
+    if (rd.ahead() && enq < niter) EDX_TRY(enqueue());
+    EDX_TRY(rd.take(alpha, beta, seen, to, ha, hb));
+    stop = check(seen, to);
+    seen = to;
+  }
+  return EDX_OK;
+}
+
+// Running one chunk ahead hides the host's check (about 60 us a chunk of 8)
+// and costs the steps of one chunk after the last: worth it while a step is
+// short against the check, on vectors that stay in cache; full
+// re-orthogonalisation makes the last steps the longest.
+constexpr size_t kAheadBytes = size_t(32) << 20;
 
 // Lowest level of H restricted to the complement of the unit vector x
 // (device, Krylov layout, any positive multiple of it): plain Lanczos from a
@@ -385,7 +604,7 @@ struct StopState {
 // value settles (tol, floored for FP32 vectors), at breakdown or after niter
 // steps.  Uses the rotating vectors and the replay scalars of L.
 edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, const LanczosWs& L,
-                            const void* x, double e0, double tnorm, hipStream_t st, double* e1,
+                            ChunkReader& rd, const void* x, double e0, double tnorm, hipStream_t st, double* e1,
                             bool* degenerate) {
   const int vtype = o->vtype;
   const int niter = o->niter;
@@ -418,37 +637,30 @@ edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, cons
   const int every = std::max(1, o->check_every);
   double th = NAN, thold = NAN, tn = tnorm;
   bool deg = false;
-  int done = 0;
-  bool stop = false;
-  while (done < niter && !stop) {
-    const int upto = std::min(niter, done + every);
-    Pending pend;
-    for (int j = done; j < upto; ++j)
-      EDX_TRY(lanczos_step(s, vtype, L, j, 0, L.alpha2, L.beta2, L.scale2, nullptr, nullptr, st,
-                           j + 1 < upto, &pend, nullptr, 0, x, xs));
-    EDX_HIP(hipMemcpyAsync(ha.data(), L.alpha2, sizeof(double) * upto, hipMemcpyDeviceToHost, st));
-    EDX_HIP(hipMemcpyAsync(hb.data(), L.beta2, sizeof(double) * (upto + 1), hipMemcpyDeviceToHost,
-                           st));
-    EDX_HIP(hipStreamSynchronize(st));
-    for (int j = done; j < upto; ++j) {
+  LowestRitz ritz;
+  auto step = [&](int j, bool more, Pending* pend) {
+    return lanczos_step(s, vtype, L, j, 0, L.alpha2, L.beta2, L.scale2, nullptr, nullptr, st, more,
+                        pend, nullptr, 0, x, xs);
+  };
+  auto check = [&](int from, int to) {
+    for (int j = from; j < to; ++j) {
       tn = std::max(tn, std::fabs(ha[j]) + hb[j] + hb[j + 1]);
-      th = tridiag_lowest(ha.data(), hb.data() + 1, j + 1, 0);
+      th = ritz.next(ha.data(), hb.data() + 1, j + 1);
       if (th - e0 < thr) {
         deg = true;
-        stop = true;
-        break;
+        return true;
       }
       const bool bd = !(hb[j + 1] > 1e-12 * tn);
       const bool settled = j > 0 && std::fabs(th - thold) <=
                                         std::max(o->tol * std::max(1.0, std::fabs(th)), floor32);
       thold = th;
-      if (bd || settled) {
-        stop = true;
-        break;
-      }
+      if (bd || settled) return true;
     }
-    done = upto;
-  }
+    return false;
+  };
+  EDX_TRY(run_chunks(rd, L.alpha2, L.beta2, niter, every, ha.data(), hb.data(), step, check));
+  // a chunk that was run ahead still uses the workspace
+  if (rd.ahead()) EDX_HIP(hipStreamSynchronize(st));
   *e1 = th;
   *degenerate = deg;
   return EDX_OK;
@@ -463,7 +675,7 @@ size_t lanczos_workspace_bytes(const edx_sector* s, int vtype, int niter, int re
 
 edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts* o, void* ws,
                                      size_t ws_bytes, double* e0, void* psi0,
-                                     edx_lanczos_report* rep, hipStream_t st) {
+                                     edx_lanczos_report* rep, hipStream_t st, bool ahead) {
   const int vtype = o->vtype;
   const int niter = o->niter;
   const int reorth = o->reorth;
@@ -493,23 +705,20 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
 
   std::vector<double> ha(niter + 2), hb(niter + 2);
   int m = 0;              // number of Lanczos steps kept (size of T)
-  int done = 0;           // steps enqueued
   bool converged = false, breakdown = false;
   double E = 0.0, Eold = NAN, tnorm = 0.0, resid = 0.0;
   const int every = std::max(1, o->check_every);
-  while (done < niter && m == 0) {
-    const int upto = std::min(niter, done + every);
-    Pending pend;
-    for (int j = done; j < upto; ++j)
-      EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
-                           j + 1 < upto, &pend));
-    EDX_HIP(hipMemcpyAsync(ha.data(), L.alpha, sizeof(double) * upto, hipMemcpyDeviceToHost, st));
-    EDX_HIP(hipMemcpyAsync(hb.data(), L.beta, sizeof(double) * (upto + 1), hipMemcpyDeviceToHost, st));
-    EDX_HIP(hipStreamSynchronize(st));
-    for (int j = done; j < upto; ++j) {
+  ChunkReader rd(ahead && reorth != 2 && L.vstride <= kAheadBytes, every, st);
+  LowestRitz ritz;
+  auto step = [&](int j, bool more, Pending* pend) {
+    return lanczos_step(s, vtype, L, j, reorth, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
+                        more, pend);
+  };
+  auto check = [&](int from, int to) {
+    for (int j = from; j < to; ++j) {
       // T_j: alpha[0..j], off-diagonal beta[1..j]
       tnorm = std::max(tnorm, std::fabs(ha[j]) + hb[j] + hb[j + 1]);
-      E = tridiag_lowest(ha.data(), hb.data() + 1, j + 1, 0);
+      E = ritz.next(ha.data(), hb.data() + 1, j + 1);
       const bool bd = !(hb[j + 1] > 1e-12 * tnorm);
       // FP32 vectors cannot resolve energies or residuals below ~eps_32 |T|:
       // the thresholds are floored there (precision mode)
@@ -527,11 +736,12 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
         m = j + 1;
         converged = ok || bd;
         breakdown = bd;
-        break;
+        return true;
       }
     }
-    done = upto;
-  }
+    return false;
+  };
+  EDX_TRY(run_chunks(rd, L.alpha, L.beta, niter, every, ha.data(), hb.data(), step, check));
   if (m == 0) m = niter;
   E = tridiag_lowest(ha.data(), hb.data() + 1, m, 0);
   std::vector<double> y(m);
@@ -592,7 +802,7 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
     // E0 means a degenerate ground level; otherwise the run goes on until its
     // lowest Ritz value settles (that is E1).
     double E1d = NAN;
-    EDX_TRY(check_degeneracy(s, o, L, acc, E, tnorm, st, &E1d, &degenerate));
+    EDX_TRY(check_degeneracy(s, o, L, rd, acc, E, tnorm, st, &E1d, &degenerate));
     E1 = E1d;
   }
   *e0 = E;

@@ -583,6 +583,7 @@ edx_status multi_ground_states(const edx_sector* const* secs, int K, const edx_l
   std::vector<double> ta(niter + 2), tb(niter + 2);
   std::vector<int> done(K, 0);
   std::vector<double> tnorm(K, 0.0), Eold(K, NAN);
+  std::vector<LowestRitz> ritz(K);
   int left = K;
   int steps = 0;
   const int every = std::max(1, o->check_every);
@@ -618,7 +619,7 @@ edx_status multi_ground_states(const edx_sector* const* secs, int K, const edx_l
       for (int j = steps; j < upto && !done[b]; ++j) {
         // the stop rule of the single-set path (FP32 floor included)
         tnorm[b] = std::max(tnorm[b], std::fabs(ta[j]) + tb[j] + tb[j + 1]);
-        const double E = tridiag_lowest(ta.data(), tb.data() + 1, j + 1, 0);
+        const double E = ritz[b].next(ta.data(), tb.data() + 1, j + 1);
         const bool bd = !(tb[j + 1] > 1e-12 * tnorm[b]);
         const double floor32 = vtype == EDX_F32 ? 2.0 * 1.1920929e-7 * tnorm[b] : 0.0;
         bool ok = j > 0 &&

@@ -71,7 +71,7 @@ edx_status lanczos_ground_state_static(const edx_sector* s, const edx_lanczos_op
   }
   void* ws = nullptr;
   EDX_TRY(scratch_ptr(dev, &ws));
-  return lanczos_ground_state_impl(s, o, ws, kScratchBytes, e0, psi0, rep, st);
+  return lanczos_ground_state_impl(s, o, ws, kScratchBytes, e0, psi0, rep, st, false);
 }
 
 }  // namespace edx

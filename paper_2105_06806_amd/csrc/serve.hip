@@ -294,7 +294,7 @@ void worker_main(edx_server* S, int slot) {
         lo.start = nullptr;
         edx_lanczos_report rep{};
         double e0 = 0;
-        st2 = lanczos_ground_state_impl(sec, &lo, ws, lw, &e0, psi, &rep, st);
+        st2 = lanczos_ground_state_impl(sec, &lo, ws, lw, &e0, psi, &rep, st, false);
         R->e0 = e0;
         R->iters = rep.iters;
         if ((st2 == EDX_OK || st2 == EDX_E_DEGENERATE) && o.ngf > 0) {
