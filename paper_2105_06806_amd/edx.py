@@ -206,10 +206,17 @@ def _check(st, ok=(EDX_OK,)):
     return st
 
 
+# The current stream's handle without building a torch.cuda.Stream object for
+# it (2.7 us, against 4.3 us for the whole launch of a small product)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream):
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _vtype_of(t):
@@ -335,8 +342,9 @@ def hv(sector, v, w, stream=None, ld=0):
     otherwise column stride ld >= D_up (ld * D_dw elements, padding rows of w
     written as zero), e.g. sector.ld."""
     _vec_len(sector, v, w, ld)
-    _check(lib.edx_hv(sector.handle, _vtype_of(v), _P(v.data_ptr()), _P(w.data_ptr()), int(ld),
-                      _stream_ptr(stream)))
+    st = lib.edx_hv(sector.handle, _vtype_of(v), v.data_ptr(), w.data_ptr(), int(ld), _stream_ptr(stream))
+    if st != EDX_OK:
+        _check(st)
     return w
 
 
