@@ -489,6 +489,39 @@ inline size_t nd_tab_lds(int P, int nt, size_t tsz) {
 
 constexpr int64_t kWinGroups = 32;   // column groups per XCD in a window (its CUs)
 
+// Which columns: group cb = workgroup index (order 0), or XCD-contiguous
+// numbering (orders 1 and 2): workgroups go round-robin over the 8 XCDs, so
+// workgroup b takes group x*q + min(x, r) + b/8 (x = b % 8) and the groups
+// running at once on one XCD are consecutive; their spin-down neighbours
+// overlap and are served by that XCD's L2.  Orders 3 and 4: the same inside
+// windows that all XCDs walk together.  Orders 2 and 4 walk the columns
+// sorted by impurity occupation, where consecutive columns share more
+// neighbours.
+__device__ __forceinline__ int64_t column_group(int order) {
+  int64_t cb = blockIdx.x;
+  if (order == 1 || order == 2) {
+    const int64_t nblk = gridDim.x, q8 = nblk / 8, r8 = nblk % 8;
+    const int64_t x8 = blockIdx.x % 8;
+    cb = x8 * q8 + std::min<int64_t>(x8, r8) + blockIdx.x / 8;
+  } else if (order >= 3) {
+    // windows of 8 * wg consecutive groups (wg = 32, one per CU, over the
+    // columns in listing order; 64 over the sorted columns -- the measured
+    // best): inside a window XCD x takes the groups x*wg ... x*wg + wg - 1,
+    // so the groups resident on one XCD are consecutive (their neighbours
+    // meet in its L2) and all XCDs work in the same window (its neighbour
+    // columns meet in the MALL); the last, partial window keeps the
+    // workgroup order
+    const int64_t wg = order == 3 ? kWinGroups : 2 * kWinGroups;
+    const int64_t win = 8 * wg;
+    const int64_t b = blockIdx.x, w0 = b - b % win;
+    if (w0 + win <= (int64_t)gridDim.x) {
+      const int64_t r = b - w0;
+      cb = w0 + (r % 8) * wg + r / 8;
+    }
+  }
+  return cb;
+}
+
 template <typename T, int WUP, int WDW, int NC, bool ND, bool PH, bool BUF>
 __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restrict__ v,
                                                    T* __restrict__ w,
@@ -534,35 +567,7 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
       n_amp[k] = nd.amp[k];
     }
   }
-  // Which columns: group cb = workgroup index (order 0), or XCD-contiguous
-  // numbering (orders 1 and 2): workgroups go round-robin over the 8 XCDs, so
-  // workgroup b takes group x*q + min(x, r) + b/8 (x = b % 8) and the groups
-  // running at once on one XCD are consecutive; their spin-down neighbours
-  // overlap and are served by that XCD's L2.  Orders 3 and 4: the same inside
-  // windows that all XCDs walk together.  Orders 2 and 4 walk the columns
-  // sorted by impurity occupation, where consecutive columns share more
-  // neighbours.
-  int64_t cb = blockIdx.x;
-  if (order == 1 || order == 2) {
-    const int64_t nblk = gridDim.x, q8 = nblk / 8, r8 = nblk % 8;
-    const int64_t x8 = blockIdx.x % 8;
-    cb = x8 * q8 + std::min<int64_t>(x8, r8) + blockIdx.x / 8;
-  } else if (order >= 3) {
-    // windows of 8 * wg consecutive groups (wg = 32, one per CU, over the
-    // columns in listing order; 64 over the sorted columns -- the measured
-    // best): inside a window XCD x takes the groups x*wg ... x*wg + wg - 1,
-    // so the groups resident on one XCD are consecutive (their neighbours
-    // meet in its L2) and all XCDs work in the same window (its neighbour
-    // columns meet in the MALL); the last, partial window keeps the
-    // workgroup order
-    const int64_t wg = order == 3 ? kWinGroups : 2 * kWinGroups;
-    const int64_t win = 8 * wg;
-    const int64_t b = blockIdx.x, w0 = b - b % win;
-    if (w0 + win <= (int64_t)gridDim.x) {
-      const int64_t r = b - w0;
-      cb = w0 + (r % 8) * wg + r / 8;
-    }
-  }
+  const int64_t cb = column_group(order);
   const int64_t j0 = cb * NC;
   const int nc = (int)std::min<int64_t>(NC, a.ddw - j0);
   int64_t jc[NC];   // this workgroup's columns (clamped copies past the end)
@@ -818,6 +823,307 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
   }
 }
 
+// ---------------------------------------------------------------- fused pass, 16-byte lanes
+// The fused pass with VEC = 2 consecutive FP64 rows a lane, where every column
+// starts on a 16-byte boundary: all vector and table accesses are 16-byte
+// loads.  The load path of a CU takes 8 clocks for a wave's 4-byte loads, 16 for
+// 8-byte and 17 for 16-byte ones (all from L1, measured), and the row-a-lane
+// pass spends 80 % of its cycles there (Ns=14 FP64, 2 columns: 392 clocks of 480
+// a row pass), so 16-byte lanes halve what bounds it.  Half-filled Ns=12 8.4 ->
+// 7.0 us, Ns=13 23.2 -> 20.3 us, Ns=14 Norb=2 84.9 -> 74.1 us, Ns=16 1639 -> 1480
+// us (best plan of either).  FP32 would need four rows a lane, and the four rows'
+// LDS reads, four words apart, then cost more than the loads save (Ns=14 50 ->
+// 56 us; storing every fourth row together did not help), so FP32 keeps a row a
+// lane.
+// Same terms in the same order as k_hv_fused: bit-identical products.
+// Of the spin-down hops the first 8 slots sit in scalar registers; wider rows
+// take their further slots, a chunk of 8 at a time, from the hop table again
+// (few columns have more than 8 real hops), which keeps a lane's gathers and
+// the scalars within the registers.
+template <typename T>
+using Lane16 = T __attribute__((ext_vector_type(16 / sizeof(T))));
+
+template <typename T>
+__device__ __forceinline__ Lane16<T> buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff,
+                                                uint32_t soff) {
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  const u4 x = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
+  return __builtin_bit_cast(Lane16<T>, x);
+}
+
+template <typename T, int WUP, int WDW, int NC, bool ND, bool PH>
+__global__ __launch_bounds__(1024) void k_hv_vec(HvArgs<T> a, const T* __restrict__ v,
+                                                 T* __restrict__ w,
+                                                 const double* __restrict__ vscale,
+                                                 double* __restrict__ partial, int order,
+                                                 const int32_t* __restrict__ corder, NdTab<T> nd,
+                                                 PhArgs<T> ph, uint32_t vbytes) {
+  using VT = Lane16<T>;
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  constexpr uint32_t VEC = 16 / sizeof(T);
+  static_assert(VEC == 2, "two patterns a lane are read as one 16-bit word");
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  bool ph_lo = false, ph_hi = false;
+  T ph_sp = T(0), ph_sp1 = T(0);
+  if constexpr (PH) {
+    const int p = blockIdx.y;
+    v += p * ph.slice;
+    w += p * ph.slice;
+    a.W += p * 64;
+    if (partial) partial += (int64_t)p * gridDim.x;
+    ph_lo = p > 0;
+    ph_hi = p + 1 < ph.dph;
+    ph_sp = (T)sqrt((double)p);
+    ph_sp1 = (T)sqrt((double)(p + 1));
+  }
+  // LDS layout of k_hv_fused
+  T* vs = reinterpret_cast<T*>(smem_raw);
+  T* amp = reinterpret_cast<T*>(
+      smem_raw + al16((size_t)NC * ((a.dup + VEC - 1) / VEC * VEC) * sizeof(T)));
+  T* Wt = amp + kAmpTable;
+  double* red = reinterpret_cast<double*>(Wt + 64);
+  const uint32_t dup = (uint32_t)a.dup;
+  const int64_t ld = a.ld;
+  int* n_off = nullptr;
+  int2* n_dud = nullptr;
+  T* n_amp = nullptr;
+  if (ND) {
+    unsigned char* q = reinterpret_cast<unsigned char*>(red + 16);
+    n_off = reinterpret_cast<int*>(q);
+    n_dud = reinterpret_cast<int2*>(q + al16((size_t)(nd.P * nd.P + 1) * 4));
+    n_amp = reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(n_dud) +
+                                 al16((size_t)nd.nt * 8));
+    for (int k = threadIdx.x; k <= nd.P * nd.P; k += blockDim.x) n_off[k] = nd.off[k];
+    for (int k = threadIdx.x; k < nd.nt; k += blockDim.x) {
+      n_dud[k] = make_int2(nd.du[k], nd.dd[k]);
+      n_amp[k] = nd.amp[k];
+    }
+  }
+  const int64_t j0 = column_group(order) * NC;
+  const int nc = (int)std::min<int64_t>(NC, a.ddw - j0);
+  int64_t jc[NC];      // this workgroup's columns (clamped copies past the end)
+  uint32_t coff[NC];   // and their byte offsets
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int64_t jj = std::min<int64_t>(j0 + c, a.ddw - 1);
+    jc[c] = (order == 2 || order == 4) ? (int64_t)__builtin_amdgcn_readfirstlane(corder[jj]) : jj;
+    coff[c] = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)jc[c] * ld * sizeof(T)));
+  }
+  const T sc = vscale ? (T)(*vscale) : T(1);
+  const __amdgpu_buffer_rsrc_t vres =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(v), 0, (int)vbytes, 0x00020000);
+  // first staging pass in flight during the set-up (see stage_issue_buf)
+  constexpr int SU = 10 / NC;
+  const uint32_t pass = blockDim.x * VEC;           // rows per pass over the block
+  const uint32_t last = (dup - 1) / VEC * VEC;      // first row of the last lane with rows
+  VT sb[NC][SU];
+  auto issue = [&](uint32_t b0) {
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      if (b0 + (uint32_t)u * pass >= dup) break;
+      const uint32_t row = std::min(b0 + (uint32_t)u * pass + (uint32_t)threadIdx.x * VEC, last);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        sb[c][u] = buf_load16<T>(vres, row * (uint32_t)sizeof(T), coff[c]);
+    }
+  };
+  auto put = [&](uint32_t b0) {
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      if (b0 + (uint32_t)u * pass >= dup) break;
+      const uint32_t row = b0 + (uint32_t)u * pass + threadIdx.x * VEC;
+#pragma unroll
+      for (uint32_t e = 0; e < VEC; ++e)
+        if (row + e < dup)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) vs[(row + e) * NC + c] = sb[c][u][e] * sc;
+    }
+  };
+  issue(0);
+  for (int i = threadIdx.x; i < kAmpTable; i += blockDim.x) amp[i] = a.amp[i];
+  for (int i = threadIdx.x; i < 64; i += blockDim.x) Wt[i] = a.W[i];
+  uint32_t goff[NC][8];   // byte offsets of the first 8 neighbour columns
+  T gamp[NC][8];          // their amplitudes times the vector scale
+  int nreal[NC];          // real (not padding) entries of the column's hop row
+  int mreal = 0;
+  T ed[NC];
+  int pd[NC];
+  T gd[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int64_t j = jc[c];
+    ed[c] = a.edw[j];
+    pd[c] = a.pdw[j];
+    gd[c] = PH ? gpat(ph, pd[c]) : T(0);
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < WDW; ++k) {
+      const uint32_t f = a.hdw[j * WDW + k];
+      cnt += (f >> kAmpShift) != kPadPair ? 1 : 0;
+      if (k < 8) {
+        goff[c][k] = __builtin_amdgcn_readfirstlane(
+            (uint32_t)((uint64_t)(f & kColMask) * (uint64_t)ld * sizeof(T)));
+        gamp[c][k] = uniform(a.amp[f >> kAmpShift] * sc);
+      }
+    }
+    nreal[c] = (int)__builtin_amdgcn_readfirstlane((uint32_t)cnt);
+    mreal = std::max(mreal, nreal[c]);
+  }
+  put(0);
+  for (uint32_t b0 = SU * pass; b0 < dup; b0 += SU * pass) {
+    issue(b0);
+    put(b0);
+  }
+  constexpr int HW = 3 * WUP / 4;   // 32-bit words of a compact spin-up row
+  const __amdgpu_buffer_rsrc_t wres =
+      __builtin_amdgcn_make_buffer_rsrc(w, 0, (int)vbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t hres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(a.hrow), 0, (int)(dup * HW * 4), 0x00020000);
+  const __amdgpu_buffer_rsrc_t eres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<T*>(a.eup), 0, (int)(dup * sizeof(T)), 0x00020000);
+  const __amdgpu_buffer_rsrc_t pres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(a.pup), 0, (int)((dup + VEC - 1) / VEC * VEC), 0x00020000);
+  __syncthreads();
+  double dot = 0.0;
+  for (uint32_t iu = threadIdx.x * VEC; iu < dup; iu += pass) {
+    const uint32_t voff = iu * (uint32_t)sizeof(T);
+    // the rows' own tables first (loads complete in issue order); rows past the
+    // last read as zero
+    uint32_t r[VEC * HW];
+#pragma unroll
+    for (int q = 0; q < (int)VEC * HW / 4; ++q) {
+      const u4 x = __builtin_amdgcn_raw_buffer_load_b128(hres, (int)(iu * HW * 4 + q * 16), 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[4 * q + i] = x[i];
+    }
+    const VT eu = buf_load16<T>(eres, voff, 0);
+    const uint32_t pats = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(pres, (int)iu, 0, 0);
+    VT g[NC][8];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) g[c][k] = buf_load16<T>(vres, voff, goff[c][k]);
+    VT pv[NC], pn[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      pv[c] = VT(T(0));
+      pn[c] = VT(T(0));
+      if constexpr (PH) {
+        const int64_t e0 = (int64_t)iu + jc[c] * ld;
+        if (ph_lo) pv[c] = *reinterpret_cast<const VT*>(v + e0 - ph.slice);
+        if (ph_hi) pn[c] = *reinterpret_cast<const VT*>(v + e0 + ph.slice);
+      }
+    }
+    // spin-up hops and the diagonal of every row, while the gathers arrive
+    VT acc[NC], xv[NC];
+#pragma unroll
+    for (uint32_t e = 0; e < VEC; ++e) {
+      T s[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) s[c] = T(0);
+      const uint32_t* re = r + e * HW;
+#pragma unroll
+      for (int q = 0; q < WUP / 4; ++q) {
+        const uint32_t ai4 = re[WUP / 2 + q];
+        // real hops come first: past the eighth, stop where no lane has more
+        if (WUP > 8 && q >= 2 && __all(ai4 == kPadPair * 0x01010101u)) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = 4 * q + i;
+          const uint32_t col = (re[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
+          const T ak = amp[(ai4 >> (8 * i)) & 0xFFu];
+          const T* src = vs + __umul24(col, (uint32_t)NC);
+#pragma unroll
+          for (int c = 0; c < NC; ++c) s[c] += ak * src[c];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        acc[c][e] = s[c];
+        xv[c][e] = vs[(iu + e) * (uint32_t)NC + c];
+      }
+    }
+    VT s2[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      s2[c] = VT(T(0));
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (uint32_t e = 0; e < VEC; ++e) s2[c][e] += gamp[c][k] * g[c][k][e];
+    }
+    if constexpr (WDW > 8) {
+#pragma unroll
+      for (int k0 = 8; k0 < WDW; k0 += 8) {
+        if (mreal <= k0) break;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const uint32_t* __restrict__ hj = a.hdw + jc[c] * WDW + k0;
+          VT h[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            h[k] = VT(T(0));
+            if (k0 + k < nreal[c])
+              h[k] = buf_load16<T>(vres, voff, (uint32_t)((uint64_t)(hj[k] & kColMask) *
+                                                             (uint64_t)ld * sizeof(T)));
+          }
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (k0 + k < nreal[c]) {
+              const T ga = amp[hj[k] >> kAmpShift] * sc;
+#pragma unroll
+              for (uint32_t e = 0; e < VEC; ++e) s2[c][e] += ga * h[k][e];
+            }
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      VT out;
+#pragma unroll
+      for (uint32_t e = 0; e < VEC; ++e) {
+        const int patu = (int)((pats >> (8 * e)) & 0xFFu);
+        const T x = xv[c][e];
+        T res = acc[c][e] + (eu[e] + ed[c] + Wt[patu * 8 + pd[c]]) * x + s2[c][e];
+        if constexpr (PH)
+          res += (gpat(ph, patu) + gd[c]) * (ph_sp * pv[c][e] + ph_sp1 * pn[c][e]) * sc;
+        if constexpr (ND) {
+          // spin exchange / pair hopping: sources near (row, jc[c])
+          if (iu + e < dup) {
+            const int key = patu * nd.P + pd[c];
+            const int t1 = n_off[key + 1];
+            T sn = T(0);
+            for (int t = n_off[key]; t < t1; ++t) {
+              const int2 sh = n_dud[t];
+              sn += n_amp[t] * v[(int64_t)(iu + e) + sh.x + (jc[c] + sh.y) * ld];
+            }
+            res += sn * sc;
+          }
+        }
+        // rows past the last are padding: written as zero
+        out[e] = iu + e < dup ? res : T(0);
+        if (c < nc && iu + e < dup) dot += (double)x * (double)res;
+      }
+      // streaming store: not read again in this pass.  The column's offset goes
+      // into the lane offset and the scalar offset stays 0: with a register
+      // there the compiler lets the next instruction overwrite the data
+      // registers at once, and on this chip the store's third dword then came
+      // out as that instruction's result now and then.
+      if (c < nc)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, out), wres,
+                                               (int)(voff + coff[c]), 0, 2);
+    }
+  }
+  for (int64_t i = (int64_t)last + VEC + threadIdx.x; i < ld; i += blockDim.x)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c < nc) w[i + jc[c] * ld] = T(0);
+  if (partial) {
+    const double s = block_sum(dot, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+  }
+}
+
 // ---------------------------------------------------------------- fused launches
 template <typename T>
 struct FusedOrder {
@@ -853,6 +1159,19 @@ edx_status launch_fused_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
   return EDX_OK;
 }
 
+template <typename T, int WUP, int WDW, int NC, bool ND, bool PH>
+edx_status launch_vec_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hipStream_t st,
+                        const T* v, T* w, const double* vscale, double* partial,
+                        FusedOrder<T> fo, uint32_t vbytes) {
+  lds += NC * 16;   // the staged columns, rounded up to whole lanes
+  EDX_HIP(allow_lds((const void*)k_hv_vec<T, WUP, WDW, NC, ND, PH>, lds));
+  const dim3 grid((unsigned)nblk, PH ? (unsigned)fo.pa.dph : 1u);
+  hipLaunchKernelGGL((k_hv_vec<T, WUP, WDW, NC, ND, PH>), grid, dim3(nthr), lds, st, a, v, w,
+                     vscale, partial, fo.order, fo.corder, fo.nd, fo.pa, vbytes);
+  EDX_HIP(hipGetLastError());
+  return EDX_OK;
+}
+
 template <typename T, int WUP, int WDW, int NC>
 edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hipStream_t st,
                           const T* v, T* w, const double* vscale, double* partial,
@@ -862,6 +1181,24 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
   // it and keep global loads
   const uint64_t vb = (uint64_t)a.ld * (uint64_t)a.ddw * sizeof(T);
   const bool buf = vb <= 0xFFFFFFFFull && a.hrow;
+  // 16-byte lanes: FP64 with columns on 16-byte boundaries and of more than 256
+  // rows (shorter ones leave half the lanes idle: Ns=10 3.6 -> 3.9 us), one or
+  // two columns a block; with H_nd not where one column fills the LDS (its term
+  // loops then have 16 waves of half as many lanes: Ns=16 Norb=2 2021 -> 2153 us)
+  if constexpr (NC <= 2 && sizeof(T) == 8) {
+    if (buf && a.ld % 2 == 0 && a.dup > 256 && lds + 16 * NC <= 160 * 1024 &&
+        ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(w)) & 15u) == 0 &&
+        !(fo.nd.nt > 0 && NC == 1 && lds > 80 * 1024)) {
+      if (fo.nd.nt > 0)
+        return launch_vec_n<T, WUP, WDW, NC, true, false>(a, nblk, nthr, lds, st, v, w, vscale,
+                                                          partial, fo, (uint32_t)vb);
+      if (fo.ph)
+        return launch_vec_n<T, WUP, WDW, NC, false, true>(a, nblk, nthr, lds, st, v, w, vscale,
+                                                          partial, fo, (uint32_t)vb);
+      return launch_vec_n<T, WUP, WDW, NC, false, false>(a, nblk, nthr, lds, st, v, w, vscale,
+                                                         partial, fo, (uint32_t)vb);
+    }
+  }
   if (fo.nd.nt > 0)
     return buf ? launch_fused_n<T, WUP, WDW, NC, true, false, true>(
                      a, nblk, nthr, lds, st, v, w, vscale, partial, fo, fo.nd, (uint32_t)vb)
@@ -1111,32 +1448,42 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   const int64_t slices = s->dph > 1 && !s->nd ? s->dph : 1;
   auto blocks = [&](int c) { return slices * ((s->ddw + c - 1) / c); };
   auto fits = [&](int c) { return smem_header() + 16 + ndl + c * colb <= kLdsBytes; };
-  // Columns per block: a spin-up table row serves them all.  Three FP32 columns
-  // from 40 KB on (Ns=16 2 -> 3 columns: 767 -> 701 us) or, with 8-slot rows,
-  // from 24 KB (Ns=15 167 -> 162 us); else two; fewer where that leaves less
-  // than 1.5 blocks per CU (Ns=11 FP64, 462 columns: 1 column 4.6 us, 2 columns
-  // 5.0 us).  FP64 with H_nd takes one: the second column's gathers and table
-  // pointers spill to scratch (Kanamori Ns=12 FP64 35 -> 12 us, Ns=14 350 -> 108
-  // us, Ns=15 Norb=3 1376 -> 319 us), as do 16-slot rows in grids of one round
-  // (Norb=2 Ns=12 FP64 12.3 -> 11.2 us); FP32 with H_nd, 12 bytes a hop less,
-  // only in such grids (Ns=12 9.6 -> 9.0 us).
+  // Columns per block: a spin-up table row serves them all.
+  // FP32: three from 40 KB on (Ns=16 2 -> 3 columns: 767 -> 701 us) or, with
+  // 8-slot rows, from 24 KB (Ns=15 167 -> 162 us); else two; with H_nd one in
+  // grids of one round (Ns=12 9.6 -> 9.0 us).
+  // FP64 on 16-byte lanes: one (Ns=12 8.1 -> 7.0 us, Ns=13 23.1 -> 20.3 us: more
+  // waves fit), two where hop rows are wide or there is H_nd and the columns are
+  // long (Norb=2 Ns=14 78.6 -> 74.1 us, with H_nd 108 -> 95 us), and from 2048
+  // columns on, where it costs a product little (Ns=14 80 -> 83 us) and lets the
+  // Lanczos update fold the step's reductions.
+  // Either: fewer where less than 1.5 blocks per CU are left (Ns=11, 462 columns:
+  // 1 column 4.6 us, 2 columns 5.0 us).
+  const bool ph = slices > 1;
   int c = 2;
-  if (!f64 && !s->nd && (colb >= 40 * 1024 || (!wide && colb >= 24 * 1024))) c = 3;
-  if (f64 && s->nd) c = 1;
-  if (c == 2 && blocks(2) <= 512 && (s->nd || (f64 && s->up.wpad > 8 && s->dw.wpad > 8))) c = 1;
+  if (f64)
+    c = !ph && (((wide || s->nd) && s->dup > 1024) || s->ddw > 2048) ? 2 : 1;
+  else if (!s->nd && (colb >= 40 * 1024 || (!wide && colb >= 24 * 1024)))
+    c = 3;
+  else if (s->nd && blocks(2) <= 512)
+    c = 1;
   while (c > 1 && (!fits(c) || blocks(c) < 384)) --c;
   p.col_cols = c;
   p.col_blocks = (int)((s->ddw + c - 1) / c);
   // Threads: all of a CU's waves in one block where its LDS image leaves room
   // for one block only (Norb=2 Ns=16 FP64 with H_nd: 512 -> 1024 threads 2303 ->
-  // 2041 us); four blocks of 256 instead of two of 512 where the columns are
-  // short -- a grid of 513-1024 blocks then runs in one round (Ns=13 25.0 -> 23.3
-  // us FP64, 14.8 -> 14.4 us FP32) -- and with H_nd, whose term loops diverge.
+  // 2041 us; one FP64 column of 8-slot rows on 16-byte lanes is as fast with 8
+  // waves: Ns=16 1498 -> 1480 us); 256 where columns are short -- FP32 grids of
+  // 513-1024 blocks then run in one round (Ns=13 14.8 -> 14.4 us), FP64 up to 1024
+  // rows (Ns=12 7.4 -> 7.0 us) -- and for FP32 with H_nd, whose term loops diverge.
   const size_t lds = c * colb + ndl;
+  const bool shortc = f64 ? s->dup <= 1024
+                          : s->dup <= 256 || (s->dup <= 2048 && blocks(c) > 512) ||
+                                (s->nd && s->dup <= 4096);
   p.col_threads = 512;
   if (lds > kLdsBytes / 2)
-    p.col_threads = 1024;
-  else if (s->dup <= 256 || (s->dup <= 2048 && blocks(c) > 512) || (s->nd && s->dup <= 4096))
+    p.col_threads = f64 && c == 1 && !wide && !s->nd ? 512 : 1024;
+  else if (shortc)
     p.col_threads = 256;
   // Order: XCD-contiguous groups while the vector stays in the MALL next to its
   // product (Ns=14 FP64 86.2 -> 84.4 us against windows), beyond that inside
