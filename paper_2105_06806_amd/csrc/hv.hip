@@ -824,9 +824,8 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
 }
 
 // ---------------------------------------------------------------- fused pass, 16-byte lanes
-// The fused pass with VEC = 2 consecutive FP64 rows a lane, where every column
-// starts on a 16-byte boundary: all vector and table accesses are 16-byte
-// loads.  The load path of a CU takes 8 clocks for a wave's 4-byte loads, 16 for
+// The fused pass with VEC = 2 consecutive FP64 rows a lane: all vector and table
+// accesses are 16-byte loads.  The load path of a CU takes 8 clocks for a wave's 4-byte loads, 16 for
 // 8-byte and 17 for 16-byte ones (all from L1, measured), and the row-a-lane
 // pass spends 80 % of its cycles there (Ns=14 FP64, 2 columns: 392 clocks of 480
 // a row pass), so 16-byte lanes halve what bounds it.  Half-filled Ns=12 8.4 ->
@@ -1109,9 +1108,13 @@ __global__ __launch_bounds__(1024) void k_hv_vec(HvArgs<T> a, const T* __restric
       // there the compiler lets the next instruction overwrite the data
       // registers at once, and on this chip the store's third dword then came
       // out as that instruction's result now and then.
-      if (c < nc)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, out), wres,
-                                               (int)(voff + coff[c]), 0, 2);
+      if (c < nc) {
+        if ((int64_t)iu + VEC <= ld)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, out), wres,
+                                                 (int)(voff + coff[c]), 0, 2);
+        else   // a dense odd column's last row: what follows is the next column
+          buf_store_nt<T>(wres, voff + coff[c], 0, out[0]);
+      }
     }
   }
   for (int64_t i = (int64_t)last + VEC + threadIdx.x; i < ld; i += blockDim.x)
@@ -1181,13 +1184,16 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
   // it and keep global loads
   const uint64_t vb = (uint64_t)a.ld * (uint64_t)a.ddw * sizeof(T);
   const bool buf = vb <= 0xFFFFFFFFull && a.hrow;
-  // 16-byte lanes: FP64 with columns on 16-byte boundaries and of more than 256
-  // rows (shorter ones leave half the lanes idle: Ns=10 3.6 -> 3.9 us), one or
-  // two columns a block; with H_nd not where one column fills the LDS (its term
+  // 16-byte lanes: FP64 with columns of more than 256 rows (shorter ones leave
+  // half the lanes idle: Ns=10 3.6 -> 3.9 us), one or two columns a block.  Buffer
+  // accesses need 4-byte boundaries only, so any column stride will do (dense odd
+  // columns, Norb=2 Ns=14 3003 rows 83.7 -> 79.1 us, Ns=15 359 -> 340 us); the
+  // phonon neighbours are read by global loads past the slice and keep to
+  // 16-byte boundaries.  With H_nd not where one column fills the LDS (its term
   // loops then have 16 waves of half as many lanes: Ns=16 Norb=2 2021 -> 2153 us)
   if constexpr (NC <= 2 && sizeof(T) == 8) {
-    if (buf && a.ld % 2 == 0 && a.dup > 256 && lds + 16 * NC <= 160 * 1024 &&
-        ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(w)) & 15u) == 0 &&
+    const bool al16 = a.ld % 2 == 0 && (reinterpret_cast<uintptr_t>(v) & 15u) == 0;
+    if (buf && (al16 || !fo.ph) && a.dup > 256 && lds + 16 * NC <= 160 * 1024 &&
         !(fo.nd.nt > 0 && NC == 1 && lds > 80 * 1024)) {
       if (fo.nd.nt > 0)
         return launch_vec_n<T, WUP, WDW, NC, true, false>(a, nblk, nthr, lds, st, v, w, vscale,
@@ -1472,8 +1478,8 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   p.col_blocks = (int)((s->ddw + c - 1) / c);
   // Threads: all of a CU's waves in one block where its LDS image leaves room
   // for one block only (Norb=2 Ns=16 FP64 with H_nd: 512 -> 1024 threads 2303 ->
-  // 2041 us; one FP64 column of 8-slot rows on 16-byte lanes is as fast with 8
-  // waves: Ns=16 1498 -> 1480 us); 256 where columns are short -- FP32 grids of
+  // 2041 us; FP64 with 8-slot rows on 16-byte lanes is as fast with 8 waves: Ns=16
+  // 1498 -> 1480 us, Ns=15 324 -> 321 us, dense 355 -> 340 us); 256 where columns are short -- FP32 grids of
   // 513-1024 blocks then run in one round (Ns=13 14.8 -> 14.4 us), FP64 up to 1024
   // rows (Ns=12 7.4 -> 7.0 us) -- and for FP32 with H_nd, whose term loops diverge.
   const size_t lds = c * colb + ndl;
@@ -1482,7 +1488,7 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
                                 (s->nd && s->dup <= 4096);
   p.col_threads = 512;
   if (lds > kLdsBytes / 2)
-    p.col_threads = f64 && c == 1 && !wide && !s->nd ? 512 : 1024;
+    p.col_threads = f64 && !wide && !s->nd ? 512 : 1024;
   else if (shortc)
     p.col_threads = 256;
   // Order: XCD-contiguous groups while the vector stays in the MALL next to its

@@ -1,10 +1,11 @@
 """The FP64 product on 16-byte lanes against the row-a-lane pass and the oracle.
 
-The lanes need columns on 16-byte boundaries: with an odd column stride the
-row-a-lane pass runs instead, and both sum the same terms in the same order, so
-their products agree bit for bit.  Odd and even numbers of rows and columns, one
-and two columns a workgroup (with a short last one), hop rows of 8, 16 and 24
-slots, H_nd and phonon terms; the padding rows of w come out as zero.
+Three columns a workgroup take the row-a-lane pass; both passes sum the same
+terms in the same order, so their products agree bit for bit.  Odd and even
+numbers of rows and columns, dense columns and even and odd strides, one and
+two columns a workgroup (with a short last one), hop rows of 8, 16 and 24 slots,
+H_nd and phonon terms; the padding rows of w come out as zero and nothing past
+its end is written.
 """
 import numpy as np
 import pytest
@@ -43,24 +44,24 @@ def test_lanes_equal_rows(edx, norb, nbath, nup, ndw, kw):
     nc = S.ddw * S.dph
     x = torch.as_tensor(inputs.random_vector(S.dim, seed=8), device="cuda")
     even = S.dup + (S.dup & 1) + 6
-    odd = even + 1
-    for cols in (1, 2):
+    ref = None
+    for cols in (3, 1, 2):
         for threads in (256, 512):
             edx.set_plan(S, "f64", mode=2, col_cols=cols, col_threads=threads, col_order=1)
-            got = {}
-            for ld in (even, odd):
+            for ld in (S.dup, even, even + 1):
                 v = torch.full((nc, ld), float("nan"), dtype=torch.float64, device="cuda")
                 v[:, : S.dup] = x.view(nc, S.dup)
-                w = torch.full_like(v, 5.0)
+                buf = torch.full((nc * ld + 64,), 5.0, dtype=torch.float64, device="cuda")
+                w = buf[: nc * ld].view(nc, ld)
                 for _ in range(3):     # repeated: a lost store would come and go
                     edx.hv(S, v.view(-1), w.view(-1), ld=ld)
                     assert torch.count_nonzero(w[:, S.dup:]) == 0
-                    y = w[:, : S.dup].clone()
-                    assert ld not in got or torch.equal(got[ld], y)
-                    got[ld] = y
-            assert torch.equal(got[even], got[odd]), (cols, threads)
+                    if ref is None:
+                        ref = w[:, : S.dup].clone()
+                    assert torch.equal(w[:, : S.dup], ref), (cols, threads, ld)
+                assert bool((buf[nc * ld:] == 5.0).all())
     if not kw:
-        ref = kron.KronH(m, nup, ndw).matvec(x.cpu().numpy())
-        scale = np.abs(ref).max()
+        y = kron.KronH(m, nup, ndw).matvec(x.cpu().numpy())
+        scale = np.abs(y).max()
         # about 40 terms an element, each rounded once: 1e-13 of the largest element is 20 times that
-        assert np.abs(got[even].reshape(-1).cpu().numpy() - ref).max() <= 1e-13 * scale
+        assert np.abs(ref.reshape(-1).cpu().numpy() - y).max() <= 1e-13 * scale
