@@ -850,7 +850,10 @@ __device__ __forceinline__ Lane16<T> buf_load16(__amdgpu_buffer_rsrc_t r, uint32
   return __builtin_bit_cast(Lane16<T>, x);
 }
 
-template <typename T, int WUP, int WDW, int NC, bool ND, bool PH>
+// ODD: the column stride may be odd, and a dense column's last row then has no
+// partner to be stored with (a variant of its own, so that the others store
+// without a branch).
+template <typename T, int WUP, int WDW, int NC, bool ND, bool PH, bool ODD>
 __global__ __launch_bounds__(1024) void k_hv_vec(HvArgs<T> a, const T* __restrict__ v,
                                                  T* __restrict__ w,
                                                  const double* __restrict__ vscale,
@@ -1109,7 +1112,7 @@ __global__ __launch_bounds__(1024) void k_hv_vec(HvArgs<T> a, const T* __restric
       // registers at once, and on this chip the store's third dword then came
       // out as that instruction's result now and then.
       if (c < nc) {
-        if ((int64_t)iu + VEC <= ld)
+        if (!ODD || (int64_t)iu + VEC <= ld)
           __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, out), wres,
                                                  (int)(voff + coff[c]), 0, 2);
         else   // a dense odd column's last row: what follows is the next column
@@ -1162,14 +1165,14 @@ edx_status launch_fused_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
   return EDX_OK;
 }
 
-template <typename T, int WUP, int WDW, int NC, bool ND, bool PH>
+template <typename T, int WUP, int WDW, int NC, bool ND, bool PH, bool ODD>
 edx_status launch_vec_n(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hipStream_t st,
                         const T* v, T* w, const double* vscale, double* partial,
                         FusedOrder<T> fo, uint32_t vbytes) {
   lds += NC * 16;   // the staged columns, rounded up to whole lanes
-  EDX_HIP(allow_lds((const void*)k_hv_vec<T, WUP, WDW, NC, ND, PH>, lds));
+  EDX_HIP(allow_lds((const void*)k_hv_vec<T, WUP, WDW, NC, ND, PH, ODD>, lds));
   const dim3 grid((unsigned)nblk, PH ? (unsigned)fo.pa.dph : 1u);
-  hipLaunchKernelGGL((k_hv_vec<T, WUP, WDW, NC, ND, PH>), grid, dim3(nthr), lds, st, a, v, w,
+  hipLaunchKernelGGL((k_hv_vec<T, WUP, WDW, NC, ND, PH, ODD>), grid, dim3(nthr), lds, st, a, v, w,
                      vscale, partial, fo.order, fo.corder, fo.nd, fo.pa, vbytes);
   EDX_HIP(hipGetLastError());
   return EDX_OK;
@@ -1195,14 +1198,17 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
     const bool al16 = a.ld % 2 == 0 && (reinterpret_cast<uintptr_t>(v) & 15u) == 0;
     if (buf && (al16 || !fo.ph) && a.dup > 256 && lds + 16 * NC <= 160 * 1024 &&
         !(fo.nd.nt > 0 && NC == 1 && lds > 80 * 1024)) {
-      if (fo.nd.nt > 0)
-        return launch_vec_n<T, WUP, WDW, NC, true, false>(a, nblk, nthr, lds, st, v, w, vscale,
-                                                          partial, fo, (uint32_t)vb);
-      if (fo.ph)
-        return launch_vec_n<T, WUP, WDW, NC, false, true>(a, nblk, nthr, lds, st, v, w, vscale,
-                                                          partial, fo, (uint32_t)vb);
-      return launch_vec_n<T, WUP, WDW, NC, false, false>(a, nblk, nthr, lds, st, v, w, vscale,
-                                                         partial, fo, (uint32_t)vb);
+      auto go = [&](auto nd_tag, auto ph_tag, auto odd_tag) {
+        return launch_vec_n<T, WUP, WDW, NC, decltype(nd_tag)::value, decltype(ph_tag)::value,
+                            decltype(odd_tag)::value>(a, nblk, nthr, lds, st, v, w, vscale,
+                                                      partial, fo, (uint32_t)vb);
+      };
+      constexpr std::true_type yes;
+      constexpr std::false_type no;
+      const bool odd = a.ld % 2 != 0;
+      if (fo.nd.nt > 0) return odd ? go(yes, no, yes) : go(yes, no, no);
+      if (fo.ph) return go(no, yes, no);
+      return odd ? go(no, no, yes) : go(no, no, no);
     }
   }
   if (fo.nd.nt > 0)
