@@ -323,7 +323,7 @@ void edx_lanczos_default_opts(edx_lanczos_opts* o) {
 size_t edx_workspace_bytes(const edx_sector* s, int32_t what, int32_t vtype, int32_t n) {
   if (!s || !valid_vtype(vtype) || n < 1) return 0;
   if (what == EDX_WS_LANCZOS) return lanczos_workspace_bytes(s, vtype, n, 0);
-  if (what == EDX_WS_GREEN) return green_workspace_bytes(s, vtype, n);
+  if (what == EDX_WS_GREEN) return green_workspace_bytes(s, vtype, n, true);
   if (what == 2) return lanczos_workspace_bytes(s, vtype, n, 2);   // full re-orthogonalisation
   if (what == EDX_WS_CHI) return chi_workspace_bytes(s, vtype, n);
   if (what == EDX_WS_PAIR) return pair_workspace_bytes(s, vtype, n);
@@ -447,7 +447,7 @@ edx_status edx_green_cf(const edx_sector* gs, const void* psi0, double e0, int32
   if (spin != 0 && spin != 1) return invalid("spin must be 0 or 1");
   if (opts->ngf > 4096) return invalid("ngf must be <= 4096");
   return green_cf_impl(gs, psi0, e0, orb, spin, opts, ws, ws_bytes, g_host, rep,
-                       static_cast<hipStream_t>(stream));
+                       static_cast<hipStream_t>(stream), true);
 }
 
 size_t edx_batch_workspace_bytes(const edx_sector* const* sectors, int32_t n, int32_t vtype,

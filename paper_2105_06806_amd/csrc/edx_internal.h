@@ -329,10 +329,13 @@ size_t lowest_workspace_bytes(const edx_sector* s, int vtype, int niter, int k);
 edx_status lowest_states_impl(const edx_sector* s, int k, const edx_lanczos_opts* o, int verify,
                               void* ws, size_t ws_bytes, double* e, void* psi,
                               edx_lowest_report* rep, hipStream_t st);
-size_t green_workspace_bytes(const edx_sector* s, int vtype, int ngf);
+// overlap: room for both branches at once where that pays (small sectors);
+// green_cf_impl uses it when it is there and overlap is asked for, which callers
+// that run several solves at once do not (their solves fill the device)
+size_t green_workspace_bytes(const edx_sector* s, int vtype, int ngf, bool overlap = false);
 edx_status green_cf_impl(const edx_sector* gs, const void* psi0, double e0, int orb, int spin,
                          const edx_gf_opts* o, void* ws, size_t ws_bytes, double* g_host,
-                         edx_gf_report* rep, hipStream_t st);
+                         edx_gf_report* rep, hipStream_t st, bool overlap = false);
 size_t chi_workspace_bytes(const edx_sector* s, int vtype, int ngf);
 // op 0: diagonal density operator c; op 1: excitonic operator of levels a < b
 edx_status chi_impl(const edx_sector* s, const void* psi0, double e0, const DiagCoef& c,

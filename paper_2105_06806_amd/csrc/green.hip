@@ -183,22 +183,27 @@ __global__ __launch_bounds__(256) void k_pair(const T* __restrict__ psi, T* __re
   }
 }
 
-__global__ void k_cf(const double* __restrict__ ap, const double* __restrict__ bp, int np,
-                     double wp, const double* __restrict__ ah, const double* __restrict__ bh,
-                     int nh, double wh, double e0, double beta, int lmats,
-                     double* __restrict__ g, int bosonic) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= lmats) return;
+// Two lanes a frequency, one per branch: each is a serial chain of divisions
+// (200 levels: 72 us with both branches in one lane), and blocks of one wave
+// spread the frequencies over the CUs.
+constexpr int kCfThreads = 64;
+
+__global__ __launch_bounds__(kCfThreads) void k_cf(
+    const double* __restrict__ ap, const double* __restrict__ bp, int np, double wp,
+    const double* __restrict__ ah, const double* __restrict__ bh, int nh, double wh, double e0,
+    double beta, int lmats, double* __restrict__ g, int bosonic) {
+  const int id = blockIdx.x * kCfThreads + threadIdx.x;
+  const int n = std::min(id >> 1, lmats - 1);
+  const int br = id & 1;
   // fermionic (2n+1) pi / beta, or bosonic 2n pi / beta
   const double wn = (2.0 * n + (bosonic ? 0.0 : 1.0)) * M_PI / beta;
+  const double* a = br == 0 ? ap : ah;
+  const double* b = br == 0 ? bp : bh;
+  const int m = br == 0 ? np : nh;
+  const double wgt = br == 0 ? wp : wh;
+  const double sg = br == 0 ? -1.0 : 1.0;
   double gr = 0.0, gi = 0.0;
-  for (int br = 0; br < 2; ++br) {
-    const double* a = br == 0 ? ap : ah;
-    const double* b = br == 0 ? bp : bh;
-    const int m = br == 0 ? np : nh;
-    const double wgt = br == 0 ? wp : wh;
-    const double sg = br == 0 ? -1.0 : 1.0;
-    if (m <= 0 || wgt == 0.0) continue;
+  if (m > 0 && wgt != 0.0) {
     // d = z + sg (a_k - e0) - b_{k+1}^2 / d, with z = i wn
     double dr = sg * (a[m - 1] - e0), di = wn;
     for (int k = m - 2; k >= 0; --k) {
@@ -210,9 +215,12 @@ __global__ void k_cf(const double* __restrict__ ap, const double* __restrict__ b
       di = wn - qi;
     }
     const double den = dr * dr + di * di;
-    gr += wgt * dr / den;
-    gi += -wgt * di / den;
+    gr = wgt * dr / den;
+    gi = -wgt * di / den;
   }
+  gr += __shfl_xor(gr, 1, 64);
+  gi += __shfl_xor(gi, 1, 64);
+  if (br != 0 || (id >> 1) >= lmats) return;
   g[2 * n] = gr;
   g[2 * n + 1] = gi;
 }
@@ -289,8 +297,8 @@ edx_status k_pair_apply(const edx_sector* src, const edx_sector* dst, int vtype,
 edx_status k_green_cf(const double* ap, const double* bp, int np, double wp, const double* ah,
                       const double* bh, int nh, double wh, double e0, double beta, int lmats,
                       double* g, hipStream_t st, int bosonic) {
-  const int grid = (lmats + 255) / 256;
-  hipLaunchKernelGGL(k_cf, dim3(grid), dim3(256), 0, st, ap, bp, np, wp, ah, bh, nh, wh, e0,
+  const int grid = (2 * lmats + kCfThreads - 1) / kCfThreads;
+  hipLaunchKernelGGL(k_cf, dim3(grid), dim3(kCfThreads), 0, st, ap, bp, np, wp, ah, bh, nh, wh, e0,
                      beta, lmats, g, bosonic);
   EDX_HIP(hipGetLastError());
   return EDX_OK;

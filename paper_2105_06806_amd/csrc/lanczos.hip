@@ -1312,7 +1312,77 @@ edx_status lowest_states_impl(const edx_sector* s, int k, const edx_lanczos_opts
 }
 
 // ---------------------------------------------------------------- Green
-size_t green_workspace_bytes(const edx_sector* s, int vtype, int ngf) {
+namespace {
+
+// The two branches of a Green's function are independent runs.  While a vector
+// stays in cache one branch leaves most of the chip idle (a step is two short
+// kernels one after the other), so they run side by side on two streams, up to
+// this vector size; beyond it a step is bound by bandwidth and they take turns
+// in one workspace.
+constexpr size_t kOverlapBytes = size_t(32) << 20;
+
+// A second stream for a call, with an event to order it behind the caller's:
+// kept for the life of the process (at most kMax of them), held by one call at
+// a time; the destructor waits for what is still running on it.
+class SideStream {
+ public:
+  SideStream() = default;
+  SideStream(const SideStream&) = delete;
+  SideStream& operator=(const SideStream&) = delete;
+  ~SideStream() {
+    if (!slot_) return;
+    (void)hipStreamSynchronize(slot_->st);
+    std::lock_guard<std::mutex> lk(mutex());
+    slot_->used = false;
+  }
+  // its work starts after what is on `st` now; false: no stream to be had
+  bool fork(hipStream_t st) {
+    slot_ = acquire();
+    return slot_ && hipEventRecord(slot_->ev, st) == hipSuccess &&
+           hipStreamWaitEvent(slot_->st, slot_->ev, 0) == hipSuccess;
+  }
+  hipStream_t stream() const { return slot_->st; }
+
+ private:
+  struct Slot {
+    hipStream_t st = nullptr;
+    hipEvent_t ev = nullptr;
+    int device = 0;
+    bool used = false;
+  };
+  static constexpr int kMax = 16;
+  static std::mutex& mutex() {
+    static std::mutex* m = new std::mutex;   // never destroyed: calls may outlive statics
+    return *m;
+  }
+  static Slot* acquire() {
+    static std::vector<Slot*>* all = new std::vector<Slot*>;
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess) return nullptr;
+    std::lock_guard<std::mutex> lk(mutex());
+    for (Slot* q : *all)
+      if (!q->used && q->device == device) {
+        q->used = true;
+        return q;
+      }
+    if ((int)all->size() >= kMax) return nullptr;
+    Slot q;
+    q.device = device;
+    q.used = true;
+    if (hipStreamCreateWithFlags(&q.st, hipStreamNonBlocking) != hipSuccess) return nullptr;
+    if (hipEventCreateWithFlags(&q.ev, hipEventDisableTiming) != hipSuccess) {
+      (void)hipStreamDestroy(q.st);
+      return nullptr;
+    }
+    all->push_back(new Slot(q));
+    return all->back();
+  }
+  Slot* slot_ = nullptr;
+};
+
+}  // namespace
+
+size_t green_workspace_bytes(const edx_sector* s, int vtype, int ngf, bool overlap) {
   // the largest neighbour sector of either spin bounds the vectors
   int64_t dmax = 1;
   const int ns = s->model.ns;
@@ -1334,8 +1404,9 @@ size_t green_workspace_bytes(const edx_sector* s, int vtype, int ngf) {
   const int64_t ddw_max = std::max({comb(ns, s->ndw - 1), comb(ns, s->ndw), comb(ns, s->ndw + 1)});
   const int hvb = (int)std::max<int64_t>(
       kMaxPartials, s->dph * (ddw_max + 8 + kNdMaxBlocks + (s->dph > 1 ? ddw_max / 8 + 1 : 0)));
-  return lanczos_ws_layout(dmax, vtype, ngf, 0, hvb, false, nullptr, nullptr) +
-         sizeof(double) * (2 * kMaxLmats + 4 * (ngf + 1)) + 512;
+  const size_t one = lanczos_ws_layout(dmax, vtype, ngf, 0, hvb, false, nullptr, nullptr);
+  const bool both = overlap && (size_t)dmax * vbytes(vtype) <= kOverlapBytes;
+  return (both ? 2 : 1) * one + sizeof(double) * (2 * kMaxLmats + 4 * (ngf + 1)) + 512;
 }
 
 namespace {
@@ -1382,7 +1453,7 @@ edx_status ensure_neighbours(const edx_sector* gs, int orb, int spin, hipStream_
 
 edx_status green_cf_impl(const edx_sector* gs, const void* psi0, double e0, int orb, int spin,
                          const edx_gf_opts* o, void* ws, size_t ws_bytes, double* g_host,
-                         edx_gf_report* rep, hipStream_t st) {
+                         edx_gf_report* rep, hipStream_t st, bool overlap) {
   const int vtype = o->vtype;
   const int ngf = o->ngf;
   if (o->lmats < 1 || o->lmats > kMaxLmats || ngf < 1 || !(o->beta > 0.0)) {
@@ -1397,36 +1468,60 @@ edx_status green_cf_impl(const edx_sector* gs, const void* psi0, double e0, int 
   EDX_TRY(ensure_neighbours(gs, orb, spin, st));
   edx_sector* const* nbs = neighbour_slot(gs, orb, spin);
   char* base = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(ws)));
-  double* gdev = nullptr;
   double w[2] = {0.0, 0.0};
   int nlen[2] = {0, 0};
   std::vector<double> ha[2], hb[2];
-  // the two branches run one after the other in the same workspace
-  for (int br = 0; br < 2; ++br) {
+  // the two branches side by side on two streams, each in its half of the
+  // workspace, or one after the other in the same
+  size_t lsize[2];
+  for (int br = 0; br < 2; ++br)
+    lsize[br] = lanczos_ws_layout(nbs[br] ? nbs[br]->vlen : 1, vtype, ngf, 0,
+                                  nbs[br] ? hv_partial_blocks(nbs[br], vtype) : 1, false, nullptr,
+                                  nullptr);
+  SideStream side;
+  const bool both =
+      overlap && nbs[0] && nbs[1] &&
+      (size_t)std::max(nbs[0]->vlen, nbs[1]->vlen) * vbytes(vtype) <= kOverlapBytes &&
+      green_workspace_bytes(gs, vtype, ngf, true) <= ws_bytes && side.fork(st);
+  LanczosWs Ls[2];
+  const hipStream_t sts[2] = {st, both ? side.stream() : st};
+  auto start = [&](int br) -> edx_status {
     const edx_sector* t = nbs[br];
-    LanczosWs L;
+    LanczosWs& L = Ls[br];
     lanczos_ws_layout(t ? t->vlen : 1, vtype, ngf, 0, t ? hv_partial_blocks(t, vtype) : 1, false,
-                      base, &L);
-    if (!t) continue;
-    EDX_TRY(k_apply_op(gs, t, vtype, psi0, L.vec, orb, spin, br == 0 ? 1 : 0, st));
-    EDX_TRY(k_norm2(vtype, L.vec, t->vlen, L.partial, st));
-    EDX_TRY(k_beta_finish(L.partial, elem_blocks(t->vlen), L.beta, L.scale, st));
+                      base + (both && br == 1 ? lsize[0] : 0), &L);
+    if (!t) return EDX_OK;
+    EDX_TRY(k_apply_op(gs, t, vtype, psi0, L.vec, orb, spin, br == 0 ? 1 : 0, sts[br]));
+    EDX_TRY(k_norm2(vtype, L.vec, t->vlen, L.partial, sts[br]));
+    return k_beta_finish(L.partial, elem_blocks(t->vlen), L.beta, L.scale, sts[br]);
+  };
+  // |phi| of a started branch; false: nothing to run
+  auto weight = [&](int br, bool* run) -> edx_status {
+    *run = false;
+    if (!nbs[br]) return EDX_OK;
     double nrm = 0.0;
-    EDX_HIP(hipMemcpyAsync(&nrm, L.beta, sizeof(double), hipMemcpyDeviceToHost, st));
-    EDX_HIP(hipStreamSynchronize(st));
+    EDX_HIP(hipMemcpyAsync(&nrm, Ls[br].beta, sizeof(double), hipMemcpyDeviceToHost, sts[br]));
+    EDX_HIP(hipStreamSynchronize(sts[br]));
     w[br] = nrm * nrm;
-    if (!(nrm > 0.0)) continue;
-    EDX_HIP(hipMemsetAsync(L.beta, 0, sizeof(double), st));
-    Pending pend;
-    for (int j = 0; j < ngf; ++j)
-      EDX_TRY(lanczos_step(t, vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr, st,
-                           j + 1 < ngf, &pend));
+    *run = nrm > 0.0;
+    if (*run) EDX_HIP(hipMemsetAsync(Ls[br].beta, 0, sizeof(double), sts[br]));
+    return EDX_OK;
+  };
+  Pending pend[2];
+  auto step = [&](int br, int j) {
+    const LanczosWs& L = Ls[br];
+    return lanczos_step(nbs[br], vtype, L, j, 0, L.alpha, L.beta, L.scale, nullptr, nullptr,
+                        sts[br], j + 1 < ngf, &pend[br]);
+  };
+  auto finish = [&](int br) -> edx_status {
+    const LanczosWs& L = Ls[br];
     ha[br].resize(ngf + 1);
     hb[br].resize(ngf + 1);
-    EDX_HIP(hipMemcpyAsync(ha[br].data(), L.alpha, sizeof(double) * ngf, hipMemcpyDeviceToHost, st));
+    EDX_HIP(hipMemcpyAsync(ha[br].data(), L.alpha, sizeof(double) * ngf, hipMemcpyDeviceToHost,
+                           sts[br]));
     EDX_HIP(hipMemcpyAsync(hb[br].data(), L.beta, sizeof(double) * (ngf + 1), hipMemcpyDeviceToHost,
-                           st));
-    EDX_HIP(hipStreamSynchronize(st));
+                           sts[br]));
+    EDX_HIP(hipStreamSynchronize(sts[br]));
     // truncate at the first breakdown
     double tn = 0.0;
     int len = ngf;
@@ -1438,16 +1533,29 @@ edx_status green_cf_impl(const edx_sector* gs, const void* psi0, double e0, int 
       }
     }
     nlen[br] = len;
+    return EDX_OK;
+  };
+  bool run[2] = {false, false};
+  if (both) {
+    for (int br = 0; br < 2; ++br) EDX_TRY(start(br));
+    for (int br = 0; br < 2; ++br) EDX_TRY(weight(br, &run[br]));
+    for (int j = 0; j < ngf; ++j)
+      for (int br = 0; br < 2; ++br)
+        if (run[br]) EDX_TRY(step(br, j));
+    for (int br = 0; br < 2; ++br)
+      if (run[br]) EDX_TRY(finish(br));
+  } else {
+    for (int br = 0; br < 2; ++br) {
+      EDX_TRY(start(br));
+      EDX_TRY(weight(br, &run[br]));
+      if (!run[br]) continue;
+      for (int j = 0; j < ngf; ++j) EDX_TRY(step(br, j));
+      EDX_TRY(finish(br));
+    }
   }
-  // G and the staged coefficients sit after the larger of the two layouts
-  size_t off = 0;
-  for (int br = 0; br < 2; ++br) {
-    const edx_sector* t = nbs[br];
-    off = std::max(off, lanczos_ws_layout(t ? t->vlen : 1, vtype, ngf, 0,
-                                          t ? hv_partial_blocks(t, vtype) : 1, false, nullptr,
-                                          nullptr));
-  }
-  gdev = reinterpret_cast<double*>(base + off);
+  // G and the staged coefficients sit after the layouts
+  const size_t off = both ? lsize[0] + lsize[1] : std::max(lsize[0], lsize[1]);
+  double* gdev = reinterpret_cast<double*>(base + off);
   double* cdev = gdev + 2 * kMaxLmats;
   std::vector<double> coeff(4 * (ngf + 1), 0.0);
   for (int br = 0; br < 2; ++br) {
