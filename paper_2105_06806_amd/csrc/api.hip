@@ -322,7 +322,8 @@ void edx_lanczos_default_opts(edx_lanczos_opts* o) {
 
 size_t edx_workspace_bytes(const edx_sector* s, int32_t what, int32_t vtype, int32_t n) {
   if (!s || !valid_vtype(vtype) || n < 1) return 0;
-  if (what == EDX_WS_LANCZOS) return lanczos_workspace_bytes(s, vtype, n, 0);
+  if (what == EDX_WS_LANCZOS)
+    return lanczos_workspace_bytes(s, vtype, n, 0) + lanczos_keep_bytes(s, vtype, n);
   if (what == EDX_WS_GREEN) return green_workspace_bytes(s, vtype, n, true);
   if (what == 2) return lanczos_workspace_bytes(s, vtype, n, 2);   // full re-orthogonalisation
   if (what == EDX_WS_CHI) return chi_workspace_bytes(s, vtype, n);

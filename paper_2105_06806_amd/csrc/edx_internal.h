@@ -251,6 +251,10 @@ edx_status k_axpy2(int vtype, void* w, const void* a, const double* pa,
                    const double* sa, const void* b, const double* pb,
                    const double* sb, int np, int64_t n, double* partial,
                    hipStream_t st);
+// psi = sum_{j < m} y[j] scale[j] u_j over m stored vectors (stride ld elements),
+// every addition rounded to the vector type as by m updates with psi
+edx_status k_psi_sum(int vtype, void* psi, const void* basis, int64_t ld, int m, const double* y,
+                     const double* scale, int64_t n, hipStream_t st);
 edx_status k_multi_dot(int vtype, const void* basis, int64_t ld, int m,
                        const void* w, int64_t n, double* partial,
                        hipStream_t st);
@@ -302,6 +306,8 @@ edx_status batch_autotune(const edx_sector* const* secs, int n, const edx_lanczo
 
 // ---- lanczos.hip
 size_t lanczos_workspace_bytes(const edx_sector* s, int vtype, int niter, int reorth);
+// what more than that keeps the run's vectors for psi0 where it pays (reorth 0, 1)
+size_t lanczos_keep_bytes(const edx_sector* s, int vtype, int niter);
 edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts* o, void* ws,
                                      size_t ws_bytes, double* e0, void* psi0,
                                      edx_lanczos_report* rep, hipStream_t st,

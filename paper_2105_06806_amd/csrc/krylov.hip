@@ -619,6 +619,37 @@ __global__ __launch_bounds__(kThreads) void k_multi_axpy_vec_kernel(T* __restric
   if (partial && threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
+// psi0 from kept vectors: one pass over them, V elements a lane (16-byte lanes, or
+// one element where psi is not on a 16-byte boundary)
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void k_psi_sum_kernel(T* __restrict__ psi,
+                                                             const T* __restrict__ basis,
+                                                             int64_t ld, int m,
+                                                             const double* __restrict__ y,
+                                                             const double* __restrict__ scale,
+                                                             int64_t n) {
+  typedef T VT __attribute__((ext_vector_type(V)));
+  const int64_t nv = n / V, step = (int64_t)gridDim.x * kThreads;
+  const int64_t id = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+  for (int64_t q = id; q < nv; q += step) {
+    VT p = VT(T(0));
+#pragma unroll 8
+    for (int j = 0; j < m; ++j) {
+      const VT x = *reinterpret_cast<const VT*>(basis + (int64_t)j * ld + q * V);
+      const double c = y[j] * scale[j];
+#pragma unroll
+      for (int e = 0; e < V; ++e) p[e] = (T)((double)p[e] + c * (double)x[e]);
+    }
+    *reinterpret_cast<VT*>(psi + q * V) = p;
+  }
+  for (int64_t i = nv * V + id; i < n; i += step) {
+    T p = T(0);
+    for (int j = 0; j < m; ++j)
+      p = (T)((double)p + y[j] * scale[j] * (double)basis[(int64_t)j * ld + i]);
+    psi[i] = p;
+  }
+}
+
 // In-place change of basis for a thick restart: basis_c <- sum_{j<m} C[j][c] basis_j
 // for c < l (C row-major, m x l, l <= kMaxKeep).  Each thread owns its
 // elements and reads all m of them before it writes, so the overwrite is safe.
@@ -859,6 +890,23 @@ edx_status k_axpy2(int vtype, void* w, const void* a, const double* pa, const do
     auto kern = vec ? k_axpy2_vec_kernel<float> : k_axpy2_kernel<float>;
     hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (float*)w, (const float*)a,
                        (const float*)b, c, n, partial);
+  }
+  EDX_HIP(hipGetLastError());
+  return EDX_OK;
+}
+
+edx_status k_psi_sum(int vtype, void* psi, const void* basis, int64_t ld, int m, const double* y,
+                     const double* scale, int64_t n, hipStream_t st) {
+  const bool vec = aligned16(psi, basis) && (ld * vbytes(vtype)) % 16 == 0;
+  const int g = multi_blocks(n);
+  if (vtype == EDX_F64) {
+    auto kern = vec ? k_psi_sum_kernel<double, 2> : k_psi_sum_kernel<double, 1>;
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (double*)psi, (const double*)basis, ld,
+                       m, y, scale, n);
+  } else {
+    auto kern = vec ? k_psi_sum_kernel<float, 4> : k_psi_sum_kernel<float, 1>;
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kThreads), 0, st, (float*)psi, (const float*)basis, ld, m,
+                       y, scale, n);
   }
   EDX_HIP(hipGetLastError());
   return EDX_OK;

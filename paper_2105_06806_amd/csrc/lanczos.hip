@@ -317,6 +317,8 @@ struct LanczosWs {
   double* beta2 = nullptr;
   double* scale2 = nullptr;
   double* gbuf = nullptr;    // Green: 2 * kMaxLmats
+  char* kept = nullptr;      // vectors u_0 .. u_keep of the run, kept for psi0
+  int keep = -1;             // (-1: none)
 };
 
 constexpr int kMaxLmats = 65536;
@@ -369,9 +371,13 @@ StepBufs bufs_for(const LanczosWs& L, int j, int reorth) {
     b.prev = j > 0 ? L.vec + (size_t)(j - 1) * L.vstride : nullptr;
     b.w = L.vec + (size_t)(j + 1) * L.vstride;
   } else {
-    b.cur = L.vec + (size_t)(j % 3) * L.vstride;
-    b.prev = j > 0 ? L.vec + (size_t)((j + 2) % 3) * L.vstride : nullptr;
-    b.w = L.vec + (size_t)((j + 1) % 3) * L.vstride;
+    // the first keep + 1 vectors have slots of their own, the others rotate
+    auto slot = [&](int i) {
+      return i <= L.keep ? L.kept + (size_t)i * L.vstride : L.vec + (size_t)(i % 3) * L.vstride;
+    };
+    b.cur = slot(j);
+    b.prev = j > 0 ? slot(j - 1) : nullptr;
+    b.w = slot(j + 1);
   }
   return b;
 }
@@ -668,6 +674,15 @@ edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, cons
 
 }  // namespace
 
+// Vectors kept for psi0 spare their steps of the replay (half-filled Ns=12 FP64:
+// 140 of about 390 steps of the whole call), for up to 1 GiB of workspace and
+// only where at least 64 fit; the smaller workspace works as well.
+size_t lanczos_keep_bytes(const edx_sector* s, int vtype, int niter) {
+  constexpr size_t kKeepBytes = size_t(1) << 30;
+  const size_t vs = align_up((size_t)s->vlen * vbytes(vtype));
+  return vs * 64 > kKeepBytes ? 0 : vs * std::min<size_t>(kKeepBytes / vs, (size_t)niter + 1);
+}
+
 size_t lanczos_workspace_bytes(const edx_sector* s, int vtype, int niter, int reorth) {
   return lanczos_ws_layout(s->vlen, vtype, niter, reorth, hv_partial_blocks(s, vtype),
                            s->ld != s->dup, nullptr, nullptr) + 256;
@@ -688,8 +703,17 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
     return EDX_E_NOMEM;
   }
   const int64_t n = s->vlen;
+  if (psi0 && reorth <= 1) {
+    // room beyond the recurrence's vectors keeps the run's first ones for psi0
+    const size_t room = (ws_bytes - need - (size_t)(base - (char*)ws)) / L.vstride;
+    if (room >= 2) {
+      L.kept = base + need;
+      L.keep = (int)std::min<size_t>(room - 1, niter);
+    }
+  }
+  void* const first = bufs_for(L, 0, reorth).cur;
   // start vector u_0 (random, or the caller's) and scale_0 = 1/|u_0|
-  EDX_TRY(k_start_vector(vtype, L.vec, s->dup, s->ld, s->ddw * s->dph, o->seed, L.partial, st,
+  EDX_TRY(k_start_vector(vtype, first, s->dup, s->ld, s->ddw * s->dph, o->seed, L.partial, st,
                          o->start));
   EDX_TRY(k_beta_finish(L.partial, elem_blocks(n), L.beta, L.scale, st));
   if (o->start) {
@@ -773,17 +797,30 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
       EDX_TRY(k_multi_axpy(vtype, acc, L.vec, (int64_t)(L.vstride / vbytes(vtype)), m, L.coef, n,
                            nullptr, st));
     } else {
-      // replay: identical start vector and recurrence, psi += y_j v_j
+      // psi0 = sum_j y_j v_j: the kept vectors are summed, the steps after them
+      // are replayed (identical recurrence); without kept vectors all are,
+      // from the same start vector.  Each addition rounds as in the replay's
+      // update, so the result does not depend on how many were kept.
       EDX_HIP(hipMemcpyAsync(L.y, y.data(), sizeof(double) * m, hipMemcpyHostToDevice, st));
-      EDX_HIP(hipMemsetAsync(acc, 0, (size_t)n * vbytes(vtype), st));
-      EDX_TRY(k_start_vector(vtype, L.vec, s->dup, s->ld, s->ddw * s->dph, o->seed, L.partial, st,
-                             o->start));
-      EDX_TRY(k_beta_finish(L.partial, elem_blocks(n), L.beta2, L.scale2, st));
-      EDX_HIP(hipMemsetAsync(L.beta2, 0, sizeof(double), st));
+      const int from = std::min(m, L.keep > 0 ? L.keep : 0);
+      double *al = L.alpha, *be = L.beta, *sc = L.scale;   // steps replay into their own scalars
+      if (from > 0) {
+        EDX_TRY(k_psi_sum(vtype, acc, L.kept, (int64_t)(L.vstride / vbytes(vtype)), from, L.y,
+                          L.scale, n, st));
+      } else {
+        al = L.alpha2;
+        be = L.beta2;
+        sc = L.scale2;
+        EDX_HIP(hipMemsetAsync(acc, 0, (size_t)n * vbytes(vtype), st));
+        EDX_TRY(k_start_vector(vtype, first, s->dup, s->ld, s->ddw * s->dph, o->seed, L.partial, st,
+                               o->start));
+        EDX_TRY(k_beta_finish(L.partial, elem_blocks(n), be, sc, st));
+        EDX_HIP(hipMemsetAsync(be, 0, sizeof(double), st));
+      }
       Pending pend;
-      for (int j = 0; j < m; ++j)
-        EDX_TRY(lanczos_step(s, vtype, L, j, reorth, L.alpha2, L.beta2, L.scale2, acc, L.y + j, st,
-                             j + 1 < m, &pend));
+      for (int j = from; j < m; ++j)
+        EDX_TRY(lanczos_step(s, vtype, L, j, reorth, al, be, sc, acc, L.y + j, st, j + 1 < m,
+                             &pend));
     }
     // normalise psi0
     EDX_TRY(k_norm2(vtype, acc, n, L.partial, st));
@@ -802,6 +839,7 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
     // E0 means a degenerate ground level; otherwise the run goes on until its
     // lowest Ritz value settles (that is E1).
     double E1d = NAN;
+    L.keep = -1;   // the check's vectors rotate
     EDX_TRY(check_degeneracy(s, o, L, rd, acc, E, tnorm, st, &E1d, &degenerate));
     E1 = E1d;
   }
