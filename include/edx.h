@@ -542,15 +542,18 @@ edx_status edx_espace_chi_pair(edx_espace* E, int32_t a, const edx_gf_opts* opts
  * Every job is an independent sector; the ground energy of each follows the
  * plain recurrence of edx_lanczos_ground_state (psi0 is not formed).  The
  * paper's counterpart is its parallelism over independent impurity problems
- * (Sec. 6 "Main", inequivalent sites).  Jobs with D >= wide_min_dim fill the
- * GPU by themselves: they run first, through the kernels and host stop rule
- * of edx_lanczos_ground_state (tol and rtol) -- jobs of one sector shape up to
+ * (Sec. 6 "Main", inequivalent sites).  Jobs with D >= wide_min_dim (by default
+ * every job) run first, through the kernels and host stop rule of
+ * edx_lanczos_ground_state (tol and rtol) -- jobs of one sector shape up to
  * tiles.multi_k at a time through the multi-set pass (one interleaved product
  * and recurrence per step for the group), the others one by one -- on three
- * streams.  The others
+ * streams, or up to eight for jobs of up to 128 MiB of vectors.  The others
  * share one cooperative launch: lanes of `lane_wgs` workgroups on one XCD
  * each pull jobs (largest first) from a device queue and evaluate the tol
- * stop rule on the device.  A job's status is EDX_OK, EDX_E_NOCONV (e0 is the
+ * stop rule on the device, every check_every steps.  With wide_min_dim = 0 the
+ * jobs below 2,000,000 states stop by the lanes' rule on either path, and a
+ * workspace that has no room for them off the lanes sends them there.  A job's
+ * status is EDX_OK, EDX_E_NOCONV (e0 is the
  * last estimate) or EDX_E_DEVICE (a lane barrier timed out). */
 typedef struct {
   double e0;
@@ -573,9 +576,9 @@ typedef struct {
                              single-set pass is faster per vector        */
   const int32_t* ccols;   /* [n] columns per column-pass item (1..4), or NULL (1) */
   const int32_t* rcols;   /* [n] columns per row-pass item, or NULL (32)   */
-  int64_t wide_min_dim;   /* jobs with D >= this run first, one at a time
-                             through the whole-GPU kernels; 0 = 2,000,000;
-                             < 0 = none (every job on a lane)              */
+  int64_t wide_min_dim;   /* jobs with D >= this run first, through the
+                             whole-GPU kernels; 0 = every job; < 0 = none
+                             (every job on a lane)                         */
 } edx_batch_tiles;
 
 /* Device workspace bytes for n jobs with lanes of lane_wgs workgroups and the
@@ -597,7 +600,7 @@ edx_status edx_batch_ground_state(const edx_sector* const* sectors, int32_t n,
 
 /* Project autotuner for the batched launch: per distinct (D_up, D_dw) it
  * times short runs of each (ccols, rcols) candidate on lanes, then each lane
- * size with each whole-GPU threshold (none, 0.25M, 1M, 2M, 4M, 8M); writes
+ * size with each whole-GPU threshold (none, 1, 0.25M, 1M, 2M, 4M, 8M); writes
  * ccols[n], rcols[n] (host), *lane_wgs and *wide_min_dim.  Candidates whose
  * workspace exceeds ws_bytes are skipped; ws must hold at least
  * edx_batch_workspace_bytes(..., 32, -1) bytes. */

@@ -1,10 +1,10 @@
 // Batched ground states of many sectors.
 //
-// Jobs whose dimension reaches a threshold (wide_min) fill the GPU by
-// themselves: they run first, one after another, through the whole-GPU
-// kernels of the plain path (lanczos.hip).  All other jobs share one
-// persistent launch: the grid is one workgroup per CU, launched cooperatively
-// so that every workgroup is resident.  Workgroups are grouped into lanes of L workgroups
+// Jobs whose dimension reaches a threshold (wide_min; by default every job) run
+// first, through the whole-GPU kernels of the plain path (lanczos.hip), several
+// at once on streams of their own.  All other jobs share one persistent launch:
+// the grid is one workgroup per CU, launched cooperatively so that every
+// workgroup is resident.  Workgroups are grouped into lanes of L workgroups
 // that sit on one XCD (workgroup b runs on XCD b % 8), so a lane shares one L2.
 // A lane pulls the next job from a device queue (jobs sorted by decreasing
 // dimension), runs the whole Lanczos recurrence of Sec. 6 "Diagonalization" for
@@ -28,6 +28,7 @@
 
 #include "common.h"
 #include "edx_internal.h"
+#include "side_stream.h"
 
 namespace edx {
 
@@ -63,10 +64,17 @@ constexpr int kWaves = kThreads / 64;
 constexpr long long kSpinLimit = 1ll << 26;
 constexpr int kColMaxB = 4;   // columns per column-pass item held in registers
 constexpr int kMaxBatchIter = 2048;   // niter bound of the batch call
-// Whole-GPU jobs run on this many streams at once (one host thread each), so
-// that one job's kernels fill the gaps while another's host checks its stop
-// rule.
+// Whole-GPU jobs run on several streams at once (one host thread each), so that
+// one job's kernels fill the gaps while another's host checks its stop rule.
+// Units of work (a job, or a group of the multi-set pass) with a workspace above
+// kSmallUnit have vectors beyond the caches and fill the chip: three streams
+// (27 jobs of Ns=14 FP32: 114 ms on 3, 120 on 6, 124 on 10).  The smaller ones
+// are bound by launches and the host's checks and have kSmallStreams more
+// (75 jobs of Ns=12 FP32: 36.8 ms on 3, 27.9 on 6, 26.7 on 10; Ns=8: 16.8,
+// 11.6, 10.5).
 constexpr int kWideStreams = 3;
+constexpr int kSmallStreams = 5;
+constexpr size_t kSmallUnit = size_t(128) << 20;
 constexpr int kMultiDefault = 8;        // bath sets per multi-set group (tiles.multi_k = 0)
 // Shapes the multi-set pass serves: up to 2^21 states, at most 4 FP64 sets.
 // Measured per vector against the single-set fused pass: half-filled Ns=12
@@ -426,20 +434,23 @@ size_t batch_lds_bytes(int vtype, int64_t max_cols_elems, int niter) {
 namespace {
 
 struct BatchLayout {
-  size_t o_jobs, o_out, o_ctl, o_parts, o_wide, o_vec, total;
-  size_t wide_bytes, vstride;
+  size_t o_jobs, o_out, o_ctl, o_parts, o_wide, o_small, o_vec, total;
+  size_t wide_bytes, small_bytes, vstride;
   int nlanes, lanes_per_xcd;
 };
 
-// wide_ws: plain Lanczos workspace of the largest job run through the
-// whole-GPU path (0 if none), one per stream; dmax_narrow: largest dimension
-// run in lanes
-BatchLayout batch_layout(int n, int vtype, int L, int ncu, size_t wide_ws, int64_t dmax_narrow) {
+// wide_ws: workspace of the largest unit run through the whole-GPU path (0 if
+// none), one for each of kWideStreams; small_ws: that of the largest unit up to
+// kSmallUnit, one for each of nsmall further streams; dmax_narrow: largest
+// dimension run in lanes
+BatchLayout batch_layout(int n, int vtype, int L, int ncu, size_t wide_ws, size_t small_ws,
+                         int nsmall, int64_t dmax_narrow) {
   BatchLayout B{};
   const size_t sz = vbytes(vtype);
   B.lanes_per_xcd = std::max(1, ncu / 8 / L);
   B.nlanes = 8 * B.lanes_per_xcd;
   B.wide_bytes = wide_ws;
+  B.small_bytes = small_ws;
   B.vstride = align_up((size_t)std::max<int64_t>(dmax_narrow, 1) * sz);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o2 = off; off += align_up(bytes); return o2; };
@@ -449,6 +460,7 @@ BatchLayout batch_layout(int n, int vtype, int L, int ncu, size_t wide_ws, int64
   B.o_ctl = take(sizeof(unsigned) * (1 + B.nlanes) + sizeof(int) * (1 + B.nlanes) + 64);
   B.o_parts = take(sizeof(double) * (2 * (size_t)L * B.nlanes));
   B.o_wide = take(align_up(wide_ws) * kWideStreams);
+  B.o_small = take(align_up(small_ws) * nsmall);
   B.o_vec = take(dmax_narrow > 0 ? B.vstride * 3 * B.nlanes : 0);
   B.total = off + 256;
   return B;
@@ -465,7 +477,16 @@ int device_cus() {
 
 }  // namespace
 
-int64_t batch_wide_default() { return 2000000; }
+// By default every job takes the whole-GPU path: it is ahead of the lanes at all
+// sizes (75 jobs FP32 of Ns=12: 28 vs 67 ms, Ns=10: 14.8 vs 29.5, Ns=8: 11.6 vs
+// 21.1, Ns=7: 9.7 vs 17.1; 600 jobs of Ns=8 and 9: 41 vs 189), as a lane's step
+// is four barriers of its 32 workgroups and a pass over the vectors for each.
+int64_t batch_wide_default() { return 1; }
+
+// Where the caller sets no threshold, a job below this size keeps the lanes' stop
+// rule (tol alone, looked at every check_every steps), so that its energy and
+// step count are those of the lanes; larger ones look at every step.
+constexpr int64_t kLaneRuleDim = 2000000;
 
 // Jobs of the whole-GPU path: D >= wide_min, and every sector with spin
 // exchange, pair hopping or phonons (the lanes implement the spin-separable
@@ -478,16 +499,39 @@ static bool is_wide(const edx_sector* s, int64_t wide_min) {
 // the multi-set pass (K the largest of 8, 4, 2 not above multi_k that the
 // shape supports and that the group fills; shapes up to kMultiMaxDim states),
 // the rest one by one; the order is by decreasing dimension.
-std::vector<std::vector<int>> wide_units(const edx_sector* const* secs, const std::vector<int>& wide,
-                                         int vtype, int multi_k) {
+struct WideUnits {
+  std::vector<std::vector<int>> units;   // the nbig above kSmallUnit first
+  int nbig = 0;
+  size_t bytes = 0, small_bytes = 0;     // largest workspace: of all, of the others
+
+  // streams beyond the main ones: one for each small unit that is left
+  int small_streams() const {
+    const int n = (int)units.size();
+    return std::max(0, std::min(kSmallStreams, n - std::max(nbig, kWideStreams)));
+  }
+};
+
+static size_t wide_unit_bytes(const edx_sector* const* secs, const std::vector<int>& u, int vtype,
+                              int niter) {
+  if (u.size() == 1) return lanczos_workspace_bytes(secs[u[0]], vtype, niter, 0);
+  return multi_workspace_bytes(secs[u[0]], (int)u.size(), vtype, niter);
+}
+
+static WideUnits wide_units(const edx_sector* const* secs, const std::vector<int>& wide, int vtype,
+                            int multi_k, int niter) {
   std::vector<std::vector<int>> units;
   std::vector<char> used(wide.size(), 0);
   for (size_t a = 0; a < wide.size(); ++a) {
     if (used[a]) continue;
     const edx_sector* s = secs[wide[a]];
-    std::vector<int> same;
-    for (size_t b = a; b < wide.size(); ++b)
-      if (!used[b] && multi_same_shape(s, secs[wide[b]])) same.push_back((int)b);
+    // itself, and what a multi-set pass could run with it: the pass serves
+    // electronic total-N sectors only, so each of a group is looked at
+    std::vector<int> same{(int)a};
+    if (multi_supported(s, 2, vtype))
+      for (size_t b = a + 1; b < wide.size(); ++b)
+        if (!used[b] && multi_same_shape(s, secs[wide[b]]) &&
+            multi_supported(secs[wide[b]], 2, vtype))
+          same.push_back((int)b);
     size_t pos = 0;
     for (int K : {8, 4, 2}) {
       if (K > multi_k || (vtype == EDX_F64 && K > kMultiMaxF64) || s->dim > kMultiMaxDim ||
@@ -512,13 +556,21 @@ std::vector<std::vector<int>> wide_units(const edx_sector* const* secs, const st
                                                    const std::vector<int>& y) {
     return secs[x[0]]->dim * (int64_t)x.size() > secs[y[0]]->dim * (int64_t)y.size();
   });
-  return units;
-}
-
-size_t wide_unit_bytes(const edx_sector* const* secs, const std::vector<int>& u, int vtype,
-                       int niter) {
-  if (u.size() == 1) return lanczos_workspace_bytes(secs[u[0]], vtype, niter, 0);
-  return multi_workspace_bytes(secs[u[0]], (int)u.size(), vtype, niter);
+  WideUnits W;
+  std::vector<std::vector<int>> small;
+  for (auto& u : units) {
+    const size_t b = wide_unit_bytes(secs, u, vtype, niter);
+    W.bytes = std::max(W.bytes, b);
+    if (b <= kSmallUnit) {
+      W.small_bytes = std::max(W.small_bytes, b);
+      small.push_back(std::move(u));
+    } else {
+      W.units.push_back(std::move(u));
+    }
+  }
+  W.nbig = (int)W.units.size();
+  for (auto& u : small) W.units.push_back(std::move(u));
+  return W;
 }
 
 edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opts* o,
@@ -533,31 +585,50 @@ edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opt
     set_error("batch: lane size must divide the CUs per XCD");
     return EDX_E_INVALID;
   }
+  const bool lane_rule = wide_min == 0;
   if (wide_min == 0) wide_min = batch_wide_default();
   // job order by decreasing D: the whole-GPU jobs (D >= wide_min) first, then
   // the lane jobs, which lanes take from the queue largest first
   std::vector<int> order(n);
-  for (int i = 0; i < n; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-    const bool wx = is_wide(secs[x], wide_min), wy = is_wide(secs[y], wide_min);
-    return wx != wy ? wx : secs[x]->dim > secs[y]->dim;
-  });
-  int nwide = 0;
-  size_t wide_ws = 0;
-  int64_t dmax_n = 0, colmax = 1;
-  std::vector<int> wide;
-  for (int k = 0; k < n; ++k) {
-    const edx_sector* s = secs[order[k]];
-    if (is_wide(s, wide_min)) {
-      ++nwide;
-      wide.push_back(order[k]);
-    } else {
-      dmax_n = std::max(dmax_n, s->dim);
+  int nwide = 0, nsmall = 0;
+  WideUnits W;
+  BatchLayout B{};
+  char* base = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(ws)));
+  auto plan = [&]() {
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+      const bool wx = is_wide(secs[x], wide_min), wy = is_wide(secs[y], wide_min);
+      return wx != wy ? wx : secs[x]->dim > secs[y]->dim;
+    });
+    int64_t dmax_n = 0;
+    std::vector<int> wide;
+    for (int k = 0; k < n; ++k) {
+      if (is_wide(secs[order[k]], wide_min))
+        wide.push_back(order[k]);
+      else
+        dmax_n = std::max(dmax_n, secs[order[k]]->dim);
     }
+    nwide = (int)wide.size();
+    W = wide_units(secs, wide, vtype, multi_k, o->niter);
+    // the further streams are as many as there are units for them and the
+    // workspace has room for
+    for (nsmall = W.small_streams(); nsmall >= 0; --nsmall) {
+      B = batch_layout(n - nwide, vtype, L, ncu, W.bytes, W.small_bytes, nsmall, dmax_n);
+      if (B.total <= ws_bytes) return true;
+    }
+    nsmall = 0;
+    return false;
+  };
+  bool room = plan();
+  if (!room && lane_rule) {
+    // a workspace that holds the lanes' vectors only
+    wide_min = kLaneRuleDim;
+    room = plan();
   }
-  const std::vector<std::vector<int>> units = wide_units(secs, wide, vtype, multi_k);
-  for (const auto& u : units) wide_ws = std::max(wide_ws, wide_unit_bytes(secs, u, vtype, o->niter));
+  const std::vector<std::vector<int>>& units = W.units;
   const int nl = n - nwide;
+  int64_t colmax = 1;
+  bool lanes = false;
   std::vector<BatchJob> jobs(nl);
   for (int k = 0; k < nl; ++k) {
     const edx_sector* s = secs[order[nwide + k]];
@@ -576,16 +647,19 @@ edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opt
     J.sdw = s->dw.wpad;
     J.ccols = std::min(kColMaxB, std::max(1, ccols ? ccols[order[nwide + k]] : 1));
     J.rcols = std::max(1, rcols ? rcols[order[nwide + k]] : 32);
-    colmax = std::max(colmax, (int64_t)J.ccols * s->dup);
   }
+  // columns that a lane could not hold are refused on either path
+  for (int i = 0; i < n; ++i)
+    if (!is_wide(secs[i], lane_rule ? kLaneRuleDim : wide_min)) {
+      colmax = std::max(colmax, std::min(kColMaxB, std::max(1, ccols ? ccols[i] : 1)) * secs[i]->dup);
+      lanes = true;
+    }
   const size_t lds = batch_lds_bytes(vtype, colmax, o->niter);
-  if (nl > 0 && lds > 160 * 1024) {
+  if (lanes && lds > 160 * 1024) {
     set_error("batch: columns per item do not fit in LDS");
     return EDX_E_UNSUPPORTED;
   }
-  const BatchLayout B = batch_layout(nl, vtype, L, ncu, wide_ws, dmax_n);
-  char* base = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(ws)));
-  if (B.total > ws_bytes) {
+  if (!room) {
     set_error("batch: workspace too small (need " + std::to_string(B.total) + " bytes)");
     return EDX_E_NOMEM;
   }
@@ -593,8 +667,8 @@ edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opt
   EDX_HIP(hipEventCreate(&e0));
   EDX_HIP(hipEventCreate(&e1));
   EDX_HIP(hipEventRecord(e0, st));
-  // whole-GPU jobs: the plain recurrence and stop rule, largest first, on
-  // kWideStreams streams (the caller's and ones created here)
+  // whole-GPU jobs: the plain recurrence and stop rule, on the caller's stream
+  // and on others that start after what is on it
   if (nwide > 0) {
     edx_lanczos_opts q = *o;
     q.reorth = 0;
@@ -602,61 +676,56 @@ edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opt
     // helper threads start on device 0: they are given the caller's device
     int dev = 0;
     EDX_HIP(hipGetDevice(&dev));
-    const int nst = std::min(kWideStreams, (int)units.size());
-    std::vector<hipStream_t> sts(nst, st);
-    std::vector<hipEvent_t> done(nst, nullptr);
-    edx_status fail = EDX_OK;
-    for (int t = 1; t < nst && fail == EDX_OK; ++t) {
-      if (hipStreamCreateWithFlags(&sts[t], hipStreamNonBlocking) != hipSuccess ||
-          hipEventCreateWithFlags(&done[t], hipEventDisableTiming) != hipSuccess ||
-          hipStreamWaitEvent(sts[t], e0, 0) != hipSuccess) {
-        set_error("batch: stream set-up failed");
-        fail = EDX_E_DEVICE;
-      }
-    }
-    std::atomic<int> next{0};
     const int nunits = (int)units.size();
+    const int nmain = std::min(kWideStreams, nunits);
+    const int nst = nmain + nsmall;
+    std::vector<SideStream> side(nst);
+    std::atomic<int> next_big{0}, next_small{W.nbig};
     std::vector<edx_status> tst(nst, EDX_OK);
     std::vector<std::string> terr(nst);
+    auto stop = [&](int t, edx_status st_, const std::string& msg) {
+      tst[t] = st_;
+      terr[t] = msg;
+      next_big.store(W.nbig);
+      next_small.store(nunits);
+    };
     auto worker = [&](int t) {
-      if (t > 0 && hipSetDevice(dev) != hipSuccess) {
-        tst[t] = EDX_E_DEVICE;
-        terr[t] = "batch: hipSetDevice failed in a helper thread";
-        next.store(nunits);
-        return;
-      }
-      char* wsp = base + B.o_wide + (size_t)t * align_up(B.wide_bytes);
+      if (t > 0 && hipSetDevice(dev) != hipSuccess)
+        return stop(t, EDX_E_DEVICE, "batch: hipSetDevice failed in a helper thread");
+      const hipStream_t ts = t > 0 ? side[t].stream() : st;
+      const bool main = t < nmain;
+      char* wsp = main ? base + B.o_wide + (size_t)t * align_up(B.wide_bytes)
+                       : base + B.o_small + (size_t)(t - nmain) * align_up(B.small_bytes);
+      const size_t wsb = main ? B.wide_bytes : B.small_bytes;
       for (;;) {
-        const int k = next.fetch_add(1);
+        // the main streams take the large units first, the others small ones only
+        int k = main ? next_big.fetch_add(1) : W.nbig;
+        if (k >= W.nbig) k = next_small.fetch_add(1);
         if (k >= nunits) break;
         const std::vector<int>& u = units[k];
+        const edx_sector* s = secs[u[0]];
+        // sectors that lanes cannot run were always checked at every step
+        const bool ends = lane_rule && !is_wide(s, kLaneRuleDim);
+        edx_lanczos_opts qj = q;
+        if (ends) qj.rtol = 0.0;
         if (u.size() > 1) {
           // one shape, several bath sets: the multi-set pass
           std::vector<const edx_sector*> g;
           for (int id : u) g.push_back(secs[id]);
           std::vector<edx_batch_result> rr(u.size());
-          const edx_status sg = multi_ground_states(g.data(), (int)u.size(), &q, wsp,
-                                                    B.wide_bytes, rr.data(), sts[t]);
-          if (sg != EDX_OK) {
-            tst[t] = sg;
-            terr[t] = std::string("batch: multi-set group: ") + edx_last_error();
-            next.store(nunits);
-            break;
-          }
+          const edx_status sg = multi_ground_states(g.data(), (int)u.size(), &qj, wsp, wsb,
+                                                    rr.data(), ts, ends);
+          if (sg != EDX_OK)
+            return stop(t, sg, std::string("batch: multi-set group: ") + edx_last_error());
           for (size_t b = 0; b < u.size(); ++b) res[u[b]] = rr[b];
           continue;
         }
-        const edx_sector* s = secs[u[0]];
         double e = 0.0;
         edx_lanczos_report rep{};
         const edx_status sj =
-            lanczos_ground_state_impl(s, &q, wsp, B.wide_bytes, &e, nullptr, &rep, sts[t], false);
-        if (sj != EDX_OK && sj != EDX_E_NOCONV && sj != EDX_E_DEGENERATE) {
-          tst[t] = sj;
-          terr[t] = std::string("batch: whole-GPU job: ") + edx_last_error();
-          next.store(nunits);
-          break;
-        }
+            lanczos_ground_state_impl(s, &qj, wsp, wsb, &e, nullptr, &rep, ts, false, ends);
+        if (sj != EDX_OK && sj != EDX_E_NOCONV && sj != EDX_E_DEGENERATE)
+          return stop(t, sj, std::string("batch: whole-GPU job: ") + edx_last_error());
         edx_batch_result& r = res[u[0]];
         r.e0 = e;
         r.beta_last = rep.beta_last;
@@ -665,34 +734,28 @@ edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opt
         r.breakdown = rep.breakdown;
       }
     };
-    if (fail == EDX_OK) {
+    {
+      // without a stream or thread to be had, a worker is left out
       std::vector<std::thread> th;
-      for (int t = 1; t < nst; ++t) th.emplace_back(worker, t);
+      for (int t = 1; t < nst; ++t) {
+        if (!side[t].fork(st)) continue;
+        try {
+          th.emplace_back(worker, t);
+        } catch (...) {
+          break;
+        }
+      }
       worker(0);
       for (auto& x : th) x.join();
     }
-    // the caller's stream continues after every helper stream's work
-    for (int t = 1; t < nst; ++t) {
-      if (done[t] && sts[t] != st) {
-        (void)hipEventRecord(done[t], sts[t]);
-        (void)hipStreamWaitEvent(st, done[t], 0);
-      }
-    }
-    for (int t = 1; t < nst; ++t) {
-      if (sts[t] != st) (void)hipStreamSynchronize(sts[t]);
-      if (done[t]) (void)hipEventDestroy(done[t]);
-      if (sts[t] != st) (void)hipStreamDestroy(sts[t]);
-    }
-    for (int t = 0; t < nst && fail == EDX_OK; ++t)
+    side.clear();   // waits for their work: the caller's stream continues after it
+    for (int t = 0; t < nst; ++t)
       if (tst[t] != EDX_OK) {
-        fail = tst[t];
         set_error(terr[t]);
+        (void)hipEventDestroy(e0);
+        (void)hipEventDestroy(e1);
+        return tst[t];
       }
-    if (fail != EDX_OK) {
-      (void)hipEventDestroy(e0);
-      (void)hipEventDestroy(e1);
-      return fail;
-    }
   }
   int herr = 0;
   std::vector<BatchOut> hout(nl);
@@ -812,8 +875,8 @@ edx_status batch_autotune(const edx_sector* const* secs, int n, const edx_lanczo
   double best = 1e300;
   int bl = 32;
   int64_t bw = batch_wide_default();
-  for (int64_t wm : {(int64_t)-1, (int64_t)250000, (int64_t)1000000, batch_wide_default(),
-                     (int64_t)4000000, (int64_t)8000000})
+  for (int64_t wm : {(int64_t)-1, batch_wide_default(), (int64_t)250000, (int64_t)1000000,
+                     (int64_t)2000000, (int64_t)4000000, (int64_t)8000000})
     for (int l : {8, 16, 32}) {
       if (batch_workspace_bytes(secs, n, o->vtype, l, wm) > ws_bytes) continue;
       double ms = 0;
@@ -832,7 +895,6 @@ edx_status batch_autotune(const edx_sector* const* secs, int n, const edx_lanczo
 size_t batch_workspace_bytes(const edx_sector* const* secs, int n, int vtype, int L,
                              int64_t wide_min) {
   if (wide_min == 0) wide_min = batch_wide_default();
-  size_t ww = 0;
   int64_t dn = 0;
   int nl = 0;
   std::vector<int> wide;
@@ -845,10 +907,12 @@ size_t batch_workspace_bytes(const edx_sector* const* secs, int n, int vtype, in
     }
   }
   // enough for every grouping up to the largest multi-set group
-  for (const auto& u : wide_units(secs, wide, vtype, 8))
-    ww = std::max(ww, wide_unit_bytes(secs, u, vtype, kMaxBatchIter));
-  for (int i : wide) ww = std::max(ww, lanczos_workspace_bytes(secs[i], vtype, kMaxBatchIter, 0));
-  return batch_layout(nl, vtype, L, device_cus(), ww, dn).total;
+  const WideUnits grp = wide_units(secs, wide, vtype, 8, kMaxBatchIter);
+  const WideUnits one = wide_units(secs, wide, vtype, 1, kMaxBatchIter);
+  return batch_layout(nl, vtype, L, device_cus(), std::max(grp.bytes, one.bytes),
+                      std::max(grp.small_bytes, one.small_bytes),
+                      std::max(grp.small_streams(), one.small_streams()), dn)
+      .total;
 }
 
 }  // namespace edx

@@ -26,6 +26,7 @@
 #include <utility>
 
 #include "edx_internal.h"
+#include "side_stream.h"
 
 namespace edx {
 
@@ -690,7 +691,8 @@ size_t lanczos_workspace_bytes(const edx_sector* s, int vtype, int niter, int re
 
 edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts* o, void* ws,
                                      size_t ws_bytes, double* e0, void* psi0,
-                                     edx_lanczos_report* rep, hipStream_t st, bool ahead) {
+                                     edx_lanczos_report* rep, hipStream_t st, bool ahead,
+                                     bool ends) {
   const int vtype = o->vtype;
   const int niter = o->niter;
   const int reorth = o->reorth;
@@ -747,7 +749,7 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
       // FP32 vectors cannot resolve energies or residuals below ~eps_32 |T|:
       // the thresholds are floored there (precision mode)
       const double floor32 = vtype == EDX_F32 ? 2.0 * 1.1920929e-7 * tnorm : 0.0;
-      bool ok = j > 0 &&
+      bool ok = j > 0 && (!ends || j + 1 == to) &&
                 std::fabs(E - Eold) <= std::max(o->tol * std::max(1.0, std::fabs(E)), floor32);
       if (ok && o->rtol > 0.0) {
         std::vector<double> yv(j + 1);
@@ -1358,65 +1360,6 @@ namespace {
 // this vector size; beyond it a step is bound by bandwidth and they take turns
 // in one workspace.
 constexpr size_t kOverlapBytes = size_t(32) << 20;
-
-// A second stream for a call, with an event to order it behind the caller's:
-// kept for the life of the process (at most kMax of them), held by one call at
-// a time; the destructor waits for what is still running on it.
-class SideStream {
- public:
-  SideStream() = default;
-  SideStream(const SideStream&) = delete;
-  SideStream& operator=(const SideStream&) = delete;
-  ~SideStream() {
-    if (!slot_) return;
-    (void)hipStreamSynchronize(slot_->st);
-    std::lock_guard<std::mutex> lk(mutex());
-    slot_->used = false;
-  }
-  // its work starts after what is on `st` now; false: no stream to be had
-  bool fork(hipStream_t st) {
-    slot_ = acquire();
-    return slot_ && hipEventRecord(slot_->ev, st) == hipSuccess &&
-           hipStreamWaitEvent(slot_->st, slot_->ev, 0) == hipSuccess;
-  }
-  hipStream_t stream() const { return slot_->st; }
-
- private:
-  struct Slot {
-    hipStream_t st = nullptr;
-    hipEvent_t ev = nullptr;
-    int device = 0;
-    bool used = false;
-  };
-  static constexpr int kMax = 16;
-  static std::mutex& mutex() {
-    static std::mutex* m = new std::mutex;   // never destroyed: calls may outlive statics
-    return *m;
-  }
-  static Slot* acquire() {
-    static std::vector<Slot*>* all = new std::vector<Slot*>;
-    int device = -1;
-    if (hipGetDevice(&device) != hipSuccess) return nullptr;
-    std::lock_guard<std::mutex> lk(mutex());
-    for (Slot* q : *all)
-      if (!q->used && q->device == device) {
-        q->used = true;
-        return q;
-      }
-    if ((int)all->size() >= kMax) return nullptr;
-    Slot q;
-    q.device = device;
-    q.used = true;
-    if (hipStreamCreateWithFlags(&q.st, hipStreamNonBlocking) != hipSuccess) return nullptr;
-    if (hipEventCreateWithFlags(&q.ev, hipEventDisableTiming) != hipSuccess) {
-      (void)hipStreamDestroy(q.st);
-      return nullptr;
-    }
-    all->push_back(new Slot(q));
-    return all->back();
-  }
-  Slot* slot_ = nullptr;
-};
 
 }  // namespace
 

@@ -759,7 +759,7 @@ def batch_workspace_bytes(sectors, vtype="f64", lane_wgs=8, wide_min_dim=None):
     h = _handles(sectors)
     if wide_min_dim is None:
         return max(int(lib.edx_batch_workspace_bytes(h, len(sectors), _vt(vtype), lane_wgs, w))
-                   for w in (-1, 250000, 1000000, 2000000, 4000000, 8000000))
+                   for w in (-1, 0, 250000, 1000000, 2000000, 4000000, 8000000))
     return int(lib.edx_batch_workspace_bytes(h, len(sectors), _vt(vtype), lane_wgs, int(wide_min_dim)))
 
 
