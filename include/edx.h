@@ -252,7 +252,9 @@ size_t edx_workspace_bytes(const edx_sector* s, int32_t what, int32_t vtype,
  * alpha_j = <v_j, H v_j>, w = H v_j - alpha_j v_j - beta_j v_{j-1},
  * beta_{j+1} = |w|, v_{j+1} = w / beta_{j+1}; scalars and dots in FP64.
  * psi0 (nullable, D elements of opts->vtype) receives the normalised ground
- * vector from a second replay of the same recurrence.  A run from one start
+ * vector: summed over the run's vectors that the workspace has room to keep
+ * (edx_workspace_bytes asks for up to 4 GiB of them; fewer or none will do),
+ * beyond them from a replay of the same recurrence.  A run from one start
  * vector sees one vector of a degenerate level; with psi0 requested and
  * opts->degen_check set, a further run deflated against psi0 tests the
  * ground level against the degeneracy threshold gs_threshold (Appendix A,

@@ -11,8 +11,9 @@
 //   or breakdown beta_{j+1} <= 1e-12 max_i(|alpha_i| + beta_i + beta_{i+1}),
 //   or j + 1 = niter.
 // E_j is the lowest eigenvalue of the tridiagonal T_j (Sturm bisection).  The
-// ground vector psi0 = sum_j y_j v_j is formed by replaying the identical
-// recurrence (deterministic kernels), so no basis is stored.
+// ground vector psi0 = sum_j y_j v_j is summed over the first vectors of the run,
+// as many as the workspace had room to keep, and formed beyond them by replaying
+// the identical recurrence (deterministic kernels): no full basis is needed.
 //
 // Precision mode (vtype = F32): vectors in FP32, all scalars, dot products
 // and the tridiagonal problem in FP64; reorth = 1 adds one Gram-Schmidt pass
@@ -675,13 +676,16 @@ edx_status check_degeneracy(const edx_sector* s, const edx_lanczos_opts* o, cons
 
 }  // namespace
 
-// Vectors kept for psi0 spare their steps of the replay (half-filled Ns=12 FP64:
-// 140 of about 390 steps of the whole call), for up to 1 GiB of workspace and
-// only where at least 64 fit; the smaller workspace works as well.
+// Vectors kept for psi0 spare their steps of the replay (half-filled, none / 32 /
+// 64 / 96 kept: Ns=12 FP64, 66 steps, 4.5 / 4.0 / 3.4 / 3.4 ms a call; Ns=14 FP32,
+// 77 steps, 24.5 / 21.8 / 18.8 / 17.6 ms; Ns=14 FP64, 92 steps, 49.9 / 44.8 /
+// 39.6 ms).  As many as a run takes as a rule, for up to 4 GiB of workspace, and
+// none where that is less than 16 of them; a smaller workspace works as well.
 size_t lanczos_keep_bytes(const edx_sector* s, int vtype, int niter) {
-  constexpr size_t kKeepBytes = size_t(1) << 30;
+  constexpr size_t kKeepBytes = size_t(4) << 30, kMin = 16, kMax = 160;
   const size_t vs = align_up((size_t)s->vlen * vbytes(vtype));
-  return vs * 64 > kKeepBytes ? 0 : vs * std::min<size_t>(kKeepBytes / vs, (size_t)niter + 1);
+  const size_t fit = std::min(kKeepBytes / vs, kMax);
+  return fit < kMin ? 0 : vs * std::min<size_t>(fit, (size_t)niter + 1);
 }
 
 size_t lanczos_workspace_bytes(const edx_sector* s, int vtype, int niter, int reorth) {
