@@ -631,7 +631,7 @@ def bench_batch(edx, torch):
     ok = sum(1 for r in res if r["status"] == 0)
     D = np.array([s.dim for s in secs], dtype=np.int64)
     wm = int(tiles["wide_min_dim"])
-    thr = 2_000_000 if wm == 0 else (None if wm < 0 else wm)
+    thr = 1 if wm == 0 else (None if wm < 0 else wm)
     in_launch = D < thr if thr else np.ones(len(D), bool)
     # the whole-GPU jobs one by one instead of in multi-set groups
     wso = edx.alloc_workspace(edx.batch_workspace_bytes(secs, "f32", tiles["lane_wgs"],
@@ -880,7 +880,9 @@ def main():
         msd, _ = time_hv(edx, torch, S, vd, wd, max(5, a.steps // 5), 2)
         single = plan["mode"] in (0, 2)
         tname = "double" if dt_name == "f64" else "float"
-        kernel = (f"k_hv_fused<{tname},{wpad},{wpad},{plan['col_cols']},false,false,true>"
+        vec = dt_name == "f64" and plan["col_cols"] <= 2   # two rows a lane (padded stride: even)
+        kernel = ((f"k_hv_vec<{tname},{wpad},{wpad},{plan['col_cols']},false,false,false>" if vec else
+                   f"k_hv_fused<{tname},{wpad},{wpad},{plan['col_cols']},false,false,true>")
                   if plan["mode"] == 2 else
                   ("k_hv_small" if plan["mode"] == 0 else f"k_hv_row + k_hv_col<{tname},{wpad}>"))
         traffic, tstate = traffic_from_profile(plan, dt_name) if single else (None, "two kernels")

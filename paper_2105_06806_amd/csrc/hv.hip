@@ -10,6 +10,8 @@
 //                 staged in LDS, so the spin-up gathers hit LDS; adds H_d and
 //                 gathers the spin-down neighbours of each element straight
 //                 from global memory (whole neighbour columns, coalesced).
+//                 The default plan of every sector.
+//  * k_hv_vec  -- the same pass with two FP64 rows a lane (16-byte accesses).
 //  * k_hv_col  -- the column pass of the two-pass plan: as k_hv_fused without
 //                 the spin-down gathers, accumulating into w.
 //  * k_hv_row  -- spin-down part over slabs of R consecutive rows.  A wave
@@ -18,7 +20,8 @@
 //                 (workgroups go round-robin over the 8 XCDs), so the slab
 //                 (R x D_dw elements) stays in that XCD's L2 while its ~8 reads
 //                 per element are served.
-//  * k_hv_small -- whole sector in LDS, one block (tiny sectors).
+//  * k_hv_small -- whole sector in LDS, one block (tiny sectors; a plan of the
+//                 autotuner's, not a default).
 //
 // Two-pass order: k_hv_row writes W = V H_dw^T, then k_hv_col adds
 // H_d o V + H_up V in place and (optionally) the per-block partial sums of
@@ -659,9 +662,9 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
   // ALL: the block owns NC columns (every block but possibly the last); then
   // nothing in the row body is conditional and the compiler keeps all
   // gathers of a row in flight together
-  // WK: spin-down slots gathered per row -- 8 when no column of the block has
-  // more real hops than that (the padding entries follow the real ones), else
-  // every slot of the padded row
+  // WK: spin-down slots gathered per row -- 8 (FP32: or 10 or 12) when no column
+  // of the block has more real hops than that (the padding entries follow the
+  // real ones), else every slot of the padded row
   auto rows = [&](auto all_tag, auto wk_tag) {
     constexpr bool ALL = decltype(all_tag)::value;
     constexpr int WK = decltype(wk_tag)::value;
@@ -791,23 +794,27 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
   // Norb=2 Ns=16 1169 -> 1038 us, Norb=3 Ns=15 235 -> 217 us; FP64 with 2
   // columns a block Norb=3 Ns=15 467 -> 412 us.  FP64 with one column a block
   // keeps the per-load skip alone (the 8-slot loop was 4 % slower there).
+  // FP32 blocks with more take 10 or 12 slots where that is enough (Norb=1 with 9
+  // or 10 electrons, or as few as leave 9 or 10 empty bath levels: 16 slots / 12 / 10:
+  // Ns=14 7/9 38.0 / 34.9 / 33.3 us, 9/9 24.8 / 22.1 / 20.8 us, Ns=13 6/9 9.3 /
+  // 8.2 / 7.7 us, Ns=15 8/9 154 / 142 / 137 us, Ns=16 8/6 555 / 549 / 496 us;
+  // Norb=2 Ns=14 61.1 / 59.5 / 58.5 us, Norb=3 Ns=15 192 / 188 / 187 us).
   constexpr bool kNarrow = WDW > 8 && (sizeof(T) == 4 || NC >= 2);
-  bool narrow = false;
+  constexpr bool kMid = kNarrow && sizeof(T) == 4 && !ND;
+  int mx = WDW;
   if constexpr (kNarrow) {
-    int mx = 0;
+    mx = 0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) mx = std::max(mx, nreal[c]);
-    narrow = mx <= 8;
   }
   auto go = [&](auto all_tag) {
-    if constexpr (kNarrow) {
-      if (narrow)
-        rows(all_tag, std::integral_constant<int, 8>{});
-      else
-        rows(all_tag, std::integral_constant<int, WDW>{});
-    } else {
-      rows(all_tag, std::integral_constant<int, WDW>{});
+    if constexpr (kNarrow)
+      if (mx <= 8) return rows(all_tag, std::integral_constant<int, 8>{});
+    if constexpr (kMid) {
+      if (mx <= 10) return rows(all_tag, std::integral_constant<int, 10>{});
+      if (mx <= 12) return rows(all_tag, std::integral_constant<int, 12>{});
     }
+    rows(all_tag, std::integral_constant<int, WDW>{});
   };
   if (nc == NC)
     go(std::true_type{});
@@ -825,9 +832,9 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
 
 // ---------------------------------------------------------------- fused pass, 16-byte lanes
 // The fused pass with VEC = 2 consecutive FP64 rows a lane: all vector and table
-// accesses are 16-byte loads.  The load path of a CU takes 8 clocks for a wave's 4-byte loads, 16 for
-// 8-byte and 17 for 16-byte ones (all from L1, measured), and the row-a-lane
-// pass spends 80 % of its cycles there (Ns=14 FP64, 2 columns: 392 clocks of 480
+// accesses are 16-byte loads.  The load path of a CU takes 8 clocks for a wave's
+// 4-byte loads, 16 for 8-byte and 17 for 16-byte ones (all from L1, measured), and
+// the row-a-lane pass spends 80 % of its cycles there (Ns=14 FP64, 2 columns: 392 clocks of 480
 // a row pass), so 16-byte lanes halve what bounds it.  Half-filled Ns=12 8.4 ->
 // 7.0 us, Ns=13 23.2 -> 20.3 us, Ns=14 Norb=2 84.9 -> 74.1 us, Ns=16 1639 -> 1480
 // us (best plan of either).  FP32 would need four rows a lane, and the four rows'
