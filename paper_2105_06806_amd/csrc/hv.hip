@@ -66,6 +66,7 @@ struct HvArgs {
   const T* __restrict__ amp;   // [256]
   const T* __restrict__ W;     // [64]
   const uint8_t* __restrict__ hrow;   // compact spin-up rows (fused pass) or nullptr
+  int norb;
 };
 
 #ifndef EDX_HV_PART
@@ -76,13 +77,13 @@ template <>
 HvArgs<double> make_args<double>(const edx_sector* s, int64_t ld) {
   return HvArgs<double>{s->dup, s->ddw, ld, s->up.hop, s->dw.hop, s->up.wpad, s->dw.wpad,
                         s->up.e64, s->dw.e64, s->up.pat, s->dw.pat, s->amp64, s->w64,
-                        s->hrow};
+                        s->hrow, s->model.norb};
 }
 template <>
 HvArgs<float> make_args<float>(const edx_sector* s, int64_t ld) {
   return HvArgs<float>{s->dup, s->ddw, ld, s->up.hop, s->dw.hop, s->up.wpad, s->dw.wpad,
                        s->up.e32, s->dw.e32, s->up.pat, s->dw.pat, s->amp32, s->w32,
-                       s->hrow};
+                       s->hrow, s->model.norb};
 }
 
 #endif
@@ -1200,11 +1201,18 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
   // columns, Norb=2 Ns=14 3003 rows 83.7 -> 79.1 us, Ns=15 359 -> 340 us); the
   // phonon neighbours are read by global loads past the slice and keep to
   // 16-byte boundaries.  With H_nd not where one column fills the LDS (its term
-  // loops then have 16 waves of half as many lanes: Ns=16 Norb=2 2021 -> 2153 us)
+  // loops then have 16 waves of half as many lanes: Ns=16 Norb=2 2021 -> 2153 us),
+  // nor there with wide rows of both spins for Norb=1, where half of the columns
+  // go past the eighth slot (Ns=16 9/9 1582 -> 1611 us; for Norb=2, a fifth of
+  // them, 1994 -> 1882 us), nor where two columns with wide spin-up rows alone
+  // leave room for one block more at most (Ns=15 9/8 256 -> 263 us; Ns=14 9/7
+  // 55.5 -> 49.8 us).
   if constexpr (NC <= 2 && sizeof(T) == 8) {
     const bool al16 = a.ld % 2 == 0 && (reinterpret_cast<uintptr_t>(v) & 15u) == 0;
     if (buf && (al16 || !fo.ph) && a.dup > 256 && lds + 16 * NC <= 160 * 1024 &&
-        !(fo.nd.nt > 0 && NC == 1 && lds > 80 * 1024)) {
+        !(NC == 1 && lds > 80 * 1024 &&
+          (fo.nd.nt > 0 || (a.norb == 1 && WUP > 8 && WDW > 8))) &&
+        !(NC == 2 && lds > 64 * 1024 && WUP > 8 && WDW <= 8)) {
       auto go = [&](auto nd_tag, auto ph_tag, auto odd_tag) {
         return launch_vec_n<T, WUP, WDW, NC, decltype(nd_tag)::value, decltype(ph_tag)::value,
                             decltype(odd_tag)::value>(a, nblk, nthr, lds, st, v, w, vscale,
@@ -1461,6 +1469,7 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   const size_t sz = vbytes(vtype);
   const size_t colb = (size_t)s->dup * sz;
   const bool wide = s->up.wpad > 8 || s->dw.wpad > 8;
+  const bool dwide = s->up.wpad <= 8 && s->dw.wpad > 8;
   const int ndt = nd_lds_terms(s);
   const size_t ndl = ndt > 0 ? 16 + nd_tab_lds(1 << s->model.norb, ndt, sz) : 0;
   // with phonons and no H_nd one launch covers all slices
@@ -1475,13 +1484,15 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   // waves fit), two where hop rows are wide or there is H_nd and the columns are
   // long (Norb=2 Ns=14 78.6 -> 74.1 us, with H_nd 108 -> 95 us), and from 2048
   // columns on, where it costs a product little (Ns=14 80 -> 83 us) and lets the
-  // Lanczos update fold the step's reductions.
+  // Lanczos update fold the step's reductions; but one where only the spin-down
+  // rows are wide (Ns=14 7/9 104 -> 46 us, Ns=15 8/9 475 -> 245 us: with two, each
+  // row reads both columns' further hops from the table).
   // Either: fewer where less than 1.5 blocks per CU are left (Ns=11, 462 columns:
   // 1 column 4.6 us, 2 columns 5.0 us).
   const bool ph = slices > 1;
   int c = 2;
   if (f64)
-    c = !ph && (((wide || s->nd) && s->dup > 1024) || s->ddw > 2048) ? 2 : 1;
+    c = !ph && !dwide && (((wide || s->nd) && s->dup > 1024) || s->ddw > 2048) ? 2 : 1;
   else if (!s->nd && (colb >= 40 * 1024 || (!wide && colb >= 24 * 1024)))
     c = 3;
   else if (s->nd && blocks(2) <= 512)
@@ -1494,9 +1505,11 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   // 2041 us; FP64 with 8-slot rows on 16-byte lanes is as fast with 8 waves: Ns=16
   // 1498 -> 1480 us, Ns=15 324 -> 321 us, dense 355 -> 340 us); 256 where columns are short -- FP32 grids of
   // 513-1024 blocks then run in one round (Ns=13 14.8 -> 14.4 us), FP64 up to 1024
-  // rows (Ns=12 7.4 -> 7.0 us) -- and for FP32 with H_nd, whose term loops diverge.
+  // rows (Ns=12 7.4 -> 7.0 us; 2048 where only the spin-down rows are wide: Ns=13
+  // 6/9 12.6 -> 10.9 us), unless the grid is less than one block per CU (Ns=12
+  // 6/9 4.5 -> 5.2 us) -- and for FP32 with H_nd, whose term loops diverge.
   const size_t lds = c * colb + ndl;
-  const bool shortc = f64 ? s->dup <= 1024
+  const bool shortc = f64 ? s->dup <= (dwide ? 2048 : 1024) && (s->dup <= 512 || blocks(c) >= 256)
                           : s->dup <= 256 || (s->dup <= 2048 && blocks(c) > 512) ||
                                 (s->nd && s->dup <= 4096);
   p.col_threads = 512;
