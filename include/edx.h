@@ -297,9 +297,9 @@ edx_status edx_lanczos_ground_state_static(const edx_sector* s,
  * column per workgroup; one spin-down gather serves all k sets.  ws: device
  * workspace of edx_hv_multi_workspace_bytes (the per-set tables and partial
  * sums; each call copies the k sets' tables into it on the stream first).
- * Faster per vector than k separate edx_hv calls only on small sectors
- * (measured: half-filled Ns=12, 1.9x in FP32); from Ns=14 on the single-set
- * pass is faster, because interleaving does not reduce the bytes that cross
+ * Faster than k separate edx_hv calls only on small sectors, where it saves
+ * launches (a product of half-filled Ns=12, FP32: 5.3 us per vector against
+ * 5.6); from Ns=14 on the single-set pass is faster, because interleaving does not reduce the bytes that cross
  * L2 per vector.  Total-N sectors without spin exchange, pair hopping or phonons,
  * hop rows of 8 or 16 entries, D_up < 2^16, a column of the k sets within LDS
  * and 32-bit byte offsets; otherwise EDX_E_UNSUPPORTED.  Sectors of different
@@ -570,8 +570,9 @@ typedef struct {
   int32_t lane_wgs;       /* workgroups per lane: 8, 16 or 32             */
   int32_t multi_k;        /* whole-GPU jobs of one sector shape (the same
                              Ns, Norb, N_up, N_dw; each its own bath) and
-                             at most 2^21 states run up to multi_k at a
-                             time (8, 4 or 2; FP64 vectors at most 4)
+                             at most 2^19 states (FP32: 2^21, 4 at a time
+                             above 2^19) run up to multi_k at a time
+                             (8, 4 or 2; FP64 vectors at most 4)
                              through the multi-set pass of edx_hv_multi,
                              the rest one by one; 0 = 8, 1 = off.  Larger
                              shapes always run one by one: there the

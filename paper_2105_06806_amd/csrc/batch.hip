@@ -76,14 +76,18 @@ constexpr int kWideStreams = 3;
 constexpr int kSmallStreams = 5;
 constexpr size_t kSmallUnit = size_t(128) << 20;
 constexpr int kMultiDefault = 8;        // bath sets per multi-set group (tiles.multi_k = 0)
-// Shapes the multi-set pass serves: up to 2^21 states, at most 4 FP64 sets.
-// Measured per vector against the single-set fused pass: half-filled Ns=12
-// (D = 853,776) 5.3 vs 10.1 us (FP32, 4 or 8 sets), 9.2-9.8 vs 11.3 us (FP64,
-// 2 or 4 sets; 8 sets 12.3 us); Ns=14 (D = 11.8M) 58-68 vs 48 us (FP32) --
-// there one column of k sets is k times the footprint in L2, so the misses
-// per vector do not fall while the grid is already full.
-constexpr int64_t kMultiMaxDim = int64_t(1) << 21;
-constexpr int kMultiMaxF64 = 4;
+// Largest group of sets of one shape that the multi-set pass serves; 1: none.
+// A group shares a step's launches, which is what bounds small sectors; its
+// product is no faster per vector than the single-set pass by now (half-filled
+// Ns=12: FP32 5.3 vs 5.6 us, FP64 9.2-9.8 vs 6.6 us).  72 sectors of 8 sets, off /
+// 2 / 4 / 8 at a time: Ns=10 FP32 15.7 / 10.9 / 7.4 / 6.3 ms, FP64 17.8 / 14.0 / 9.5
+// ms (8 do not pay), Ns=11 (36 of 4 sets) FP64 11.5 / 10.5 / 9.4 ms; Ns=12 FP32 27.2 /
+// 23.9 / 21.5 / 25.5 ms, FP64 38.6 / 46.0 / 51.5 ms; Ns=14 FP32 58-68 us a product
+// against 50.
+int multi_max(int64_t dim, int vtype) {
+  if (dim <= int64_t(1) << 19) return vtype == EDX_F64 ? 4 : 8;
+  return vtype == EDX_F32 && dim <= int64_t(1) << 21 ? 4 : 1;
+}
 
 __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t k) {
   uint64_t z = seed + (k + 1) * 0x9E3779B97F4A7C15ull;
@@ -497,7 +501,7 @@ static bool is_wide(const edx_sector* s, int64_t wide_min) {
 
 // Work units of the whole-GPU path: jobs of one shape grouped K at a time for
 // the multi-set pass (K the largest of 8, 4, 2 not above multi_k that the
-// shape supports and that the group fills; shapes up to kMultiMaxDim states),
+// shape supports, that pays there and that the group fills),
 // the rest one by one; the order is by decreasing dimension.
 struct WideUnits {
   std::vector<std::vector<int>> units;   // the nbig above kSmallUnit first
@@ -534,9 +538,7 @@ static WideUnits wide_units(const edx_sector* const* secs, const std::vector<int
           same.push_back((int)b);
     size_t pos = 0;
     for (int K : {8, 4, 2}) {
-      if (K > multi_k || (vtype == EDX_F64 && K > kMultiMaxF64) || s->dim > kMultiMaxDim ||
-          !multi_supported(s, K, vtype))
-        continue;
+      if (K > multi_k || K > multi_max(s->dim, vtype) || !multi_supported(s, K, vtype)) continue;
       while (same.size() - pos >= (size_t)K) {
         std::vector<int> u;
         for (int q = 0; q < K; ++q) {
