@@ -67,6 +67,16 @@ __device__ __forceinline__ void fold_sum2(const double (&x)[U], const double (&y
   sy = ((red[4] + red[5]) + red[6]) + red[7];
 }
 
+// Streaming (non-temporal) 16-byte buffer store at byte offset `off`.  The whole
+// offset goes into the lane offset and the scalar offset stays 0: with a
+// register there the compiler takes the data registers as free at once (no wait
+// state between the store and the next instruction), and on this chip the
+// store's third dword then came out as that instruction's result now and then.
+__device__ __forceinline__ void buf_store16_nt(__amdgpu_buffer_rsrc_t r, uint32_t off,
+                                               unsigned int __attribute__((ext_vector_type(4))) x) {
+  __builtin_amdgcn_raw_buffer_store_b128(x, r, (int)off, 0, 2);
+}
+
 // Counter-based SplitMix64 (Steele, Lea and Flood's finaliser): draw k of
 // stream `seed` (the start vectors' element k takes draw k).
 __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t k) {

@@ -87,10 +87,10 @@ __device__ __forceinline__ void load_k(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
   }
 }
 
-// streaming store of K values
+// streaming store of K values at byte offset `off` (see buf_store16_nt for why
+// there is no scalar offset)
 template <typename T, int K>
-__device__ __forceinline__ void store_k(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
-                                        const T (&x)[K]) {
+__device__ __forceinline__ void store_k(__amdgpu_buffer_rsrc_t r, uint32_t off, const T (&x)[K]) {
   constexpr int B = K * (int)sizeof(T);
   typedef unsigned int u2 __attribute__((ext_vector_type(2)));
   typedef unsigned int u4 __attribute__((ext_vector_type(4)));
@@ -110,17 +110,17 @@ __device__ __forceinline__ void store_k(__amdgpu_buffer_rsrc_t r, uint32_t voff,
   for (; o + 16 <= B; o += 16) {
     u4 y;
     y.x = words[o / 4]; y.y = words[o / 4 + 1]; y.z = words[o / 4 + 2]; y.w = words[o / 4 + 3];
-    __builtin_amdgcn_raw_buffer_store_b128(y, r, (int)(voff + o), (int)soff, 2);
+    buf_store16_nt(r, off + o, y);
   }
 #pragma unroll
   for (; o + 8 <= B; o += 8) {
     u2 y;
     y.x = words[o / 4]; y.y = words[o / 4 + 1];
-    __builtin_amdgcn_raw_buffer_store_b64(y, r, (int)(voff + o), (int)soff, 2);
+    __builtin_amdgcn_raw_buffer_store_b64(y, r, (int)(off + o), 0, 2);
   }
 #pragma unroll
   for (; o + 4 <= B; o += 4)
-    __builtin_amdgcn_raw_buffer_store_b32(words[o / 4], r, (int)(voff + o), (int)soff, 2);
+    __builtin_amdgcn_raw_buffer_store_b32(words[o / 4], r, (int)(off + o), 0, 2);
 }
 
 __device__ __forceinline__ float m_uniform(float x) {
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(1024) void k_hv_multi(MultiArgs<T> a, const T* __re
       res[b] = acc[b] + (eu[b] + ed[b] + Wt[b * 64 + pu + pd]) * x + s2;
       dot[b] += (double)x * (double)res[b];
     }
-    store_k<T, K>(wres, voff, coff, res);
+    store_k<T, K>(wres, voff + coff, res);
   }
   // padding rows of the output column are zero
   for (int64_t i = dup * K + threadIdx.x; i < ld * K; i += blockDim.x) w[j * ld * K + i] = T(0);

@@ -197,3 +197,30 @@ def test_batch_groups_edge_shapes(edx):
     for S, r, E0 in zip(jobs, res, refs):
         assert r["status"] == 0, (S.dim, r)
         assert abs(r["e0"] - E0) <= 1e-10 * max(1.0, abs(E0)), (S.dim, r["e0"], E0)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("k", [2, 4, 8])
+@pytest.mark.parametrize("norb,nbath,sec", [(1, 10, (5, 6)), (3, 3, (5, 7))])   # hop rows of 8 and 16
+def test_hv_multi_repeats_bit_for_bit(edx, norb, nbath, sec, k, dtype):
+    """The 16-byte stores: a product repeated on fresh outputs is the same to
+    the last bit, every set of it that of the one-column fused pass, and
+    nothing past its end is written (a lost dword would come and go)."""
+    import torch
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    ms = _models(norb, nbath, k, seed0=1600 + k)
+    Ss = [edx.build_sector(m, *sec) for m in ms]
+    xs = [torch.as_tensor(inputs.random_vector(Ss[0].dim, seed=30 + b), dtype=tdt, device="cuda")
+          for b in range(k)]
+    ref = []
+    for S, x in zip(Ss, xs):
+        edx.set_plan(S, dtype, mode=2, col_cols=1, col_threads=256, row_rows=64, row_cols=16, col_order=0)
+        ref.append(edx.hv(S, x, torch.empty_like(x)).clone())
+    v = edx.interleave(Ss[0], xs)
+    buf = torch.empty(v.numel() + 64, dtype=tdt, device="cuda")
+    for _ in range(10):
+        buf.fill_(5.0)
+        edx.hv_multi(Ss, v, buf[: v.numel()])
+        for y, r in zip(edx.deinterleave(Ss[0], buf[: v.numel()], k), ref):
+            assert torch.equal(y, r)
+        assert bool((buf[v.numel():] == 5.0).all())
