@@ -76,8 +76,12 @@ struct SpinTables {
   uint32_t* hop = nullptr;    // [D * wpad] packed, row-major: hop[i*wpad + k]
   double* e64 = nullptr;      // [D] diagonal energy
   float* e32 = nullptr;       // [D] same, rounded
-  uint8_t* pat = nullptr;     // [D] impurity pattern
+  uint8_t* pat = nullptr;     // [pat_bytes(D)] impurity pattern
 };
+
+// Bytes of a table of D impurity patterns: the product on 16-byte lanes reads
+// two rows' patterns as one 16-bit word, so an odd table ends in a zero byte.
+constexpr int64_t pat_bytes(int64_t D) { return (D + 1) / 2 * 2; }
 
 // Launch plan of edx_hv (see edx_hv_plan).
 struct HvPlan {

@@ -992,7 +992,7 @@ __global__ __launch_bounds__(1024) void k_hv_vec(HvArgs<T> a, const T* __restric
   const __amdgpu_buffer_rsrc_t eres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<T*>(a.eup), 0, (int)(dup * sizeof(T)), 0x00020000);
   const __amdgpu_buffer_rsrc_t pres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(a.pup), 0, (int)((dup + VEC - 1) / VEC * VEC), 0x00020000);
+      const_cast<uint8_t*>(a.pup), 0, (int)pat_bytes(dup), 0x00020000);
   __syncthreads();
   double dot = 0.0;
   for (uint32_t iu = threadIdx.x * VEC; iu < dup; iu += pass) {

@@ -146,6 +146,7 @@ __global__ void k_diag(const uint32_t* __restrict__ map, int64_t D, int norb,
                        int ns, const double* __restrict__ elev, double upj,
                        double* __restrict__ e64, float* __restrict__ e32,
                        uint8_t* __restrict__ pat) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && pat_bytes(D) > D) pat[D] = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < D;
        i += (int64_t)gridDim.x * blockDim.x) {
     const uint32_t s = map[i];
@@ -260,7 +261,7 @@ edx_status build_spin(edx_sector* S, SpinTables& T, int n, const int* counts,
   EDX_HIP(hipGetLastError());
   EDX_TRY(dalloc(S, &T.e64, D * sizeof(double)));
   EDX_TRY(dalloc(S, &T.e32, D * sizeof(float)));
-  EDX_TRY(dalloc(S, &T.pat, D));
+  EDX_TRY(dalloc(S, &T.pat, pat_bytes(D)));
   k_diag<<<grid_for(D, 256), 256, 0, st>>>(T.map, D, m.norb, m.ns, d_elev,
                                            m.Ust - m.Jh, T.e64, T.e32, T.pat);
   EDX_HIP(hipGetLastError());
@@ -488,7 +489,7 @@ size_t sector_table_bytes(int ns, int nup, int ndw) {
   size_t b = 0;
   for (int n : {nup, ndw}) {
     const size_t D = (size_t)comb(ns, n);
-    b += ((size_t)4 << ns) + D * (4 + 24 * 4 + 8 + 4 + 1) + 6 * a;
+    b += ((size_t)4 << ns) + D * (4 + 24 * 4 + 8 + 4) + (size_t)pat_bytes(D) + 6 * a;
   }
   b += (kMaxNs + 1) * (kMaxNs + 1) * 4 + 256 * 12 + 64 * 12 + 16 + 8 * kMaxNs + 8 * a;
   b += (size_t)comb(ns, ndw) * 4 + a;   // column order
