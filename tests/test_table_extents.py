@@ -21,7 +21,8 @@ def _src(name):
 
 def test_pattern_table_is_allocated_as_it_is_read():
     hv, tables = _src("hv.hip"), _src("tables.hip")
-    lanes = hv[hv.index("void k_hv_vec("):]        # k_hv_fused, before it, reads single bytes
+    # (the row-a-lane passes before and after it read single bytes)
+    lanes = hv[hv.index("void k_hv_vec("):hv.index("// ---------------------------------------------------------------- fused launches")]
     reads = re.findall(r"make_buffer_rsrc\(\s*const_cast<uint8_t\*>\(a\.pup\), 0, \(int\)([^,]+), ", lanes)
     assert reads == ["pat_bytes(dup)"]
     assert re.findall(r"dalloc\(S, &T\.pat, (.+)\)\);", tables) == ["pat_bytes(D)"]
