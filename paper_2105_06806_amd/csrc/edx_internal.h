@@ -106,6 +106,9 @@ struct edx_sector {
   int64_t vlen = 0;          // ld * ddw * dph elements per Krylov vector
   int dph = 1;               // phonon states N_ph + 1 (1: no phonons); slowest index
   int device = 0;
+  // <u, H u> of a vector u = beta v stays within FP64: it grows as the cube of
+  // the parameters, which lie between 1e-90 and 1e90 (0 among them is no matter)
+  bool cubes_fit = true;
   edx::SpinTables up, dw;
   // Signed amplitudes indexed by (hop entry >> 24); identical for both spins.
   double* amp64 = nullptr;   // [256] device

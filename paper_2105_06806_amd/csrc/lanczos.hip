@@ -394,7 +394,8 @@ StepBufs bufs_for(const LanczosWs& L, int j, int reorth) {
 // leaves few partials, the step's reductions are folded into the update (see
 // k_update): alpha_j, and with FP64 vectors also beta_j and scale_j, whose
 // partials the step before left in `pend` (n = 0: they are written); the
-// product then takes the unscaled u_j.  The update also forms the dot products
+// product then takes the unscaled u_j, except of the start vector, whose norm is
+// the caller's, and of parameters whose cubes FP64 does not hold.  The update also forms the dot products
 // of a projection that follows (local re-orthogonalisation, defl), which so
 // costs one launch and one more pass over w (Ns=13 FP32 with reorth = 1: three
 // reads of vectors and two launches a step less).
@@ -418,7 +419,7 @@ edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int 
   // lower half there.
   const bool local = reorth == 1;
   const bool fold = hb <= (local ? kMaxElemBlocks : kMaxPartials);
-  const bool unscaled = fold && vtype == EDX_F64;
+  const bool unscaled = fold && vtype == EDX_F64 && j > 0 && s->cubes_fit;
   double* X = L.partial + kMaxPartials;
   double* Y = X + kMaxElemBlocks;
   if (pend->n > 0 && pend->part == Y) std::swap(X, Y);
@@ -462,7 +463,8 @@ edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int 
     }
   }
   *pend = Pending{};
-  if (unscaled && more)
+  // the next step's product takes its vector unscaled
+  if (fold && vtype == EDX_F64 && s->cubes_fit && more)
     *pend = Pending{out, eb};
   else
     EDX_TRY(k_beta_finish(out, eb, beta + j + 1, scale + j + 1, st));

@@ -499,6 +499,20 @@ size_t sector_table_bytes(int ns, int nup, int ndw) {
   return b;
 }
 
+static double largest_parameter(const Model& m) {
+  double h = 0.0;
+  auto see = [&](double x) { h = std::max(h, std::fabs(x)); };
+  for (double x : m.eps_imp) see(x);
+  for (double x : m.eps_bath) see(x);
+  for (double x : m.vhyb) see(x);
+  for (double x : {m.U, m.Ust, m.Jh, m.xmu, m.Jx, m.Jp}) see(x);
+  if (m.nph > 0) {
+    see(m.w0);
+    for (double x : m.g) see(x);
+  }
+  return h;
+}
+
 edx_status build_sector_impl(const Model& m, int nup, int ndw, hipStream_t st,
                              edx_sector** out, const Allocator* alloc, const int* cup,
                              const int* cdw) {
@@ -507,6 +521,8 @@ edx_status build_sector_impl(const Model& m, int nup, int ndw, hipStream_t st,
   S->model = m;
   S->nup = nup;
   S->ndw = ndw;
+  const double h = largest_parameter(m);
+  S->cubes_fit = h == 0.0 || (h > 1e-90 && h < 1e90);
   EDX_HIP(hipGetDevice(&S->device));
 
   // binomial table C(c, k), c, k <= 24
