@@ -123,14 +123,14 @@ __device__ bool lane_barrier(unsigned* ctr, unsigned& gen, int L, int* err) {
   return fail == 0;
 }
 
-// number of eigenvalues of T_m below x (Sturm sequence)
+// number of eigenvalues of T_m below x (Sturm sequence); a pivot of zero counts
+// as negative, as which the next one takes it
 __device__ int sturm(const double* a, const double* b, int m, double x) {
   int cnt = 0;
-  double q = a[0] - x;
-  cnt += q < 0.0;
-  for (int i = 1; i < m; ++i) {
+  double q = 0.0;
+  for (int i = 0; i < m; ++i) {
+    q = a[i] - x - (i > 0 ? b[i] * b[i] / q : 0.0);   // b[i] couples i-1 and i
     if (fabs(q) < 1e-300) q = -1e-300;
-    q = a[i] - x - b[i] * b[i] / q;   // b[i] couples i-1 and i
     cnt += q < 0.0;
   }
   return cnt;

@@ -38,14 +38,14 @@ edx_status k_coef_scale2(double* coef, const double* scale, int m, hipStream_t s
 // ---------------------------------------------------------------- tridiagonal
 namespace {
 
-// number of eigenvalues of T (diag a[0..m), off b[0..m-1)) smaller than x
+// number of eigenvalues of T (diag a[0..m), off b[0..m-1)) smaller than x; a
+// pivot of zero counts as negative, as which the next one takes it
 int sturm_count(const double* a, const double* b, int m, double x, double tiny) {
   int cnt = 0;
-  double q = a[0] - x;
-  if (q < 0) ++cnt;
-  for (int i = 1; i < m; ++i) {
+  double q = 0.0;
+  for (int i = 0; i < m; ++i) {
+    q = a[i] - x - (i > 0 ? b[i - 1] * b[i - 1] / q : 0.0);
     if (std::fabs(q) < tiny) q = -tiny;
-    q = a[i] - x - b[i - 1] * b[i - 1] / q;
     if (q < 0) ++cnt;
   }
   return cnt;
