@@ -603,10 +603,10 @@ edx_status edx_batch_ground_state(const edx_sector* const* sectors, int32_t n,
 
 /* Project autotuner for the batched launch: per distinct (D_up, D_dw) it
  * times short runs of each (ccols, rcols) candidate on lanes, then each lane
- * size with each whole-GPU threshold (none, 1, 0.25M, 1M, 2M, 4M, 8M); writes
- * ccols[n], rcols[n] (host), *lane_wgs and *wide_min_dim.  Candidates whose
- * workspace exceeds ws_bytes are skipped; ws must hold at least
- * edx_batch_workspace_bytes(..., 32, -1) bytes. */
+ * size with each whole-GPU threshold (-1: every job on a lane, 0: every job off
+ * them, 0.25M, 1M, 2M, 4M, 8M); writes ccols[n], rcols[n] (host), *lane_wgs and
+ * *wide_min_dim.  Candidates whose workspace exceeds ws_bytes are skipped; ws
+ * must hold at least edx_batch_workspace_bytes(..., 32, -1) bytes. */
 edx_status edx_batch_autotune(const edx_sector* const* sectors, int32_t n,
                               const edx_lanczos_opts* opts, void* ws,
                               size_t ws_bytes, int32_t* ccols, int32_t* rcols,

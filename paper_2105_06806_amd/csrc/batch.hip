@@ -876,8 +876,10 @@ edx_status batch_autotune(const edx_sector* const* secs, int n, const edx_lanczo
   }
   double best = 1e300;
   int bl = 32;
-  int64_t bw = batch_wide_default();
-  for (int64_t wm : {(int64_t)-1, batch_wide_default(), (int64_t)250000, (int64_t)1000000,
+  // 0: every job off the lanes, by the rule of a call without a threshold (an
+  // explicit threshold has the jobs above it checked at every step)
+  int64_t bw = 0;
+  for (int64_t wm : {(int64_t)-1, (int64_t)0, (int64_t)250000, (int64_t)1000000,
                      (int64_t)2000000, (int64_t)4000000, (int64_t)8000000})
     for (int l : {8, 16, 32}) {
       if (batch_workspace_bytes(secs, n, o->vtype, l, wm) > ws_bytes) continue;
