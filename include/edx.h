@@ -240,11 +240,19 @@ void edx_lanczos_default_opts(edx_lanczos_opts* o);
 #define EDX_WS_LANCZOS 0
 #define EDX_WS_GREEN 1
 #define EDX_WS_LANCZOS_BASIS 2
+#define EDX_WS_LANCZOS_MIN 5
+#define EDX_WS_GREEN_MIN 6
 
 /* Device workspace bytes for edx_lanczos_ground_state (what = EDX_WS_LANCZOS,
- * n = niter; what = EDX_WS_LANCZOS_BASIS = 2 for reorth 2 or 3), edx_green_cf (what = EDX_WS_GREEN, n = ngf), edx_chi and
- * edx_chi_exciton (what = EDX_WS_CHI = 3, n = ngf) or edx_chi_pair
- * (what = EDX_WS_PAIR = 4, n = ngf). */
+ * n = niter; what = EDX_WS_LANCZOS_BASIS = 2 for reorth 2 or 3), edx_green_cf
+ * (what = EDX_WS_GREEN, n = ngf), edx_chi and edx_chi_exciton (what =
+ * EDX_WS_CHI = 3, n = ngf) or edx_chi_pair (what = EDX_WS_PAIR = 4, n = ngf).
+ * EDX_WS_LANCZOS is the size that is fastest with psi0: it holds up to 4 GiB of
+ * Krylov vectors beyond what the run needs.  EDX_WS_LANCZOS_MIN = 5 is what the
+ * run needs, with or without psi0 (all of it that a call without psi0 uses).
+ * EDX_WS_GREEN holds two branches at once for vectors of up to 32 MiB;
+ * EDX_WS_GREEN_MIN = 6 is what one after the other needs.  Every size from the
+ * least up is accepted. */
 size_t edx_workspace_bytes(const edx_sector* s, int32_t what, int32_t vtype,
                            int32_t n);
 
@@ -253,8 +261,8 @@ size_t edx_workspace_bytes(const edx_sector* s, int32_t what, int32_t vtype,
  * beta_{j+1} = |w|, v_{j+1} = w / beta_{j+1}; scalars and dots in FP64.
  * psi0 (nullable, D elements of opts->vtype) receives the normalised ground
  * vector: summed over the run's vectors that the workspace has room to keep
- * (edx_workspace_bytes asks for up to 4 GiB of them; fewer or none will do),
- * beyond them from a replay of the same recurrence.  A run from one start
+ * (EDX_WS_LANCZOS asks for up to 4 GiB of them; fewer or none will do), beyond
+ * them from a replay of the same recurrence.  A run from one start
  * vector sees one vector of a degenerate level; with psi0 requested and
  * opts->degen_check set, a further run deflated against psi0 tests the
  * ground level against the degeneracy threshold gs_threshold (Appendix A,
@@ -275,7 +283,7 @@ edx_status edx_lanczos_ground_state(const edx_sector* s,
  * GPU inside the library (held from the first call on that GPU until the
  * process ends) instead of a caller buffer, and the call itself allocates
  * nothing.  The sector's device must be the current device.  A sector whose
- * workspace (edx_workspace_bytes, what = EDX_WS_LANCZOS, or
+ * workspace (edx_workspace_bytes, what = EDX_WS_LANCZOS_MIN, or
  * EDX_WS_LANCZOS_BASIS for reorth 2 and 3) exceeds 256 MiB -> EDX_E_NOMEM.
  * Every call on one GPU uses the same array: calls that overlap on one GPU
  * (from several host threads or streams) race and must be serialised by the

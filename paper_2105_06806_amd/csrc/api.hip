@@ -324,7 +324,9 @@ size_t edx_workspace_bytes(const edx_sector* s, int32_t what, int32_t vtype, int
   if (!s || !valid_vtype(vtype) || n < 1) return 0;
   if (what == EDX_WS_LANCZOS)
     return lanczos_workspace_bytes(s, vtype, n, 0) + lanczos_keep_bytes(s, vtype, n);
+  if (what == EDX_WS_LANCZOS_MIN) return lanczos_workspace_bytes(s, vtype, n, 0);
   if (what == EDX_WS_GREEN) return green_workspace_bytes(s, vtype, n, true);
+  if (what == EDX_WS_GREEN_MIN) return green_workspace_bytes(s, vtype, n, false);
   if (what == 2) return lanczos_workspace_bytes(s, vtype, n, 2);   // full re-orthogonalisation
   if (what == EDX_WS_CHI) return chi_workspace_bytes(s, vtype, n);
   if (what == EDX_WS_PAIR) return pair_workspace_bytes(s, vtype, n);

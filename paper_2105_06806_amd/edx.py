@@ -20,6 +20,7 @@ LIB_PATH = os.path.join(_HERE, "libedx.so")
  EDX_PENDING) = range(8)
 F64, F32 = 0, 1
 WS_LANCZOS, WS_GREEN, WS_LANCZOS_FULL = 0, 1, 2
+WS_LANCZOS_MIN, WS_GREEN_MIN = 5, 6   # the least that a call accepts
 
 
 class EdxError(RuntimeError):
@@ -481,15 +482,26 @@ def alloc_workspace(nbytes, device="cuda"):
     return torch.empty(int(nbytes), dtype=torch.uint8, device=device)
 
 
+def _own_workspace(size, least):
+    """A call's own workspace: of size() bytes, or of least() where the device
+    has no room for that."""
+    try:
+        return alloc_workspace(size())
+    except torch.cuda.OutOfMemoryError:
+        return alloc_workspace(least())
+
+
 def lanczos_ground_state(sector, want_psi=True, ws=None, stream=None, allow=(EDX_OK,), **kw):
     """Returns (e0, psi0 tensor or None, report dict, status)."""
     o = lanczos_opts(**kw)
     _check_start(sector, o, kw.get("start"))
-    what = WS_LANCZOS_FULL if o.reorth >= 2 else WS_LANCZOS
-    need = workspace_bytes(sector, what, o.vtype, o.niter)
-    if ws is None:
-        ws = alloc_workspace(need)
     psi = torch.empty(sector.dim, dtype=_dtype_of(o.vtype), device="cuda") if want_psi else None
+    if ws is None:
+        # vectors are kept for psi0 alone, and where there is room for them
+        least = WS_LANCZOS_FULL if o.reorth >= 2 else WS_LANCZOS_MIN
+        what = WS_LANCZOS if want_psi and o.reorth < 2 else least
+        ws = _own_workspace(lambda: workspace_bytes(sector, what, o.vtype, o.niter),
+                            lambda: workspace_bytes(sector, least, o.vtype, o.niter))
     e0 = ctypes.c_double()
     rep = LanczosReport()
     st = lib.edx_lanczos_ground_state(sector.handle, ctypes.byref(o), _P(ws.data_ptr()), ws.numel(),
@@ -525,9 +537,9 @@ def green_cf(sector, psi0, e0, orb=0, spin=0, ngf=200, beta=200.0, lmats=4096, w
     """Impurity G(i w_n) as a complex numpy array, plus the report dict."""
     vtype = _check_state(sector, psi0)
     o = GfOpts(int(ngf), int(lmats), vtype, 0, float(beta))
-    need = workspace_bytes(sector, WS_GREEN, vtype, ngf)
     if ws is None:
-        ws = alloc_workspace(need)
+        ws = _own_workspace(lambda: workspace_bytes(sector, WS_GREEN, vtype, ngf),
+                            lambda: workspace_bytes(sector, WS_GREEN_MIN, vtype, ngf))
     g = np.zeros(2 * lmats, np.float64)
     rep = GfReport()
     bufs = {}
@@ -787,7 +799,9 @@ def batch_ground_state(sectors, tiles=None, ws=None, stream=None, **kw):
     lw = tiles["lane_wgs"] if tiles else 32
     wmin = tiles.get("wide_min_dim", 0) if tiles else 0
     if ws is None:
-        ws = alloc_workspace(batch_workspace_bytes(sectors, o.vtype, lw, wmin))
+        # without a threshold the lanes take what there is no room for off them
+        ws = _own_workspace(lambda: batch_workspace_bytes(sectors, o.vtype, lw, wmin),
+                            lambda: batch_workspace_bytes(sectors, o.vtype, lw, wmin or 2000000))
     res = (BatchResult * n)()
     ms = ctypes.c_double()
     tp = None
