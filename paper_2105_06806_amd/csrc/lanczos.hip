@@ -23,7 +23,6 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
-#include <mutex>
 #include <utility>
 
 #include "edx_internal.h"
@@ -475,20 +474,18 @@ edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int 
 // With a slot of pinned memory the copies of a chunk are queued behind it and
 // the next chunk behind them, so the device goes on while the host applies the
 // stop rule; without one a chunk is copied and waited for before the next.
-// Slots are kept for the life of the process (at most kMaxSlots of them, 4 KiB
-// and two events each), held by one call at a time.
+// A slot (4 KiB and two events) is held by one call at a time.
 class ChunkReader {
  public:
   static constexpr int kMaxChunk = 128;
   ChunkReader(bool ahead, int every, hipStream_t st) : st_(st) {
-    if (ahead && every <= kMaxChunk) slot_ = acquire();
+    if (ahead && every <= kMaxChunk) slot_ = SlotPool<Slot>::take();
   }
   ~ChunkReader() {
     if (!slot_) return;
     for (int i = 0; i < 2; ++i)
       if (busy_[i]) (void)hipEventSynchronize(slot_->ev[i]);
-    std::lock_guard<std::mutex> lk(mutex());
-    slot_->used = false;
+    SlotPool<Slot>::give(slot_);
   }
   ChunkReader(const ChunkReader&) = delete;
   ChunkReader& operator=(const ChunkReader&) = delete;
@@ -530,42 +527,25 @@ class ChunkReader {
 
  private:
   struct Slot {
+    static constexpr int kKeep = 64;
     double* host = nullptr;   // two chunks of alpha and beta
     hipEvent_t ev[2] = {nullptr, nullptr};
     int device = 0;
-    bool used = false;
+    Slot* next = nullptr;
+    bool make() {
+      if (hipHostMalloc((void**)&host, sizeof(double) * 4 * kMaxChunk, hipHostMallocDefault) !=
+          hipSuccess)
+        return false;
+      for (hipEvent_t& e : ev)
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return false;
+      return true;
+    }
+    void drop() {
+      for (hipEvent_t e : ev)
+        if (e) (void)hipEventDestroy(e);
+      if (host) (void)hipHostFree(host);
+    }
   };
-  static constexpr int kMaxSlots = 64;
-  static std::mutex& mutex() {
-    static std::mutex* m = new std::mutex;   // never destroyed: calls may outlive statics
-    return *m;
-  }
-  static Slot* acquire() {
-    int device = -1;
-    if (hipGetDevice(&device) != hipSuccess) return nullptr;
-    static std::vector<Slot*>* all = new std::vector<Slot*>;
-    std::lock_guard<std::mutex> lk(mutex());
-    for (Slot* q : *all)
-      if (!q->used && q->device == device) {
-        q->used = true;
-        return q;
-      }
-    if ((int)all->size() >= kMaxSlots) return nullptr;
-    Slot q;
-    q.device = device;
-    q.used = true;
-    if (hipHostMalloc((void**)&q.host, sizeof(double) * 4 * kMaxChunk, hipHostMallocDefault) !=
-        hipSuccess)
-      return nullptr;
-    for (hipEvent_t& e : q.ev)
-      if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-        if (q.ev[0]) (void)hipEventDestroy(q.ev[0]);
-        (void)hipHostFree(q.host);
-        return nullptr;
-      }
-    all->push_back(new Slot(q));
-    return all->back();
-  }
 
   hipStream_t st_;
   Slot* slot_ = nullptr;

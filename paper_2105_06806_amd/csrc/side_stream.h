@@ -1,14 +1,12 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
-#include <mutex>
-#include <vector>
+#include "slot_pool.h"
 
 namespace edx {
 
-// A second stream for a call, with an event to order it behind the caller's:
-// kept for the life of the process (at most kMax of them), held by one call at
-// a time; the destructor waits for what is still running on it.
+// A second stream for a call, with an event to order it behind the caller's;
+// the destructor waits for what is still running on it and gives it back.
 class SideStream {
  public:
   SideStream() = default;
@@ -17,50 +15,42 @@ class SideStream {
   ~SideStream() {
     if (!slot_) return;
     (void)hipStreamSynchronize(slot_->st);
-    std::lock_guard<std::mutex> lk(mutex());
-    slot_->used = false;
+    SlotPool<Slot>::give(slot_);
   }
-  // its work starts after what is on `st` now; false: no stream to be had
+  // its work starts after what is on `st` now; false: no stream to be had, or
+  // `st` is being captured (the stream would become part of the graph)
   bool fork(hipStream_t st) {
-    slot_ = acquire();
-    return slot_ && hipEventRecord(slot_->ev, st) == hipSuccess &&
-           hipStreamWaitEvent(slot_->st, slot_->ev, 0) == hipSuccess;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) return failed();
+    if (cs != hipStreamCaptureStatusNone) return false;
+    slot_ = SlotPool<Slot>::take();
+    if (!slot_) return false;
+    if (hipEventRecord(slot_->ev, st) == hipSuccess &&
+        hipStreamWaitEvent(slot_->st, slot_->ev, 0) == hipSuccess)
+      return true;
+    return failed();
   }
   hipStream_t stream() const { return slot_->st; }
 
  private:
   struct Slot {
+    static constexpr int kKeep = 16;
     hipStream_t st = nullptr;
     hipEvent_t ev = nullptr;
     int device = 0;
-    bool used = false;
-  };
-  static constexpr int kMax = 16;
-  static std::mutex& mutex() {
-    static std::mutex* m = new std::mutex;   // never destroyed: calls may outlive statics
-    return *m;
-  }
-  static Slot* acquire() {
-    static std::vector<Slot*>* all = new std::vector<Slot*>;
-    int device = -1;
-    if (hipGetDevice(&device) != hipSuccess) return nullptr;
-    std::lock_guard<std::mutex> lk(mutex());
-    for (Slot* q : *all)
-      if (!q->used && q->device == device) {
-        q->used = true;
-        return q;
-      }
-    if ((int)all->size() >= kMax) return nullptr;
-    Slot q;
-    q.device = device;
-    q.used = true;
-    if (hipStreamCreateWithFlags(&q.st, hipStreamNonBlocking) != hipSuccess) return nullptr;
-    if (hipEventCreateWithFlags(&q.ev, hipEventDisableTiming) != hipSuccess) {
-      (void)hipStreamDestroy(q.st);
-      return nullptr;
+    Slot* next = nullptr;
+    bool make() {
+      return hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess &&
+             hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
     }
-    all->push_back(new Slot(q));
-    return all->back();
+    void drop() {
+      if (ev) (void)hipEventDestroy(ev);
+      if (st) (void)hipStreamDestroy(st);
+    }
+  };
+  static bool failed() {
+    (void)hipGetLastError();   // the call goes on without the stream
+    return false;
   }
   Slot* slot_ = nullptr;
 };
