@@ -493,10 +493,12 @@ edx_status check_group(const edx_sector* const* secs, int K, int vtype) {
       set_error("multi: sectors of different shapes");
       return EDX_E_INVALID;
     }
-  if (!multi_supported(secs[0], K, vtype)) {
-    set_error("multi: sector shape not supported by the multi-set pass");
-    return EDX_E_UNSUPPORTED;
-  }
+  // each of them: a shape says nothing of H_nd and phonon terms
+  for (int b = 0; b < K; ++b)
+    if (!multi_supported(secs[b], K, vtype)) {
+      set_error("multi: sector not supported by the multi-set pass");
+      return EDX_E_UNSUPPORTED;
+    }
   return EDX_OK;
 }
 

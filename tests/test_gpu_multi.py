@@ -224,3 +224,22 @@ def test_hv_multi_repeats_bit_for_bit(edx, norb, nbath, sec, k, dtype):
         for y, r in zip(edx.deinterleave(Ss[0], buf[: v.numel()], k), ref):
             assert torch.equal(y, r)
         assert bool((buf[v.numel():] == 5.0).all())
+
+
+@pytest.mark.parametrize("at", [0, 1, 3])
+@pytest.mark.parametrize("kind", ["nd", "phonon"])
+def test_hv_multi_refuses_terms_it_does_not_apply(edx, kind, at):
+    """A set with spin exchange or phonons is refused wherever it stands."""
+    import torch
+    plain = dict(norb=2, nbath=3) if kind == "nd" else dict(norb=1, nbath=7)
+    kw = dict(Jx=0.4, Jp=0.3) if kind == "nd" else dict(nph=1, w0=0.5, g=0.3)
+    ms = [inputs.make_model(U=2.0, Jh=0.3, seed=1700 + b, symmetric=False, **plain, **(kw if b == at else {}))
+          for b in range(4)]
+    Ss = [edx.build_sector(m, 4, 4) for m in ms]
+    n = Ss[0].ld * Ss[0].ddw * 4
+    # apart by a vector with phonons, so that the overlap check has nothing to say
+    buf = torch.zeros(4 * n, dtype=torch.float64, device="cuda")
+    ws = edx.alloc_workspace(64 << 20)
+    with pytest.raises(edx.EdxError) as ei:
+        edx.hv_multi(Ss, buf[:n], buf[3 * n:], ws=ws)
+    assert ei.value.status == edx.EDX_E_UNSUPPORTED
