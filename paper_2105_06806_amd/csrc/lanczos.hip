@@ -531,6 +531,7 @@ class ChunkReader {
     double* host = nullptr;   // two chunks of alpha and beta
     hipEvent_t ev[2] = {nullptr, nullptr};
     int device = 0;
+    int64_t serial = 0;
     Slot* next = nullptr;
     bool make() {
       if (hipHostMalloc((void**)&host, sizeof(double) * 4 * kMaxChunk, hipHostMallocDefault) !=

@@ -38,6 +38,7 @@ class SideStream {
     hipStream_t st = nullptr;
     hipEvent_t ev = nullptr;
     int device = 0;
+    int64_t serial = 0;
     Slot* next = nullptr;
     bool make() {
       return hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess &&

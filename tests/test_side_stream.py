@@ -72,6 +72,16 @@ int main() {
     edx::SideStream again;
     CHECK(again.fork(&caller) && g_streams == 16 + 3 * 8);    // one that was kept
   }
+  {
+    // the same ones in the same order again, whatever order they came back in
+    auto a = std::make_unique<edx::SideStream>(), b = std::make_unique<edx::SideStream>();
+    CHECK(a->fork(&caller) && b->fork(&caller));
+    hipStream_t first = a->stream(), second = b->stream();
+    a.reset();
+    b.reset();
+    edx::SideStream c, d;
+    CHECK(c.fork(&caller) && c.stream() == first && d.fork(&caller) && d.stream() == second);
+  }
   // none to be had: the call goes on, and its next look at the last error is clean
   g_device = 5;
   g_limit = 0;
