@@ -57,3 +57,21 @@ def test_step_small_sectors(edx, ns, nup, ndw, reorth):
     assert abs(e0 - e) <= 1e-12 * max(1.0, abs(e))
     x = psi.cpu().numpy()
     assert np.linalg.norm(H @ x - e * x) <= 1e-8
+
+
+@pytest.mark.parametrize("dtype,reorth", [("f64", 0), ("f64", 1), ("f32", 0), ("f32", 1)])
+def test_step_few_columns(edx, dtype, reorth):
+    """Ns=14 1/13: D_dw = 14 columns of 14 rows, fewer partials than a workgroup
+    has threads; against the oracle (FP64 to rounding, FP32 at its energy floor)."""
+    m = inputs.make_model(1, 13, 2.0, seed=78)
+    S = edx.build_sector(m, 1, 13)
+    assert S.ddw == 14 and S.dup == 14
+    tol, rtol = (1e-14, 1e-11) if dtype == "f64" else (1e-9, 1e-6)
+    e0, psi, rep, _ = edx.lanczos_ground_state(S, vtype=dtype, niter=196, tol=tol, rtol=rtol, seed=5,
+                                               reorth=reorth, allow=(edx.EDX_E_DEGENERATE,))
+    H = fock.explicit_hamiltonian(m, 1, 13)
+    e = np.linalg.eigvalsh(H.toarray() if hasattr(H, "toarray") else H)[0]
+    eps, res = (1e-12, 1e-8) if dtype == "f64" else (1e-6, 1e-3)
+    assert abs(e0 - e) <= eps * max(1.0, abs(e))
+    x = psi.double().cpu().numpy()
+    assert np.linalg.norm(H @ x - e * x) <= res * max(1.0, abs(e))
