@@ -68,10 +68,10 @@ constexpr int kMaxBatchIter = 2048;   // niter bound of the batch call
 // one job's kernels fill the gaps while another's host checks its stop rule.
 // Units of work (a job, or a group of the multi-set pass) with a workspace above
 // kSmallUnit have vectors beyond the caches and fill the chip: three streams
-// (27 jobs of Ns=14 FP32: 114 ms on 3, 120 on 6, 124 on 10).  The smaller ones
-// are bound by launches and the host's checks and have kSmallStreams more
-// (75 jobs of Ns=12 FP32: 36.8 ms on 3, 27.9 on 6, 26.7 on 10; Ns=8: 16.8,
-// 11.6, 10.5).
+// (27 jobs of Ns=14 FP32: 160 ms on 1, 121 on 2, 114 on 3, 120 on 6).  The smaller
+// ones are bound by launches and the host's checks and have kSmallStreams more
+// (75 jobs of Ns=12 FP32: 36.6 ms on 3, 27.3 on 6, 26.0 on 8, 25.8 on 10; Ns=8:
+// 16.8, 11.3, 10.0, 9.6).
 constexpr int kWideStreams = 3;
 constexpr int kSmallStreams = 5;
 constexpr size_t kSmallUnit = size_t(128) << 20;
@@ -482,8 +482,8 @@ int device_cus() {
 }  // namespace
 
 // By default every job takes the whole-GPU path: it is ahead of the lanes at all
-// sizes (75 jobs FP32 of Ns=12: 28 vs 67 ms, Ns=10: 14.8 vs 29.5, Ns=8: 11.6 vs
-// 21.1, Ns=7: 9.7 vs 17.1; 600 jobs of Ns=8 and 9: 41 vs 189), as a lane's step
+// sizes (75 jobs FP32 of Ns=12: 26 vs 67 ms, Ns=10: 13.1 vs 30.8, Ns=8: 10.1 vs
+// 21.0, Ns=7: 8.3 vs 17.3; 600 jobs of Ns=8 and 9: 36 vs 189), as a lane's step
 // is four barriers of its 32 workgroups and a pass over the vectors for each.
 int64_t batch_wide_default() { return 1; }
 

@@ -663,6 +663,7 @@ __global__ __launch_bounds__(1024) void k_hv_fused(HvArgs<T> a, const T* __restr
   // ALL: the block owns NC columns (every block but possibly the last); then
   // nothing in the row body is conditional and the compiler keeps all
   // gathers of a row in flight together
+  // Of the spin-up row every slot of the padded row is walked.
   // WK: spin-down slots gathered per row -- 8 (FP32: or 10 or 12) when no column
   // of the block has more real hops than that (the padding entries follow the
   // real ones), else every slot of the padded row
@@ -1197,11 +1198,12 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
   // phonon neighbours are read by global loads past the slice and keep to
   // 16-byte boundaries.  With H_nd not where one column fills the LDS (its term
   // loops then have 16 waves of half as many lanes: Ns=16 Norb=2 2021 -> 2153 us),
-  // nor there with wide rows of both spins for Norb=1, where half of the columns
-  // go past the eighth slot (Ns=16 9/9 1582 -> 1611 us; for Norb=2, a fifth of
-  // them, 1994 -> 1882 us), nor where two columns with wide spin-up rows alone
-  // leave room for one block more at most (Ns=15 9/8 256 -> 263 us; Ns=14 9/7
-  // 55.5 -> 49.8 us).
+  // nor there with wide rows of both spins where many columns go past the eighth
+  // slot, which Norb = 1 stands for: half of them do (Ns=16 9/9 1582 -> 1611 us),
+  // for Norb=2 a fifth (1994 -> 1882 us); nor where two columns with wide spin-up
+  // rows alone leave room for one block more at most (Ns=15 9/8 256 -> 263 us;
+  // Ns=14 9/7 55.5 -> 49.8 us).  Each of these exceptions rests on the one or two
+  // sectors named.
   if constexpr (NC <= 2 && sizeof(T) == 8) {
     const bool al16 = a.ld % 2 == 0 && (reinterpret_cast<uintptr_t>(v) & 15u) == 0;
     if (buf && (al16 || !fo.ph) && a.dup > 256 && lds + 16 * NC <= 160 * 1024 &&
@@ -1456,7 +1458,8 @@ size_t smem_header() { return kAmpTable * 8 + 64 * 8 + 16 * 8; }
 // measured and, since its staging has no check per load, the one-workgroup pass
 // too (half-filled Ns=8 FP64 9.8 -> 3.6 us, Ns=7 4.4 -> 3.5 us).  The rules
 // below are the fastest of (columns, threads, order) swept over Ns = 7..16, Norb
-// 1..3, both types, launches back to back; a CU holds 16 waves of these kernels.
+// 1..3, both types, launches back to back.  The registers of these kernels leave
+// 16 (FP64 with two columns or H_nd) to 32 waves on a CU, a block has 16 at most.
 HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   HvPlan p;
   p.mode = 2;
@@ -1477,9 +1480,12 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   // grids of one round (Ns=12 9.6 -> 9.0 us).
   // FP64 on 16-byte lanes: one (Ns=12 8.1 -> 7.0 us, Ns=13 23.1 -> 20.3 us: more
   // waves fit), two where hop rows are wide or there is H_nd and the columns are
-  // long (Norb=2 Ns=14 78.6 -> 74.1 us, with H_nd 108 -> 95 us), and from 2048
-  // columns on, where it costs a product little (Ns=14 80 -> 83 us) and lets the
-  // Lanczos update fold the step's reductions; but one where only the spin-down
+  // long (Norb=2 Ns=14 78.6 -> 74.1 us, with H_nd 108 -> 95 us), and above 2048
+  // columns.  Up to 4096 of them that lets the Lanczos update fold the step's
+  // reductions, for a little on the product (Ns=14 7/7: a step 155.2 -> 151.0 us,
+  // the product 79.3 -> 81.0 us; 6/7: 133.9 -> 130.7, 67.6 -> 70.6 us); beyond, where
+  // nothing folds, the product itself gains (Ns=15 7/7 329.1 -> 322.7 us, a step
+  // 606.6 -> 604.0 us) as long as two columns fit.  But one where only the spin-down
   // rows are wide (Ns=14 7/9 104 -> 46 us, Ns=15 8/9 475 -> 245 us: with two, each
   // row reads both columns' further hops from the table).
   // Either: fewer where less than 1.5 blocks per CU are left (Ns=11, 462 columns:
@@ -1495,8 +1501,8 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   while (c > 1 && (!fits(c) || blocks(c) < 384)) --c;
   p.col_cols = c;
   p.col_blocks = (int)((s->ddw + c - 1) / c);
-  // Threads: all of a CU's waves in one block where its LDS image leaves room
-  // for one block only (Norb=2 Ns=16 FP64 with H_nd: 512 -> 1024 threads 2303 ->
+  // Threads: 16 waves in one block where its LDS image leaves room for one block
+  // only (Norb=2 Ns=16 FP64 with H_nd: 512 -> 1024 threads 2303 ->
   // 2041 us; FP64 with 8-slot rows on 16-byte lanes is as fast with 8 waves: Ns=16
   // 1498 -> 1480 us, Ns=15 324 -> 321 us, dense 355 -> 340 us); 256 where columns are short -- FP32 grids of
   // 513-1024 blocks then run in one round (Ns=13 14.8 -> 14.4 us), FP64 up to 1024
