@@ -50,36 +50,6 @@ int sturm_count(const double* a, const double* b, int m, double x, double tiny) 
   return cnt;
 }
 
-}  // namespace
-
-// k-th smallest eigenvalue (k = 0, 1, ...) of the symmetric tridiagonal matrix.
-double tridiag_lowest(const double* a, const double* b, int m, int k) {
-  if (m == 1) return a[0];
-  double lo = a[0], hi = a[0], nrm = 0.0;
-  for (int i = 0; i < m; ++i) {
-    const double r = (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i < m - 1 ? std::fabs(b[i]) : 0.0);
-    lo = std::min(lo, a[i] - r);
-    hi = std::max(hi, a[i] + r);
-    nrm = std::max(nrm, std::fabs(a[i]) + r);
-  }
-  const double tiny = std::max(nrm, 1.0) * 1e-300;
-  const double eps = std::numeric_limits<double>::epsilon();
-  lo -= eps * nrm + tiny;
-  hi += eps * nrm + tiny;
-  for (int it = 0; it < 200; ++it) {
-    const double mid = 0.5 * (lo + hi);
-    if (mid <= lo || mid >= hi) break;
-    if (sturm_count(a, b, m, mid, tiny) > k)
-      hi = mid;
-    else
-      lo = mid;
-    if (hi - lo <= 2.0 * eps * std::max(std::fabs(lo), std::fabs(hi))) break;
-  }
-  return 0.5 * (lo + hi);
-}
-
-namespace {
-
 // For kLanes shifts at once, whether T - x has a negative pivot (x above the
 // lowest eigenvalue).  The pivot recurrence is one division after another, so
 // independent shifts in vector lanes cost little more than one.
@@ -103,14 +73,58 @@ void any_below(const double* a, const double* b, int m, const double (&x)[kLanes
   for (int l = 0; l < kLanes; ++l) neg[l] = low[l] < 0.0;
 }
 
+// Gershgorin bounds of T, a little widened, and the threshold of a zero pivot
+void tridiag_bounds(const double* a, const double* b, int m, double& lo, double& hi, double& nrm,
+                    double& tiny) {
+  lo = hi = a[0];
+  nrm = 0.0;
+  for (int i = 0; i < m; ++i) {
+    const double r = (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i < m - 1 ? std::fabs(b[i]) : 0.0);
+    lo = std::min(lo, a[i] - r);
+    hi = std::max(hi, a[i] + r);
+    nrm = std::max(nrm, std::fabs(a[i]) + r);
+  }
+  tiny = std::max(nrm, 1.0) * 1e-300;
+  const double eps = std::numeric_limits<double>::epsilon();
+  lo -= eps * nrm + tiny;
+  hi += eps * nrm + tiny;
+}
+
+// Bisection from lo, hi: below(x) says whether an eigenvalue wanted lies below x
+template <typename Below>
+double bisect(double lo, double hi, Below below) {
+  const double eps = std::numeric_limits<double>::epsilon();
+  for (int it = 0; it < 200; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    if (mid <= lo || mid >= hi) break;
+    if (below(mid))
+      hi = mid;
+    else
+      lo = mid;
+    if (hi - lo <= 2.0 * eps * std::max(std::fabs(lo), std::fabs(hi))) break;
+  }
+  return 0.5 * (lo + hi);
+}
+
 }  // namespace
+
+// k-th smallest eigenvalue (k = 0, 1, ...) of the symmetric tridiagonal matrix.
+double tridiag_lowest(const double* a, const double* b, int m, int k) {
+  if (m == 1) return a[0];
+  double lo, hi, nrm, tiny;
+  tridiag_bounds(a, b, m, lo, hi, nrm, tiny);
+  return bisect(lo, hi, [&](double x) { return sturm_count(a, b, m, x, tiny) > k; });
+}
 
 // The lowest eigenvalue of T_m lies at or below that of T_{m-1} (interlacing)
 // and, once the run converges, hardly below it: the bracket starts there, as
 // wide as a few of the last decreases, and is cut into kLanes + 1 parts per
-// sweep down to the width at which tridiag_lowest stops.  4-8 sweeps where the
-// bisection from the Gershgorin bounds takes 55 (ground state of half-filled
-// Ns=12, 140 steps: 30 us of host time a step before).
+// sweep down to the width at which tridiag_lowest stops.  The bisection of
+// tridiag_lowest then runs on it, with a count only for the few points inside:
+// the value is that function's to the last bit, so that it settles exactly once
+// the run has converged, which a stop rule with tol = 0 waits for.  4-8 sweeps
+// where the bisection alone takes 55 (ground state of half-filled Ns=12, 140 steps:
+// 30 us of host time a step before).
 double LowestRitz::next(const double* a, const double* b, int m) {
   const bool warm = m == m_ + 1 && m > 2;
   const double eold = e_;
@@ -118,17 +132,10 @@ double LowestRitz::next(const double* a, const double* b, int m) {
   if (m == 1) {
     e = a[0];
   } else {
-    double lo = a[0], hi = a[0], nrm = 0.0;
-    for (int i = 0; i < m; ++i) {
-      const double r = (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i < m - 1 ? std::fabs(b[i]) : 0.0);
-      lo = std::min(lo, a[i] - r);
-      hi = std::max(hi, a[i] + r);
-      nrm = std::max(nrm, std::fabs(a[i]) + r);
-    }
-    const double tiny = std::max(nrm, 1.0) * 1e-300;
+    double from, to, nrm, tiny;
+    tridiag_bounds(a, b, m, from, to, nrm, tiny);
+    double lo = from, hi = to;   // no eigenvalue below lo, one below hi
     const double eps = std::numeric_limits<double>::epsilon();
-    lo -= eps * nrm + tiny;
-    hi += eps * nrm + tiny;
     double x[kLanes];
     bool neg[kLanes];
     if (warm) {
@@ -156,7 +163,13 @@ double LowestRitz::next(const double* a, const double* b, int m) {
         }
       if (!(hi - lo < w)) break;   // no point between them is left
     }
-    e = 0.5 * (lo + hi);
+    e = bisect(from, to, [&](double y) {
+      if (y >= hi) return true;
+      if (y <= lo) return false;
+      const bool below = sturm_count(a, b, m, y, tiny) > 0;
+      (below ? hi : lo) = y;
+      return below;
+    });
   }
   de_ = m > 1 ? std::max(0.0, eold - e) : 0.0;
   e_ = e;

@@ -56,3 +56,26 @@ def test_lowest_ritz_value(solvers):
             assert abs(follow(state, pa, pb, m) - ev[0]) <= tol
             for k in range(m):
                 assert abs(bisect(pa, pb, m, k) - ev[k]) <= tol, (m, k)
+
+
+def test_followed_value_is_the_bisected_one(solvers):
+    """To the last bit, after every row, so that a run which has converged sees
+    the same value again (a stop rule with tol = 0 waits for that)."""
+    bisect, follow = solvers
+    rng = np.random.default_rng(8)
+    settled = 0
+    for trial in range(60):
+        m = int(rng.integers(2, 120))
+        a, b = rng.normal(size=m), np.abs(rng.normal(size=m)) + 0.2
+        a[0] -= rng.choice([0.0, 4.0])        # a level that converges within a few rows
+        a *= 10.0 ** rng.integers(-3, 4)
+        b *= 10.0 ** rng.integers(-3, 1)
+        pa, pb = a.ctypes.data_as(_D), b.ctypes.data_as(_D)
+        state = (ctypes.c_double * 4)()
+        last = None
+        for k in range(1, m + 1):
+            e = follow(state, pa, pb, k)
+            assert e == bisect(pa, pb, k, 0)
+            settled += e == last
+            last = e
+    assert settled > 1000
