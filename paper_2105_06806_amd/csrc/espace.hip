@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "edx_internal.h"
+#include "side_stream.h"
 
 struct edx_espace {
   edx_espace_opts o{};
@@ -42,6 +43,9 @@ namespace {
 // each): small sectors are bound by launch and synchronisation latency, which
 // the other streams' work hides
 constexpr int kEspaceStreams = 3;
+// They come from the pool that the batch and the Green's functions use: streams
+// made beside those kept there could end up on the hardware queue of the caller's
+// (27 sectors' thermal G after a batch of small sectors: 29 -> 43 ms).
 
 edx_status invalid_e(const std::string& msg) {
   set_error(msg);
@@ -69,12 +73,14 @@ edx_status for_kept_states(const edx_espace* E, void* ws, size_t ws_bytes, size_
     return EDX_E_DEVICE;
   }
   std::vector<hipStream_t> sts(T, st);
-  for (int t = 1; t < T; ++t)
-    if (hipStreamCreateWithFlags(&sts[t], hipStreamNonBlocking) != hipSuccess) {
-      for (int q = 1; q < t; ++q) (void)hipStreamDestroy(sts[q]);
+  std::vector<SideStream> side(T);
+  for (int t = 1; t < T; ++t) {
+    if (!side[t].fork(st)) {
       set_error("espace: stream set-up failed");
       return EDX_E_DEVICE;
     }
+    sts[t] = side[t].stream();
+  }
   std::vector<edx_status> tst(T, EDX_OK);
   std::vector<std::string> terr(T);
   std::atomic<bool> stop{false};
@@ -100,10 +106,7 @@ edx_status for_kept_states(const edx_espace* E, void* ws, size_t ws_bytes, size_
   for (int t = 1; t < T; ++t) th.emplace_back(worker, t);
   worker(0);
   for (auto& x : th) x.join();
-  for (int t = 1; t < T; ++t) {
-    (void)hipStreamSynchronize(sts[t]);
-    (void)hipStreamDestroy(sts[t]);
-  }
+  side.clear();   // waits for their work
   for (int t = 0; t < T; ++t)
     if (tst[t] != EDX_OK) {
       set_error(terr[t]);
@@ -233,12 +236,14 @@ edx_status edx_espace_diag(edx_espace* E, edx_sector* const* secs, int32_t nsec,
     return EDX_E_DEVICE;
   }
   std::vector<hipStream_t> sts(nthr, st);
+  std::vector<SideStream> side(nthr);
   edx_status fail = EDX_OK;
-  for (int t = 1; t < nthr; ++t)
-    if (hipStreamCreateWithFlags(&sts[t], hipStreamNonBlocking) != hipSuccess) {
-      sts[t] = st;
+  for (int t = 1; t < nthr && fail == EDX_OK; ++t) {
+    if (side[t].fork(st))
+      sts[t] = side[t].stream();
+    else
       fail = EDX_E_DEVICE;
-    }
+  }
   std::atomic<int> next{0};
   std::vector<edx_status> tst(nthr, EDX_OK);
   std::vector<std::string> terr(nthr);
@@ -273,11 +278,7 @@ edx_status edx_espace_diag(edx_espace* E, edx_sector* const* secs, int32_t nsec,
     worker(0);
     for (auto& x : th) x.join();
   }
-  for (int t = 1; t < nthr; ++t)
-    if (sts[t] != st) {
-      (void)hipStreamSynchronize(sts[t]);
-      (void)hipStreamDestroy(sts[t]);
-    }
+  side.clear();   // waits for their work
   for (int t = 0; t < nthr && fail == EDX_OK; ++t)
     if (tst[t] != EDX_OK) {
       fail = tst[t];

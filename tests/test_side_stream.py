@@ -117,3 +117,10 @@ def test_side_streams(tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
+
+
+def test_calls_take_their_streams_from_the_pool():
+    """A stream made beside the kept ones may share the hardware queue of the
+    caller's stream; only the server makes its own, for its lifetime."""
+    made = [f for f in sorted(os.listdir(CSRC)) if "hipStreamCreate" in open(os.path.join(CSRC, f)).read()]
+    assert made == ["serve.hip", "side_stream.h"]
