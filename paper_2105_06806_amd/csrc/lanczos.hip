@@ -487,10 +487,10 @@ edx_status lanczos_step(const edx_sector* s, int vtype, const LanczosWs& L, int 
 // With a slot of pinned memory the copies of a chunk are queued behind it and
 // the next chunk behind them, so the device goes on while the host applies the
 // stop rule; without one a chunk is copied and waited for before the next.
-// A slot (4 KiB and two events) is held by one call at a time.
+// A slot (256 bytes and two events) is held by one call at a time.
 class ChunkReader {
  public:
-  static constexpr int kMaxChunk = 128;
+  static constexpr int kMaxChunk = 8;   // longer ones are not run ahead (see kAheadBytes)
   ChunkReader(bool ahead, int every, hipStream_t st) : st_(st) {
     if (ahead && every <= kMaxChunk) slot_ = SlotPool<Slot>::take();
   }
@@ -597,7 +597,11 @@ edx_status run_chunks(ChunkReader& rd, const double* alpha, const double* beta, 
 
 // Running one chunk ahead hides the host's check (about 60 us a chunk of 8)
 // and costs the steps of one chunk after the last: worth it while a step is
-// short against the check, on vectors that stay in cache; full
+// short against the check, on vectors that stay in cache, and chunks are short
+// (ground states with psi0, ms without / with the chunk ahead, every 1 / 4 / 8 /
+// 16 / 32 / 128 steps: Ns=8 FP64 5.3/2.9, 3.3/2.1, 2.5/2.1, 2.2/2.3, 2.2/2.9,
+// 3.1/6.5; Ns=12 FP64 10.5/6.2, 7.0/4.7, 5.9/4.6, 5.5/5.0, 5.4/5.8, 6.3/10.6;
+// Ns=13 FP32 7.8/5.0, 6.0/4.7, 5.4/5.0, 5.3/5.7, 5.8/7.5, 9.3/17.6); full
 // re-orthogonalisation makes the last steps the longest.
 constexpr size_t kAheadBytes = size_t(32) << 20;
 
@@ -1358,8 +1362,11 @@ namespace {
 // stays in cache one branch leaves most of the chip idle (a step is two short
 // kernels one after the other), so they run side by side on two streams, up to
 // this vector size; beyond it a step is bound by bandwidth and they take turns
-// in one workspace.
+// in one workspace.  A few steps do not pay for the second stream (at once / in
+// turn, ngf = 1, 6, 16: Ns=4 FP64 205/180, 312/305, 435/454 us; Ns=8 202/179,
+// 310/314, 444/496 us; Ns=12 207/206, 353/400, 564/724 us).
 constexpr size_t kOverlapBytes = size_t(32) << 20;
+constexpr int kOverlapSteps = 6;
 
 }  // namespace
 
@@ -1461,7 +1468,7 @@ edx_status green_cf_impl(const edx_sector* gs, const void* psi0, double e0, int 
                                   nullptr);
   SideStream side;
   const bool both =
-      overlap && nbs[0] && nbs[1] &&
+      overlap && ngf >= kOverlapSteps && nbs[0] && nbs[1] &&
       (size_t)std::max(nbs[0]->vlen, nbs[1]->vlen) * vbytes(vtype) <= kOverlapBytes &&
       green_workspace_bytes(gs, vtype, ngf, true) <= ws_bytes && side.fork(st);
   LanczosWs Ls[2];
