@@ -1508,11 +1508,14 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   // 513-1024 blocks then run in one round (Ns=13 14.8 -> 14.4 us), FP64 up to 1024
   // rows (Ns=12 7.4 -> 7.0 us; 2048 where only the spin-down rows are wide: Ns=13
   // 6/9 12.6 -> 10.9 us), unless the grid is less than one block per CU (Ns=12
-  // 6/9 4.5 -> 5.2 us) -- and for FP32 with H_nd, whose term loops diverge.
+  // 6/9 4.5 -> 5.2 us) -- and for FP32 with H_nd, whose term loops diverge, except
+  // longer columns in grids of two blocks a CU and less (512 -> 256 threads: 3003
+  // rows of 1001 columns 23.7 -> 21.5 us, of 455 12.7 -> 16.0 us, of 91 8.5 -> 12.1 us;
+  // 924 of 924 9.3 -> 8.1 us, of 220 5.5 -> 6.5 us; 495 of 220 5.4 -> 5.2 us).
   const size_t lds = c * colb + ndl;
   const bool shortc = f64 ? s->dup <= (dwide ? 2048 : 1024) && (s->dup <= 512 || blocks(c) >= 256)
                           : s->dup <= 256 || (s->dup <= 2048 && blocks(c) > 512) ||
-                                (s->nd && s->dup <= 4096);
+                                (s->nd && s->dup <= 4096 && (s->dup <= 512 || blocks(c) > 512));
   p.col_threads = 512;
   if (lds > kLdsBytes / 2)
     p.col_threads = f64 && !wide && !s->nd ? 512 : 1024;

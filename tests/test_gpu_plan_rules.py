@@ -1,0 +1,41 @@
+"""Default launch plans at the edges of their rules, for FP32 products with spin
+exchange and pair hopping: 256 threads where columns are short or the grid has
+more than two blocks a CU, else 512 (the product's result does not depend on it)."""
+import numpy as np
+import pytest
+
+from oracle import fock
+from paper_2105_06806_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def edx():
+    import torch
+    from paper_2105_06806_amd import edx as E
+    assert torch.cuda.is_available()
+    return E
+
+
+@pytest.mark.parametrize("norb,nbath,nup,ndw,threads", [
+    (2, 6, 6, 12, 512),      # 3003 rows, 91 columns
+    (3, 4, 10, 14, 512),     # 3003 rows, 15 columns
+    (3, 3, 6, 3, 512),       # 924 rows, 220 columns
+    (3, 3, 6, 6, 256),       # 924 rows, 924 columns
+    (3, 3, 4, 3, 256),       # 495 rows, 220 columns
+])
+def test_threads_with_nd_terms(edx, norb, nbath, nup, ndw, threads):
+    import torch
+    m = inputs.make_model(norb, nbath, 2.5, Jh=0.4, seed=91, symmetric=False, Jx=0.4, Jp=0.3)
+    S = edx.build_sector(m, nup, ndw)
+    assert edx.get_plan(S, "f32")["col_threads"] == threads
+    x = torch.as_tensor(inputs.random_vector(S.dim, seed=3), dtype=torch.float32, device="cuda")
+    y = edx.hv(S, x, torch.empty_like(x)).clone()
+    for other in (256, 512):
+        edx.set_plan(S, "f32", col_threads=other)
+        assert torch.equal(edx.hv(S, x, torch.empty_like(x)), y)
+    if S.dim <= 50000:
+        ref = fock.explicit_hamiltonian(m, nup, ndw) @ x.double().cpu().numpy()
+        # FP32 terms, about 25 an element, each rounded once
+        assert np.abs(y.double().cpu().numpy() - ref).max() <= 2e-6 * np.abs(ref).max()
