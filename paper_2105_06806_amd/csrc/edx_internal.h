@@ -370,6 +370,7 @@ class LowestRitz {
   double next(const double* a, const double* b, int m);   // m = 1, 2, 3, ...
  private:
   double e_ = 0.0, de_ = 0.0;   // last value and its last decrease
+  double cell_lo_ = 0.0, cell_hi_ = 0.0;   // its cell of the bisection
   int m_ = 0;
 };
 void tridiag_vector(const double* a, const double* b, int m, double lam,

@@ -117,64 +117,63 @@ double tridiag_lowest(const double* a, const double* b, int m, int k) {
 }
 
 // The lowest eigenvalue of T_m lies at or below that of T_{m-1} (interlacing)
-// and, once the run converges, hardly below it: the bracket starts there, as
-// wide as a few of the last decreases, and is cut into kLanes + 1 parts per
-// sweep down to the width at which tridiag_lowest stops.  The bisection of
-// tridiag_lowest then runs on it, with a count only for the few points inside:
-// the value is that function's to the last bit, so that it settles exactly once
-// the run has converged, which a stop rule with tol = 0 waits for.  4-8 sweeps
-// where the bisection alone takes 55 (ground state of half-filled Ns=12, 140 steps:
-// 30 us of host time a step before).
+// and, once the run converges, hardly below it.  The bisection of tridiag_lowest
+// is run with few counts: eight shifts at once around the last value and its
+// cell decide most of its points, the next seven points of its tree at once the
+// rest.  The value is that function's to the last bit, so that it settles exactly
+// once the run has converged, which a stop rule with tol = 0 waits for; a settled
+// value takes one sweep where the bisection takes 55 (ground state of half-filled
+// Ns=12, 140 steps: 30 us of host time a step with the bisection alone).
 double LowestRitz::next(const double* a, const double* b, int m) {
   const bool warm = m == m_ + 1 && m > 2;
   const double eold = e_;
-  double e;
-  if (m == 1) {
-    e = a[0];
-  } else {
-    double from, to, nrm, tiny;
-    tridiag_bounds(a, b, m, from, to, nrm, tiny);
-    double lo = from, hi = to;   // no eigenvalue below lo, one below hi
-    const double eps = std::numeric_limits<double>::epsilon();
-    double x[kLanes];
-    bool neg[kLanes];
-    if (warm) {
-      // x[0] just above the last value, the others at growing distances below
-      double d = std::max(2.0 * de_, 8.0 * eps * nrm);
-      x[0] = eold + 4.0 * eps * nrm;
-      for (int l = 1; l < kLanes; ++l, d *= 8.0) x[l] = eold - d;
-      any_below(a, b, m, x, tiny, neg);
-      for (int l = 0; l < kLanes; ++l)
-        if (neg[l])
-          hi = std::min(hi, x[l]);
-        else
-          lo = std::max(lo, x[l]);
-    }
-    for (int it = 0; it < 60 && hi - lo > 2.0 * eps * std::max(std::fabs(lo), std::fabs(hi)); ++it) {
-      const double w = hi - lo;
-      for (int l = 0; l < kLanes; ++l) x[l] = lo + w * ((l + 1) * (1.0 / (kLanes + 1)));
-      any_below(a, b, m, x, tiny, neg);
-      for (int l = 0; l < kLanes; ++l)
-        if (neg[l]) {
-          hi = std::min(hi, x[l]);
-          break;
-        } else {
-          lo = std::max(lo, x[l]);
-        }
-      if (!(hi - lo < w)) break;   // no point between them is left
-    }
-    e = bisect(from, to, [&](double y) {
-      if (y >= hi) return true;
-      if (y <= lo) return false;
-      const bool below = sturm_count(a, b, m, y, tiny) > 0;
-      (below ? hi : lo) = y;
-      return below;
-    });
-  }
-  de_ = m > 1 ? std::max(0.0, eold - e) : 0.0;
-  e_ = e;
   m_ = m;
-  return e;
+  if (m == 1) {
+    de_ = 0.0;
+    return e_ = a[0];
+  }
+  double from, to, nrm, tiny;
+  tridiag_bounds(a, b, m, from, to, nrm, tiny);
+  const double eps = std::numeric_limits<double>::epsilon();
+  double lo = from, hi = to;   // no eigenvalue below lo, one below hi
+  auto sweep = [&](const double (&x)[kLanes]) {
+    bool neg[kLanes];
+    any_below(a, b, m, x, tiny, neg);
+    for (int l = 0; l < kLanes; ++l)
+      if (neg[l])
+        hi = std::min(hi, x[l]);
+      else
+        lo = std::max(lo, x[l]);
+  };
+  if (warm) {
+    // the last cell, a point just above it and others at growing distances below
+    double x[kLanes] = {cell_hi_, cell_lo_, eold + 4.0 * eps * nrm};
+    double d = std::max(2.0 * de_, 8.0 * eps * nrm);
+    for (int l = 3; l < kLanes; ++l, d *= 8.0) x[l] = cell_lo_ - d;
+    sweep(x);
+  }
+  double l = from, h = to;
+  for (int it = 0; it < 200;) {
+    const double mid = 0.5 * (l + h);
+    if (mid <= l || mid >= h) break;
+    if (mid > lo && mid < hi) {
+      const double q1 = 0.5 * (l + mid), q3 = 0.5 * (mid + h);
+      const double x[kLanes] = {mid, q1, q3, 0.5 * (l + q1), 0.5 * (q1 + mid), 0.5 * (mid + q3),
+                                0.5 * (q3 + h), mid};
+      sweep(x);
+    }
+    if (mid >= hi)
+      h = mid;
+    else
+      l = mid;
+    ++it;
+    if (h - l <= 2.0 * eps * std::max(std::fabs(l), std::fabs(h))) break;
+  }
+  cell_lo_ = l;
+  cell_hi_ = h;
+  e_ = 0.5 * (l + h);
+  de_ = std::max(0.0, eold - e_);
+  return e_;
 }
 
 // Eigenvector of T for eigenvalue lam by inverse iteration, Gaussian

@@ -48,7 +48,7 @@ def test_lowest_ritz_value(solvers):
     bisect, follow = solvers
     for a, b in _matrices():
         pa, pb = a.ctypes.data_as(_D), b.ctypes.data_as(_D)
-        state = (ctypes.c_double * 4)()                   # a fresh LowestRitz
+        state = (ctypes.c_double * 16)()                   # a fresh LowestRitz
         for m in range(1, a.size + 1):
             t = np.diag(a[:m]) + np.diag(b[: m - 1], 1) + np.diag(b[: m - 1], -1)
             ev = np.linalg.eigvalsh(t)
@@ -71,7 +71,7 @@ def test_followed_value_is_the_bisected_one(solvers):
         a *= 10.0 ** rng.integers(-3, 4)
         b *= 10.0 ** rng.integers(-3, 1)
         pa, pb = a.ctypes.data_as(_D), b.ctypes.data_as(_D)
-        state = (ctypes.c_double * 4)()
+        state = (ctypes.c_double * 16)()
         last = None
         for k in range(1, m + 1):
             e = follow(state, pa, pb, k)
