@@ -10,7 +10,7 @@
 //                 staged in LDS, so the spin-up gathers hit LDS; adds H_d and
 //                 gathers the spin-down neighbours of each element straight
 //                 from global memory (whole neighbour columns, coalesced).
-//                 The default plan of every sector.
+//                 The default plan of all but the smallest sectors.
 //  * k_hv_vec  -- the same pass with two FP64 rows a lane (16-byte accesses).
 //  * k_hv_col  -- the column pass of the two-pass plan: as k_hv_fused without
 //                 the spin-down gathers, accumulating into w.
@@ -20,8 +20,7 @@
 //                 (workgroups go round-robin over the 8 XCDs), so the slab
 //                 (R x D_dw elements) stays in that XCD's L2 while its ~8 reads
 //                 per element are served.
-//  * k_hv_small -- whole sector in LDS, one block (tiny sectors; a plan of the
-//                 autotuner's, not a default).
+//  * k_hv_small -- whole sector in LDS, one block (the smallest sectors).
 //
 // Two-pass order: k_hv_row writes W = V H_dw^T, then k_hv_col adds
 // H_d o V + H_up V in place and (optionally) the per-block partial sums of
@@ -1454,14 +1453,24 @@ size_t smem_header() { return kAmpTable * 8 + 64 * 8 + 16 * 8; }
 
 }  // namespace
 
-// Every sector takes the fused pass: it beat the two-pass plan on every sector
-// measured and, since its staging has no check per load, the one-workgroup pass
-// too (half-filled Ns=8 FP64 9.8 -> 3.6 us, Ns=7 4.4 -> 3.5 us).  The rules
+// Sectors above kSmallDim states and those with H_nd or phonons take the fused
+// pass: it beat the two-pass plan on every sector measured.  The smallest are a
+// state a thread of one workgroup, which is then ahead (kernel time of one
+// workgroup / fused: 36 to 784 states 3.0-3.3 / 4.1-4.6 us, 1225 3.8 / 4.2, 3024
+// 6.4 / 4.2, 4900 9.3 / 4.2; the ten lowest states of 400: 22.4 -> 21.3 ms, while the
+// ground state of 1225, bound by its launches, took 1.54 -> 1.59 ms).  The rules
 // below are the fastest of (columns, threads, order) swept over Ns = 7..16, Norb
 // 1..3, both types, launches back to back.  The registers of these kernels leave
 // 16 (FP64 with two columns or H_nd) to 32 waves on a CU, a block has 16 at most.
+constexpr int64_t kSmallDim = 1024;
+
 HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   HvPlan p;
+  if (s->dim <= kSmallDim && !s->nd && s->dph == 1) {
+    p.mode = 0;
+    p.col_blocks = 1;
+    return p;
+  }
   p.mode = 2;
   const bool f64 = vtype == EDX_F64;
   const size_t sz = vbytes(vtype);

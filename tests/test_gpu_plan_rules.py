@@ -1,6 +1,9 @@
-"""Default launch plans at the edges of their rules, for FP32 products with spin
-exchange and pair hopping: 256 threads where columns are short or the grid has
-more than two blocks a CU, else 512 (the product's result does not depend on it)."""
+"""Default launch plans at the edges of their rules.
+
+FP32 products with spin exchange and pair hopping: 256 threads where columns are
+short or the grid has more than two blocks a CU, else 512 (the product's result
+does not depend on it).  One workgroup for the whole sector up to a state a
+thread, without such terms and without phonons."""
 import numpy as np
 import pytest
 
@@ -39,3 +42,31 @@ def test_threads_with_nd_terms(edx, norb, nbath, nup, ndw, threads):
         ref = fock.explicit_hamiltonian(m, nup, ndw) @ x.double().cpu().numpy()
         # FP32 terms, about 25 an element, each rounded once
         assert np.abs(y.double().cpu().numpy() - ref).max() <= 2e-6 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("norb,nbath,nup,ndw,kw,mode", [
+    (1, 0, 1, 0, {}, 0),
+    (1, 7, 2, 2, {}, 0),                              # 784 states
+    (2, 2, 3, 3, {}, 0),
+    (1, 6, 3, 3, {}, 2),                              # 1225 states
+    (1, 7, 4, 4, {}, 2),
+    (2, 2, 3, 3, dict(Jx=0.4, Jp=0.3), 2),
+    (1, 4, 2, 2, dict(nph=2, w0=0.5, g=0.3), 2),
+])
+def test_smallest_sectors_in_one_workgroup(edx, norb, nbath, nup, ndw, kw, mode, dtype):
+    import torch
+    m = inputs.make_model(norb, nbath, 2.5, Jh=0.4 if norb > 1 else 0.0, seed=92, symmetric=False, **kw)
+    S = edx.build_sector(m, nup, ndw)
+    assert edx.get_plan(S, dtype)["mode"] == mode
+    td = torch.float64 if dtype == "f64" else torch.float32
+    x = torch.as_tensor(inputs.random_vector(S.dim, seed=4), dtype=td, device="cuda")
+    y = edx.hv(S, x, torch.empty_like(x)).double().cpu().numpy()
+    if not kw.get("nph"):
+        ref = fock.explicit_hamiltonian(m, nup, ndw) @ x.double().cpu().numpy()
+        # at most 25 terms an element, each rounded once
+        assert np.abs(y - ref).max() <= (1e-14 if dtype == "f64" else 2e-6) * max(1.0, np.abs(ref).max())
+    p = S.ld
+    v = edx.pad(S, x)
+    w = edx.unpad(S, edx.hv(S, v, torch.full_like(v, float("nan")), ld=p))
+    assert np.array_equal(w.double().cpu().numpy(), y)
