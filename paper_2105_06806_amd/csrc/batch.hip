@@ -491,6 +491,10 @@ int64_t batch_wide_default() { return 1; }
 // rule (tol alone, looked at every check_every steps), so that its energy and
 // step count are those of the lanes; larger ones look at every step.
 constexpr int64_t kLaneRuleDim = 2000000;
+// Steps that such a job enqueues at least before the host looks: a look at every
+// step takes longer than the few steps after the last one (25 sectors of Ns=4 FP64,
+// check_every = 1: 2.4 ms on lanes, 2.6 a step at a time, 1.3 four at a time).
+constexpr int kMinChunk = 4;
 
 // Jobs of the whole-GPU path: D >= wide_min, and every sector with spin
 // exchange, pair hopping or phonons (the lanes implement the spin-separable
@@ -707,9 +711,13 @@ edx_status batch_run(const edx_sector* const* secs, int n, const edx_lanczos_opt
         const std::vector<int>& u = units[k];
         const edx_sector* s = secs[u[0]];
         // sectors that lanes cannot run were always checked at every step
-        const bool ends = lane_rule && !is_wide(s, kLaneRuleDim);
+        const int ends = lane_rule && !is_wide(s, kLaneRuleDim) ? std::max(1, o->check_every) : 0;
         edx_lanczos_opts qj = q;
-        if (ends) qj.rtol = 0.0;
+        if (ends > 0) {
+          qj.rtol = 0.0;
+          // the host need not look as often as the rule does
+          qj.check_every = ends * ((kMinChunk + ends - 1) / ends);
+        }
         if (u.size() > 1) {
           // one shape, several bath sets: the multi-set pass
           std::vector<const edx_sector*> g;

@@ -318,20 +318,21 @@ size_t lanczos_keep_bytes(const edx_sector* s, int vtype, int niter);
 edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts* o, void* ws,
                                      size_t ws_bytes, double* e0, void* psi0,
                                      edx_lanczos_report* rep, hipStream_t st,
-                                     bool ahead = true, bool ends = false);
+                                     bool ahead = true, int ends = 0);
 // ahead: may keep the device a chunk of steps ahead of the host's stop rule
 // (small sectors; takes a slot of pinned host memory, which a first call
 // allocates).  Not where other solves fill the device meanwhile (batch, server):
 // the chunk after the last one would be lost to them.
-// ends: the stop rule looks at the last step of each chunk only (check_every
-// steps; breakdown at every step), as the batch's lanes do.
+// ends > 0: the stop rule looks at multiples of that many steps and at the last
+// only (breakdown at every step), as the batch's lanes do; check_every says how
+// many steps are enqueued before the host looks.
 // ---- multi.hip: K bath sets of one sector shape at once (interleaved vectors)
 bool multi_supported(const edx_sector* s, int K, int vtype);
 bool multi_same_shape(const edx_sector* a, const edx_sector* b);
 size_t multi_workspace_bytes(const edx_sector* s, int K, int vtype, int niter);
 edx_status multi_ground_states(const edx_sector* const* secs, int K, const edx_lanczos_opts* o,
                                void* ws, size_t ws_bytes, edx_batch_result* res, hipStream_t st,
-                               bool ends = false);
+                               int ends = 0);
 size_t multi_hv_workspace_bytes(const edx_sector* s, int K, int vtype);
 edx_status multi_hv(const edx_sector* const* secs, int K, int vtype, const void* v, void* w,
                     void* ws, size_t ws_bytes, hipStream_t st);

@@ -695,7 +695,7 @@ size_t lanczos_workspace_bytes(const edx_sector* s, int vtype, int niter, int re
 edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts* o, void* ws,
                                      size_t ws_bytes, double* e0, void* psi0,
                                      edx_lanczos_report* rep, hipStream_t st, bool ahead,
-                                     bool ends) {
+                                     int ends) {
   const int vtype = o->vtype;
   const int niter = o->niter;
   const int reorth = o->reorth;
@@ -752,7 +752,7 @@ edx_status lanczos_ground_state_impl(const edx_sector* s, const edx_lanczos_opts
       // FP32 vectors cannot resolve energies or residuals below ~eps_32 |T|:
       // the thresholds are floored there (precision mode)
       const double floor32 = vtype == EDX_F32 ? 2.0 * 1.1920929e-7 * tnorm : 0.0;
-      bool ok = j > 0 && (!ends || j + 1 == to) &&
+      bool ok = j > 0 && (ends <= 0 || (j + 1) % ends == 0 || j + 1 == niter) &&
                 std::fabs(E - Eold) <= std::max(o->tol * std::max(1.0, std::fabs(E)), floor32);
       if (ok && o->rtol > 0.0) {
         std::vector<double> yv(j + 1);

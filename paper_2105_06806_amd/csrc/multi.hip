@@ -532,7 +532,7 @@ size_t multi_workspace_bytes(const edx_sector* s, int K, int vtype, int niter) {
 // niter), a set's result frozen at its stop while the others go on.
 edx_status multi_ground_states(const edx_sector* const* secs, int K, const edx_lanczos_opts* o,
                                void* ws, size_t ws_bytes, edx_batch_result* res, hipStream_t st,
-                               bool ends) {
+                               int ends) {
   const int vtype = o->vtype;
   const int niter = o->niter;
   const edx_sector* s0 = secs[0];
@@ -625,7 +625,7 @@ edx_status multi_ground_states(const edx_sector* const* secs, int K, const edx_l
         const double E = ritz[b].next(ta.data(), tb.data() + 1, j + 1);
         const bool bd = !(tb[j + 1] > 1e-12 * tnorm[b]);
         const double floor32 = vtype == EDX_F32 ? 2.0 * 1.1920929e-7 * tnorm[b] : 0.0;
-        bool ok = j > 0 && (!ends || j + 1 == upto) &&
+        bool ok = j > 0 && (ends <= 0 || (j + 1) % ends == 0 || j + 1 == niter) &&
                   std::fabs(E - Eold[b]) <= std::max(o->tol * std::max(1.0, std::fabs(E)), floor32);
         if (ok && o->rtol > 0.0) {
           std::vector<double> yv(j + 1);
