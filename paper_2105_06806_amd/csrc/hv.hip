@@ -1227,8 +1227,16 @@ edx_status launch_fused_k(const HvArgs<T>& a, int nblk, int nthr, size_t lds, hi
                      a, nblk, nthr, lds, st, v, w, vscale, partial, fo, fo.nd, (uint32_t)vb)
                : launch_fused_n<T, WUP, WDW, NC, true, false>(a, nblk, nthr, lds, st, v, w,
                                                               vscale, partial, fo, fo.nd);
+  // FP32 phonon slices of more than 12 MiB together: global loads, but for 16-slot
+  // rows of columns that start on 128-byte lines.  (Buffer / global loads: Ns=12 N_ph=1,
+  // 7 MB, 9.5/10.8 us dense and 9.7/10.9 us padded, N_ph=2, 10 MB, 14.5/14.4 and
+  // 13.8/14.1 us, N_ph=4, 17 MB, 24.3/21.2 and 22.1/20.8 us; Ns=14 6/7 N_ph=1, 82 MB,
+  // 108.8/86.4 and 88.3/80.5 us; Ns=15 N_ph=1 464/438 and 360/359 us; 16-slot rows:
+  // Ns=15 7/9 N_ph=1 350.9/291.6 us dense, 14 10/10 N_ph=5 35.6/37.7 us padded.)
+  const bool phbuf = buf && !(sizeof(T) == 4 && ((WUP <= 8 && WDW <= 8) || a.ld % 32 != 0) &&
+                              vb * (uint64_t)fo.pa.dph > (12ull << 20));
   if (fo.ph)
-    return buf ? launch_fused_n<T, WUP, WDW, NC, false, true, true>(
+    return phbuf ? launch_fused_n<T, WUP, WDW, NC, false, true, true>(
                      a, nblk, nthr, lds, st, v, w, vscale, partial, fo, fo.nd, (uint32_t)vb)
                : launch_fused_n<T, WUP, WDW, NC, false, true>(a, nblk, nthr, lds, st, v, w, vscale,
                                                               partial, fo, fo.nd);

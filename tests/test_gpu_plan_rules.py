@@ -70,3 +70,31 @@ def test_smallest_sectors_in_one_workgroup(edx, norb, nbath, nup, ndw, kw, mode,
     v = edx.pad(S, x)
     w = edx.unpad(S, edx.hv(S, v, torch.full_like(v, float("nan")), ld=p))
     assert np.array_equal(w.double().cpu().numpy(), y)
+
+
+@pytest.mark.parametrize("nbath,nup,ndw,nph", [
+    (11, 6, 6, 2), (11, 6, 6, 3),          # 8-slot rows below and above 12 MiB of slices
+    (13, 10, 10, 2), (13, 10, 10, 3),      # 16-slot rows
+    (13, 9, 7, 1), (10, 5, 4, 40),         # one spin's rows wide; many slices
+])
+def test_phonon_slices_by_either_load_path(edx, nbath, nup, ndw, nph):
+    """FP32 products on dense, odd and padded columns take buffer or global loads
+    by their size and stride: the same terms in the same order, so the same bits."""
+    import torch
+    m = inputs.make_model(1, nbath, 2.5, seed=93, symmetric=False, nph=nph, w0=0.5, g=0.3)
+    S = edx.build_sector(m, nup, ndw)
+    nc = S.ddw * S.dph
+    x = torch.as_tensor(inputs.random_vector(S.dim, seed=5), device="cuda").view(nc, S.dup)
+    y64 = edx.hv(S, x.reshape(-1), torch.empty(S.dim, dtype=torch.float64, device="cuda")).view(nc, S.dup)
+    ref = None
+    for ld in (S.dup, S.dup + 1, (S.dup + 31) // 32 * 32):
+        v = torch.full((nc, ld), float("nan"), dtype=torch.float32, device="cuda")
+        v[:, : S.dup] = x
+        w = torch.full((nc, ld), 5.0, dtype=torch.float32, device="cuda")
+        edx.hv(S, v.view(-1), w.view(-1), ld=ld)
+        assert torch.count_nonzero(w[:, S.dup:]) == 0
+        if ref is None:
+            ref = w[:, : S.dup].clone()
+            # FP32 against the FP64 product: about 20 terms an element
+            assert float((ref.double() - y64).abs().max()) <= 2e-6 * float(y64.abs().max())
+        assert torch.equal(w[:, : S.dup], ref), ld
