@@ -1528,11 +1528,16 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   // 6/9 4.5 -> 5.2 us) -- and for FP32 with H_nd, whose term loops diverge, except
   // longer columns in grids of two blocks a CU and less (512 -> 256 threads: 3003
   // rows of 1001 columns 23.7 -> 21.5 us, of 455 12.7 -> 16.0 us, of 91 8.5 -> 12.1 us;
-  // 924 of 924 9.3 -> 8.1 us, of 220 5.5 -> 6.5 us; 495 of 220 5.4 -> 5.2 us).
+  // 924 of 924 9.3 -> 8.1 us, of 220 5.5 -> 6.5 us; 495 of 220 5.4 -> 5.2 us), and
+  // with phonons where four such blocks a CU leave a second round less than half
+  // full (1502 blocks: 435 -> 495 us, Norb=2 369 -> 386 us; 1716 blocks 186 -> 171 us).
   const size_t lds = c * colb + ndl;
   const bool shortc = f64 ? s->dup <= (dwide ? 2048 : 1024) && (s->dup <= 512 || blocks(c) >= 256)
                           : s->dup <= 256 || (s->dup <= 2048 && blocks(c) > 512) ||
-                                (s->nd && s->dup <= 4096 && (s->dup <= 512 || blocks(c) > 512));
+                                (s->nd && s->dup <= 4096 &&
+                                 (s->dup <= 512 ||
+                                  (blocks(c) > 512 &&
+                                   !(s->dph > 1 && blocks(c) > 1024 && blocks(c) <= 1536))));
   p.col_threads = 512;
   if (lds > kLdsBytes / 2)
     p.col_threads = f64 && !wide && !s->nd ? 512 : 1024;
@@ -1542,9 +1547,13 @@ HvPlan hv_default_plan(const edx_sector* s, int vtype) {
   // product (Ns=14 FP64 86.2 -> 84.4 us against windows), beyond that inside
   // windows all XCDs walk together: over the columns in listing order, or for
   // FP32 columns of 40 KB and more over the pattern-sorted ones (Ns=16 FP32 742
-  // -> 701 us; FP64 1682 us against 1705 us sorted).
+  // -> 701 us; FP64 1682 us against 1705 us sorted).  FP32 with H_nd and phonons: sorted
+  // above 16 MiB a slice, as the terms follow the pattern (contiguous / sorted:
+  // Norb=3 8/10, 78 MB, N_ph=3 762 / 700 us; 9/11, 27 MB, N_ph=1 147 / 136 us; Norb=2
+  // 7/7, 47 MB, N_ph=4 504 / 481 us; 455 rows of 6435, 12 MB, N_ph=4 207 / 213 us).
   const size_t bytes = (size_t)s->ld * (size_t)s->ddw * sz;
   p.col_order = bytes <= ((size_t)160 << 20) ? 1 : (!f64 && !s->nd && colb >= 40 * 1024 ? 4 : 3);
+  if (!f64 && s->nd && s->dph > 1 && bytes > ((size_t)16 << 20)) p.col_order = 4;
   p.row_rows = (s->dup % 2 == 0) ? 128 : 64;
   p.row_cols = 8;
   return p;

@@ -98,3 +98,21 @@ def test_phonon_slices_by_either_load_path(edx, nbath, nup, ndw, nph):
             # FP32 against the FP64 product: about 20 terms an element
             assert float((ref.double() - y64).abs().max()) <= 2e-6 * float(y64.abs().max())
         assert torch.equal(w[:, : S.dup], ref), ld
+
+
+@pytest.mark.parametrize("nup,ndw,nph,threads,order", [
+    (6, 6, 1, 512, 4),       # 3003 x 3003: a second round of 256-thread blocks would be half empty
+    (7, 7, 1, 256, 4),       # 3432 x 3432
+    (10, 7, 1, 256, 1),      # 1001 x 3432: below 16 MiB a slice
+    (6, 6, 0, 256, 1),
+])
+def test_plans_with_nd_terms_and_phonons(edx, nup, ndw, nph, threads, order):
+    import torch
+    m = inputs.make_model(2, 6, 2.5, Jh=0.4, seed=94, symmetric=False, Jx=0.4, Jp=0.3, nph=nph, w0=0.5, g=0.3)
+    S = edx.build_sector(m, nup, ndw)
+    p = edx.get_plan(S, "f32")
+    assert (p["col_threads"], p["col_order"]) == (threads, order)
+    x = torch.rand(S.dim, device="cuda", generator=torch.Generator(device="cuda").manual_seed(6))
+    y = edx.hv(S, x, torch.empty_like(x)).clone()
+    edx.set_plan(S, "f32", col_threads=512, col_order=0)
+    assert torch.equal(edx.hv(S, x, torch.empty_like(x)), y)
